@@ -39,7 +39,10 @@ template <>
 struct Mth<float> {
     __device__ static float exp_(float x) { return __builtin_amdgcn_exp2f(x * 1.44269504088896341f); }
     __device__ static float log_(float x) { return __builtin_amdgcn_logf(x) * 0.693147180559945309f; }
+    // log2 for the guess of a bin, and how far off the guess may be in bins
+    // where s bins span a factor of two of the argument
     __device__ static float log2_(float x) { return __builtin_amdgcn_logf(x); }
+    __device__ static float guess_tol(float) { return 1e-4f; }
     __device__ static float sqrt_(float x) { return __builtin_amdgcn_sqrtf(x); }
     // log(1 + x) by Goldberg's method (What every computer scientist should
     // know about floating-point arithmetic, 1991): with u = 1 + x rounded,
@@ -57,7 +60,14 @@ template <>
 struct Mth<double> {
     __device__ static double exp_(double x) { return exp(x); }
     __device__ static double log_(double x) { return log(x); }
-    __device__ static double log2_(double x) { return log2(x); }
+    // log2 for the guess of a bin (which decides nothing within guess_tol of an
+    // edge): the exponent, and the FP32 logarithm of the mantissa, within 2e-7.
+    // The library's log2 took about 60 FP64 instructions, four times per step.
+    __device__ static double log2_(double x) {
+        return (double)(__builtin_amdgcn_logf((float)__builtin_amdgcn_frexp_mant(x)) +
+                        (float)__builtin_amdgcn_frexp_exp(x));
+    }
+    __device__ static double guess_tol(double s) { return fmax(1e-4, 1e-5 * s); }
     __device__ static double sqrt_(double x) { return sqrt(x); }
     __device__ static double log1p_(double x) { return log1p(x); }
     __device__ static double rcp_(double x) { return 1.0 / x; }
@@ -230,17 +240,17 @@ __device__ __forceinline__ int refine_bin(T v, const T* e, int n, T g) {
 }
 
 // Bin of v, or -1 outside [lo, hi). The arithmetic position g of v in bin
-// units is accurate to a few 1e-6, so a point more than 1e-4 of a bin from
-// both edges is in bin floor(g); only points closer to an edge are compared
-// with the stored edges.
+// units is accurate to a few 1e-6, so a point more than tol (1e-4) of a bin
+// from both edges is in bin floor(g); only points closer to an edge are
+// compared with the stored edges.
 template <typename T>
-__device__ __forceinline__ int bin_of(T v, const T* e, int n, T g, T lo, T hi) {
-    if (!(v >= lo) || !(v < hi)) return -1;
-    const T gc = fmin(fmax(g, T(0)), T(n));
-    const int k = min((int)gc, n - 1);
+__device__ __forceinline__ int bin_of(T v, const T* e, int n, T g, T lo, T hi, T tol = T(1e-4)) {
+    const bool in = v >= lo && v < hi;
+    int k = min(max((int)g, 0), n - 1);
     const T fr = g - T(k);
-    if (fr > T(1e-4) && fr < T(1) - T(1e-4)) return k;
-    return refine_bin<T>(v, e, n, g);
+    // one branch, rarely taken: the lanes outside the range carry along
+    if (in && !(fr > tol && fr < T(1) - tol)) k = refine_bin<T>(v, e, n, g);
+    return in ? k : -1;
 }
 
 // kinds of kinematic observables, fixed at compile time in k_step; the bit
@@ -253,7 +263,26 @@ enum : int { kKinNone = 0, kKinV2 = 1, kKinGH4 = 2, kKinGHN = 3, kKinLOSVD = 4, 
 template <int KIN>
 struct KinSlots {
     static constexpr int n = ((KIN & 7) == kKinGH4) ? 4 : ((KIN & 7) == kKinGHN) ? kMaxGH : 1;
+    // a particle has all n entries or none
+    static constexpr bool all = (KIN & 7) != kKinGHN;
 };
+
+// f(m) for every kinematic entry m < kn of a particle: behind one branch where
+// it has all or none (a branch per entry made their LDS reads wait in turn)
+template <int KIN, typename F>
+__device__ __forceinline__ void each_entry(int kn, F&& f) {
+    constexpr int NS = KinSlots<KIN>::n;
+    if constexpr (KinSlots<KIN>::all) {
+        if (kn > 0) {
+#pragma unroll
+            for (int m = 0; m < NS; ++m) f(m);
+        }
+    } else {
+#pragma unroll
+        for (int m = 0; m < NS; ++m)
+            if (m < kn) f(m);
+    }
+}
 
 // Non-zero kernels K_j of one phase-space point: the radial bin jr (K = 1),
 // or with a_lm the mesh interval jr with the cloud-in-cell weight g of its
@@ -374,7 +403,8 @@ __device__ __forceinline__ Kern<T, KIN> kernels(const Hot<T>& h, const Tabs<T, A
     Kern<T, KIN> o;
     const T R2 = x * x + y * y;
     const T r2 = R2 + z * z;
-    o.jr = bin_of<T>(r2, tb.re2, h.n_r, (Mth<T>::log2_(r2) - h.lr0) * h.lrs, h.r2lo, h.r2hi);
+    o.jr = bin_of<T>(r2, tb.re2, h.n_r, (Mth<T>::log2_(r2) - h.lr0) * h.lrs, h.r2lo, h.r2hi,
+                    Mth<T>::guess_tol(h.lrs));
     if ((KIN & kKinAlm) && o.jr >= 0) {
         // cloud-in-cell weight of the inner mesh radius (linear in r) and the
         // direction; r >= r_min > 0 here
@@ -392,7 +422,8 @@ __device__ __forceinline__ Kern<T, KIN> kernels(const Hot<T>& h, const Tabs<T, A
     o.jk = -1;
     o.kn = 0;
     if (KK == kKinNone) return o;
-    const int p = bin_of<T>(R2, tb.Re2, h.n_R, (Mth<T>::log2_(R2) - h.lR0) * h.lRs, h.R2lo, h.R2hi);
+    const int p = bin_of<T>(R2, tb.Re2, h.n_R, (Mth<T>::log2_(R2) - h.lR0) * h.lRs, h.R2lo, h.R2hi,
+                            Mth<T>::guess_tol(h.lRs));
     if (p < 0) return o;
     const int base = h.jk0 + p * h.nk;
     if (KK == kKinV2) {
@@ -470,6 +501,44 @@ __device__ __forceinline__ T accel_of(const Hot<T>& h, T r) {
         s += h.GMn * m * Mth<T>::rcp_(r * r * r);
     }
     return s;
+}
+
+// kick of one step at (x, y, z) in the analytic potential (without the
+// Hernquist stars for STARS = false)
+template <typename T, bool STARS>
+__device__ __forceinline__ void kick(const Hot<T>& h, T x, T y, T z, T& vx, T& vy, T& vz) {
+    const T R2 = x * x + y * y, z2 = z * z;
+    T s = accel_of<T, STARS>(h, Mth<T>::sqrt_(R2 + z2)) * h.dt;
+    T sz = s;
+    if (h.halo) {  // logarithmic halo: -v0^2 (x, y, z/q^2) / (r0^2 + R^2 + z^2/q^2)
+        asm volatile("");  // a branch (uniform over the fit), not both sides and a select
+        const T sh = h.hv2 * Mth<T>::rcp_(h.hr02 + R2 + z2 * h.hiq2) * h.dt;
+        s += sh;
+        sz += sh * h.hiq2;
+    }
+    vx -= s * x;
+    vy -= s * y;
+    vz -= sz * z;
+}
+
+// The weight u (prior uh) after the force of change (eq. modFOC) of a particle
+// with kernels kk, with the force table tb.rp of the last residuals.
+template <typename T, typename A, int KIN>
+__device__ __forceinline__ T corrected_weight(const Hot<T>& h, const Tabs<T, A>& tb,
+                                              const Kern<T, KIN>& kk, T u, T uh) {
+    T chi = T(0);
+    if ((KIN & kKinAlm) && kk.jr >= 0) {
+        const int b0 = kk.jr * h.nlm, b1 = b0 + h.nlm;
+        const T g1 = T(1) - kk.g;
+        ylm_walk(h.l_max, kk.ct, kk.st, kk.cp, kk.sp, [&](int lm, T Y) {
+            chi += Y * (kk.g * tb.rp[b0 + lm] + g1 * tb.rp[b1 + lm]);
+        });
+    } else if (kk.jr >= 0) {
+        chi = tb.rp[kk.jr];
+    }
+    each_entry<KIN>(kk.kn, [&](int m) { chi += kk.k[m] * tb.rp[kk.jk + m]; });
+    const T lr = Mth<T>::log_(u * Mth<T>::rcp_(uh));
+    return u * Mth<T>::exp_(-h.foc_mu * (lr + h.foc_cs) - chi);
 }
 
 // Prior cell (k, l) -> k n_x + l of one phase-space point.
@@ -594,15 +663,14 @@ __device__ __forceinline__ void deposit(const Hot<T>& h, const Tabs<T, float>& t
 template <typename T, int KIN>
 __device__ __forceinline__ void deposit(const Hot<T>& h, const Tabs<T, double>& tb,
                                         const Kern<T, KIN>& kk, T u, int priv) {
-    constexpr int NS = KinSlots<KIN>::n;
     const int kp = h.kp;
     const T w = u * h.w0;
     if ((KIN & kKinAlm) && kk.jr >= 0)
         deposit_alm(h, kk, w, [&](int j, T val) { atomicAdd(&tb.sum[j * kp + priv], (double)val); });
     if (!(KIN & kKinAlm) && kk.jr >= 0) atomicAdd(&tb.sum[kk.jr * kp + priv], (double)w);
-#pragma unroll
-    for (int m = 0; m < NS; ++m)
-        if (m < kk.kn) atomicAdd(&tb.sum[(kk.jk + m) * kp + priv], (double)(w * kk.k[m]));
+    each_entry<KIN>(kk.kn, [&](int m) {
+        atomicAdd(&tb.sum[(kk.jk + m) * kp + priv], (double)(w * kk.k[m]));
+    });
 }
 
 

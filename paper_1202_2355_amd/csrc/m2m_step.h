@@ -181,42 +181,16 @@ __device__ __forceinline__ void step_tile(const FitDev& fd, const Tile& tl, int3
         // the prior of the particle's cell at the last refresh (same
         // phase-space point: no push in between)
         if (assign) uh = ucell[min((int)CI[i], C - 1)];
-        if (correct) {
-            // force of change at z^k with the residuals of step k
-            const Kern<T, KIN> kk = kernels<T, A, KIN>(h, tb, x, y, z, vz);
-            T chi = T(0);
-            if ((KIN & kKinAlm) && kk.jr >= 0) {
-                const int b0 = kk.jr * h.nlm, b1 = b0 + h.nlm;
-                const T g1 = T(1) - kk.g;
-                ylm_walk(h.l_max, kk.ct, kk.st, kk.cp, kk.sp, [&](int lm, T Y) {
-                    chi += Y * (kk.g * tb.rp[b0 + lm] + g1 * tb.rp[b1 + lm]);
-                });
-            } else if (kk.jr >= 0) {
-                chi = tb.rp[kk.jr];
-            }
-#pragma unroll
-            for (int m = 0; m < KinSlots<KIN>::n; ++m)
-                if (m < kk.kn) chi += kk.k[m] * tb.rp[kk.jk + m];
-            const T lr = Mth<T>::log_(u * Mth<T>::rcp_(uh));
-            u = u * Mth<T>::exp_(-h.foc_mu * (lr + h.foc_cs) - chi);
-        }
+        // force of change at z^k with the residuals of step k
+        if (correct)
+            u = corrected_weight<T, A, KIN>(h, tb, kernels<T, A, KIN>(h, tb, x, y, z, vz), u, uh);
         if (push) {
             x += h.hdt * vx;
             y += h.hdt * vy;
             z += h.hdt * vz;
-            const T R2 = x * x + y * y, z2 = z * z;
             // with the self-consistent potential the expansion takes the
             // place of the Hernquist stars
-            T s = accel_of<T, (KIN & kKinScf) == 0>(h, Mth<T>::sqrt_(R2 + z2)) * h.dt;
-            T sz = s;
-            if (h.halo) {  // logarithmic halo: -v0^2 (x, y, z/q^2) / (r0^2 + R^2 + z^2/q^2)
-                const T sh = h.hv2 * Mth<T>::rcp_(h.hr02 + R2 + z2 * h.hiq2) * h.dt;
-                s += sh;
-                sz += sh * h.hiq2;
-            }
-            vx -= s * x;
-            vy -= s * y;
-            vz -= sz * z;
+            kick<T, (KIN & kKinScf) == 0>(h, x, y, z, vx, vy, vz);
             if (KIN & kKinScf) {
                 T gx, gy, gz;
                 // the common degrees with their loops unrolled
