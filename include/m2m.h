@@ -256,7 +256,16 @@ m2m_status m2m_set_targets(m2m_ctx* ctx, int32_t J, const double* Y, const doubl
                            const double* V_p, const double* sigma_p);
 
 /* Enqueue n_steps M2M steps (asynchronous). correct = 0 runs them without
- * weight correction (relaxation, Sec. 4.1): push, deposit and smoothing. */
+ * weight correction (relaxation, Sec. 4.1): push, deposit and smoothing.
+ * Fits of at most 1024 observables and 2^22 particles, with radial bins in an
+ * analytic potential, no prior smoothing, no refresh on every single step and
+ * FP64 bins (M2M_DEPOSIT_F64), take up to 256 steps per launch: one kernel
+ * whose blocks exchange their sums. Its blocks wait for each other, so runs of
+ * fits on different streams of one device are ordered one after another, and
+ * while any fit is in a batch, or if the stream is being captured, the steps
+ * are launched one by one (two kernels each) as for all other fits. A launch
+ * whose blocks do not all start within 50 ms (the compute units are held by
+ * other work) is done by one block alone. */
 m2m_status m2m_step(m2m_ctx* ctx, int32_t n_steps, int32_t correct);
 
 /* Recompute the cell priors from the current state now (Sec. 2.3.1) and
@@ -333,7 +342,7 @@ m2m_status m2m_get_state(m2m_ctx* ctx, void* host_blob, size_t* bytes);
 m2m_status m2m_set_state(m2m_ctx* ctx, const void* host_blob, size_t bytes);
 
 /* Timing by HIP events on the context's stream. With r = ceil(n_steps / 32)
- * (n_steps 1..4096), runs r graphs of 32 steps as m2m_step does, then r
+ * (n_steps 1..4096), runs r graphs of 32 steps of two kernels each, then r
  * graphs of 32 steps each followed by one more finalize reduction in a
  * measuring mode that changes no state: 64 r steps in all, which advance
  * the fit. With S and S2 the mean times per step of the two runs,
@@ -368,8 +377,9 @@ m2m_status m2m_destroy(m2m_ctx* ctx);
  * calling thread's last failed m2m_observe_noalloc. */
 const char* m2m_last_error(const m2m_ctx* ctx);
 
-/* Launch shape of the fused step kernel for contexts created afterwards and
- * for batches rebuilt afterwards: threads per block (256, 512 or 1024) and
+/* Launch shape of the fused step kernel (not of the kernel that takes several
+ * steps per launch, see m2m_step) for contexts created afterwards and for
+ * batches rebuilt afterwards: threads per block (256, 512 or 1024) and
  * tiles (blocks) per compute unit (1..16); each thread handles one particle
  * at a time. EINVAL otherwise. Chosen by the package's autotuner. */
 m2m_status m2m_set_launch(int32_t block, int32_t tiles_per_cu);
@@ -417,7 +427,9 @@ int32_t m2m_get_deposit_mode(void);
  * with FP64 bins (M2M_DEPOSIT_F64) and observables without a_lm
  * coefficients, Gauss-Hermite moments beyond h_4 or the self-consistent
  * potential, below 2^30 particles; other fits and batches take contiguous
- * ranges. The sums are the same up to rounding order. EINVAL otherwise. */
+ * ranges. The sums are the same up to rounding order. A fit created with 0 or
+ * 1 takes every step by the step kernel (one step per launch). EINVAL
+ * otherwise. */
 m2m_status m2m_set_interleave(int32_t mode);
 int32_t m2m_get_interleave(void);
 

@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <atomic>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
@@ -39,6 +40,7 @@ int g_groups = 2;           // groups of a batch of two or more fits (1 or 2)
 int g_batch_graphs = 0;     // batches replay captured graphs (1) or launch directly (0)
 int g_deposit = M2M_DEPOSIT_F64;
 int g_kpriv_cap = 0;  // most private bin copies per block (0: as many as fit, at most 8)
+std::atomic<int> g_batched{0};  // fits in batches now (any batch of the process)
 int g_interleave = -1;  // tiles of one fit: contiguous (0), interleaved (1), by state size (-1)
 
 size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
@@ -299,6 +301,7 @@ struct WsLayout {
     size_t st, fd, tiles, jobs, redge2, rmesh, Redge2, vedge, Vp, isp, rp, ucell, lctab, cidx;
     size_t cdata, gprior, scf_rho, scf_sum, scf_tab, sm_basis;
     size_t Y, sigma, yv, ytil, delta, obs, hist, chi2p, partials, total;
+    size_t run, run_sync, run_rows, run_res, run_cell, run_parts;  // run kernel: exchange areas
     int seg_cap, row_len, nbj, ncj, npj, J, C, P;  // P: interval sums of the expansion
 };
 
@@ -316,6 +319,18 @@ int seg_cap_of(int64_t n, int row_len) {
     cap = std::max<int64_t>(1, std::min<int64_t>(cap, 4096));
     cap = std::min<int64_t>(cap, std::max<int64_t>(1, n / kSegAlign));
     return (int)cap;
+}
+
+// Most observables and particles of fits that step by the run kernel.
+constexpr int kRunMaxJ = 1024;
+constexpr int64_t kRunMaxN = int64_t(1) << 22;
+
+// The run kernel is built for fits with radial bins in an analytic potential
+// and no smoothing of the priors. A refresh on every step is left out too: the
+// rows of two refreshes in a row would share one buffer.
+bool run_kind(const m2m_obs_layout& L, const m2m_params& P, int64_t n) {
+    return L.dens == M2M_DENS_BINS && P.scf_nr == 0 && !P.smooth && P.prior_every != 1 &&
+           num_obs(L) <= kRunMaxJ && n <= kRunMaxN;
 }
 
 // cell_index = false: no per-particle cell index (observation only)
@@ -369,6 +384,15 @@ WsLayout plan(const m2m_obs_layout& L, const m2m_params& P, int64_t n, bool f64,
     w.scf_tab = take(8 * (size_t)std::max(w.P, 1));
     // eigendecomposition of the smoothing penalty (both L_z halves share it)
     w.sm_basis = take(P.smooth ? 8 * smooth_basis_len(P.n_E, P.n_x) : 8);
+    w.run = o;
+    if (cell_index && run_kind(L, P, n)) {
+        const size_t jobs = (size_t)(w.J + kRunCols - 1) / kRunCols, vw = f64 ? 16 : 8;
+        w.run_sync = take(sizeof(RunSync));
+        w.run_rows = take(16 * (size_t)run_shape(n, f64, w.J).blocks * (size_t)(w.J + 2 * w.C));
+        w.run_res = take(vw * (size_t)w.J);
+        w.run_cell = take(vw * (size_t)w.C);
+        w.run_parts = take(16 * jobs * (size_t)kRunMaxSteps);
+    }
     w.total = o;
     return w;
 }
@@ -489,6 +513,11 @@ struct m2m_ctx {
     bool acc64 = true;
     bool wt = false;  // write-through particle stores (kModeWriteThrough)
     bool il = false;  // interleaved tiles in the step kernel (kModeInterleave)
+    int dev = 0;      // the device the context was created on
+    bool run = false; // steps by the run kernel (see use_run)
+    RunShape run_sh{};
+    RunArgs run_args{};
+    uint32_t run_tag = 0, run_start = 0;  // tag of the last step run so; blocks started so far
     hipGraphExec_t graph_prof = nullptr;  // steps with an extra measuring reduction
     bool targets = false;
     bool ytil_init = false;
@@ -613,12 +642,17 @@ m2m_status flush_assign(m2m_ctx* c) {
     return M2M_OK;
 }
 
+m2m_status error_status(m2m_ctx* c, const FitState& s) {
+    if (s.error & 2) return fail(c, M2M_EDEVICE, "a run of steps did not complete on the device");
+    if (s.error & 1) return fail(c, M2M_ENONFINITE, "chi^2 became non-finite");
+    return M2M_OK;
+}
+
 m2m_status check_error(m2m_ctx* c) {
     FitState s{};
     m2m_status r = read_state(c, s);
     if (r != M2M_OK) return r;
-    if (s.error & 1) return fail(c, M2M_ENONFINITE, "chi^2 became non-finite");
-    return M2M_OK;
+    return error_status(c, s);
 }
 
 // Rebuild the self-consistent potential from the current state: the step
@@ -639,6 +673,62 @@ hipError_t launch_one_step(m2m_ctx* c, hipStream_t s) {
                                s);
     if (e == hipSuccess) e = launch_finalize1(c->f64, c->fd, c->n_tiles, kModeStep, s);
     return e;
+}
+
+// ---- run kernel -------------------------------------------------------------
+// A run of one fit wants every compute unit to itself: its blocks wait for
+// each other. Runs of different streams are therefore put one after another
+// (the second stream waits for the first at the time of its launch); the
+// stream of the last run on a device is remembered until its context goes.
+struct RunGate {
+    std::mutex mu;
+    m2m_ctx* owner = nullptr;
+    hipStream_t stream = nullptr;
+    hipEvent_t ev = nullptr;
+};
+constexpr int kRunDevices = 64;
+RunGate g_run_gate[kRunDevices];
+
+bool capturing(hipStream_t s) {
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    return hipStreamIsCapturing(s, &st) != hipSuccess || st != hipStreamCaptureStatusNone;
+}
+
+// Steps by the run kernel, if the fit's kind has it. Not while any fit is in a
+// batch (the batch's kernels hold compute units that the run would wait for),
+// and not into a stream that is being captured (a replay would repeat the tags
+// of its exchange): those take the step and finalize kernels.
+bool use_run(const m2m_ctx* c) {
+    return c->run && g_batched.load(std::memory_order_relaxed) == 0 && !capturing(c->stream);
+}
+
+m2m_status launch_run(m2m_ctx* c, int32_t n_steps, int32_t correct) {
+    if (c->run_tag > 0xffffffffu - (uint32_t)kRunMaxSteps || c->run_start > 0x40000000u) {
+        // the counters start anew: no word of the exchange may carry an old tag
+        M2M_HIP(c, hipMemsetAsync(c->ws + c->w.run, 0, c->w.total - c->w.run, c->stream));
+        c->run_tag = 0;
+        c->run_start = 0;
+    }
+    RunArgs a = c->run_args;
+    a.n_steps = n_steps;
+    a.correct = correct ? 1 : 0;
+    a.tag0 = c->run_tag;
+    a.start0 = c->run_start;
+    RunGate& g = g_run_gate[c->dev];
+    std::lock_guard<std::mutex> lock(g.mu);
+    if (g.owner && g.stream != c->stream && !capturing(g.stream)) {
+        if (!g.ev) M2M_HIP(c, hipEventCreateWithFlags(&g.ev, hipEventDisableTiming));
+        M2M_HIP(c, hipEventRecord(g.ev, g.stream));
+        M2M_HIP(c, hipStreamWaitEvent(c->stream, g.ev, 0));
+    }
+    M2M_HIP(c, (c->f64 ? launch_run_f64 : launch_run_f32)(c->run_sh.block, c->kin, c->fd, a,
+                                                         c->run_sh.blocks,
+                                                         c->lds + (size_t)a.keep_bytes, c->stream));
+    g.owner = c;
+    g.stream = c->stream;
+    c->run_tag += (uint32_t)n_steps;
+    c->run_start += (uint32_t)c->run_sh.blocks;
+    return M2M_OK;
 }
 
 // Capture n repetitions of body(stream) on the capture stream, instantiate
@@ -908,6 +998,28 @@ m2m_status m2m_create(const m2m_potential* pot, const m2m_obs_layout* layout,
     c->st = f.st;
     c->tiles = reinterpret_cast<Tile*>(b + w.tiles);
     c->jobs = reinterpret_cast<FinJob*>(b + w.jobs);
+    // ---- run kernel: one block of it per compute unit has to fit
+    if (hipGetDevice(&c->dev) != hipSuccess) return bail(M2M_EDEVICE);
+    c->run_sh = run_shape(n, c->f64, w.J);
+    c->run = w.total > w.run && c->acc64 && g_interleave < 0 && c->dev >= 0 && c->dev < kRunDevices &&
+             c->run_sh.blocks <= n_cus() && c->lds + kRunStaticLds <= max_lds();
+    if (c->run) {
+        c->run_args.n_jobs = (w.J + kRunCols - 1) / kRunCols;
+        c->run_args.n_cell_jobs = (w.C + kRunCols - 1) / kRunCols;
+        // the kernels kept in LDS between steps (Kept in m2m_run.h), if they fit
+        const int64_t per = (int64_t)c->run_sh.blocks * c->run_sh.block;
+        const int64_t slots = (n + per - 1) / per * c->run_sh.block;
+        const int vals = c->lay.kin != M2M_KIN_GH ? 0 : (c->lay.gh_nmax == 4 ? 4 : kMaxGH);
+        const size_t kept = (size_t)slots * (vals * (c->f64 ? 8u : 4u) + 4u);
+        c->run_args.keep_at = (int32_t)c->lds;
+        c->run_args.keep_bytes =
+            c->lds + kept + kRunStaticLds <= max_lds() ? (int32_t)kept : 0;
+        c->run_args.sync = reinterpret_cast<RunSync*>(b + w.run_sync);
+        c->run_args.rows = reinterpret_cast<uint64_t*>(b + w.run_rows);
+        c->run_args.res = reinterpret_cast<uint64_t*>(b + w.run_res);
+        c->run_args.cell = reinterpret_cast<uint64_t*>(b + w.run_cell);
+        c->run_args.parts = reinterpret_cast<uint64_t*>(b + w.run_parts);
+    }
 
     // ---- tables
     std::vector<double> lct(kLcTable);
@@ -1016,6 +1128,12 @@ m2m_status m2m_step(m2m_ctx* c, int32_t n_steps, int32_t correct) {
     if (n_steps < 0) return fail(c, M2M_EINVAL, "n_steps must be >= 0");
     if (n_steps == 0) return M2M_OK;
     c->may_assign = true;
+    if (use_run(c)) {
+        for (int32_t done = 0; done < n_steps; done += kRunMaxSteps)
+            if (m2m_status s = launch_run(c, std::min(n_steps - done, kRunMaxSteps), correct); s != M2M_OK)
+                return s;
+        return M2M_OK;
+    }
     M2M_HIP(c, launch_poke(c->st, n_steps, correct ? 1 : 0, c->stream));
     const int full = n_steps / kGraphSteps, rem = n_steps % kGraphSteps;
     if (full > 0) {
@@ -1098,8 +1216,7 @@ m2m_status m2m_get_observables(m2m_ctx* c, double* y, double* y_tilde, double* d
     if (y_tilde) M2M_HIP(c, copy_sync(c->stream, y_tilde, c->fd.ytil, 8 * J, hipMemcpyDeviceToHost));
     if (delta) M2M_HIP(c, copy_sync(c->stream, delta, c->fd.delta, 8 * J, hipMemcpyDeviceToHost));
     if (chi2) *chi2 = st.chi2;
-    if (st.error & 1) return fail(c, M2M_ENONFINITE, "chi^2 became non-finite");
-    return M2M_OK;
+    return error_status(c, st);
 }
 
 m2m_status m2m_get_chi2_history(m2m_ctx* c, double* out, int32_t max, int32_t* n_out) {
@@ -1308,6 +1425,11 @@ m2m_status m2m_destroy(m2m_ctx* c) {
     if (!c) return M2M_EINVAL;
     if (c->batch) return fail(c, M2M_ESTATE, "fit is in a batch");
     (void)hipStreamSynchronize(c->stream);
+    if (c->run) {
+        RunGate& g = g_run_gate[c->dev];
+        std::lock_guard<std::mutex> lock(g.mu);
+        if (g.owner == c) g.owner = nullptr;  // its runs have ended
+    }
     if (c->idle_ev) {
         // the batch runs that may still read the fit have ended
         (void)hipEventSynchronize(c->idle_ev);
@@ -1385,7 +1507,8 @@ struct m2m_batch {
 namespace {
 
 size_t footprint(const m2m_ctx* c) {
-    return (size_t)c->n * 8 * (c->f64 ? 8 : 4) + c->w.total;
+    // without the run kernel's areas, which no batched step uses
+    return (size_t)c->n * 8 * (c->f64 ? 8 : 4) + c->w.run;
 }
 
 hipError_t grow(void** p, size_t* cap, size_t need) {
@@ -1595,6 +1718,7 @@ hipError_t run_set(const m2m_batch* b, const LaunchSet& L, int steps, hipStream_
 // forget it, so that no later poll reads the context.
 hipError_t retire(m2m_batch* b, m2m_ctx* c) {
     c->batch = nullptr;
+    --g_batched;
     c->may_assign = true;  // its batched steps may have refreshed the priors
     for (auto& v : b->snap_fits)
         for (m2m_ctx*& x : v)
@@ -1717,6 +1841,7 @@ m2m_status m2m_batch_admit(m2m_batch* b, m2m_ctx* c, int32_t n_steps) {
     b->kin = c->kin;
     b->fits.push_back(c);
     c->batch = b;
+    ++g_batched;
     b->dirty = true;
     return M2M_OK;
 }
@@ -1877,6 +2002,7 @@ m2m_status m2m_batch_destroy(m2m_batch* b) {
     if (!b) return M2M_EINVAL;
     (void)hipStreamSynchronize(b->stream);
     for (m2m_ctx* c : b->fits) c->batch = nullptr;
+    g_batched -= (int)b->fits.size();
     free_set(b->all);
     for (int g = 0; g < kGroups; ++g) {
         free_set(b->grp[g]);

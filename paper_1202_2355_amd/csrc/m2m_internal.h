@@ -165,6 +165,62 @@ struct FinJob {
     int32_t n_tiles;  // rows of the fit to reduce
 };
 
+// ---- run kernel (m2m_run.h): several steps of one fit in one launch ---------
+constexpr int kRunCols = 16;        // columns per reduction job
+constexpr int kRunMaxSteps = 256;   // steps per launch
+constexpr int kRunMaxBlocks = 256;  // one block per compute unit
+constexpr size_t kRunStaticLds = 2 * 16 * kRunCols * 8 + 256;  // its static LDS (16 waves), rounded up
+constexpr uint64_t kRunStart = 5000000;   // 50 ms (100 MHz counter): see all_running
+constexpr uint64_t kRunWait = 1000000000; // 10 s: a wait within a run that failed
+
+// counters of the launches of a context
+struct RunSync {
+    uint32_t start;  // blocks that have started, over all launches (kRunOff: this one is called off)
+    uint32_t left;   // blocks that have left a launch that was called off
+    uint32_t dead;   // a wait ended without its value
+};
+
+// Exchange areas in the fit's workspace: 64-bit words of 32 data and 32 tag
+// bits (m2m_run.h).
+struct RunArgs {
+    int32_t n_steps, correct;
+    uint32_t tag0;             // the steps' tags are tag0 + 1 .. tag0 + n_steps
+    uint32_t start0;           // sync->start before this launch
+    int32_t keep_at, keep_bytes;  // LDS offset and size of the kept kernels (0: not kept)
+    int32_t n_jobs, n_cell_jobs;  // ceil(J / kRunCols), ceil(C / kRunCols)
+    RunSync* sync;
+    uint64_t *rows;   // blocks x (J + 2 C) sums, 2 words each
+    uint64_t *res;    // J entries of the force table, 1 word (FP32) or 2
+    uint64_t *cell;   // C cell priors, the same
+    uint64_t *parts;  // kRunMaxSteps x n_jobs parts of chi^2, 2 words each
+};
+
+// Blocks and threads per block of a run over n particles of J observables: at
+// most one block per compute unit, and at least one per reduction job. FP32:
+// 8 waves a block up to 2^15 particles, above that 16. FP64: 8 waves (16 would
+// leave 128 registers a lane and spill 45 to 65), half of them idle up to 2^15
+// particles. Measured us a step, Gauss-Hermite (blocks x threads): FP32 16384
+// particles 32x512 4.8, 16x1024 5.7, 64x256 5.7, 256x256 9.8; 131072 128x1024
+// 6.0, 256x1024 6.5, 256x512 7.5; 10^6 256x1024 12.3, 256x512 17.8. FP64 16384
+// 64x512 6.0, 32x512 6.2, 256x256 10.8; 65536 128x512 7.2, 256x512 8.4.
+struct RunShape {
+    int block, blocks;
+};
+inline RunShape run_shape(int64_t n, bool f64, int J) {
+    const bool small = n <= 32768;
+    const int block = small || f64 ? 512 : 1024, per = f64 && small ? 256 : block;
+    const int64_t jobs = (J + kRunCols - 1) / kRunCols;
+    int64_t b = (n + per - 1) / per;
+    b = b > 16 ? b : 16;
+    b = b > jobs ? b : jobs;
+    return RunShape{block, (int)(b < kRunMaxBlocks ? b : kRunMaxBlocks)};
+}
+
+hipError_t launch_run_f32(int block, int kin, const FitDev& fd, const RunArgs& ra, int blocks,
+                          size_t lds, hipStream_t s);
+hipError_t launch_run_f64(int block, int kin, const FitDev& fd, const RunArgs& ra, int blocks,
+                          size_t lds, hipStream_t s);
+
 // ---- launchers (m2m_kernels.hip) ------------------------------------------
 // kin: kinematic kind of every fit in the launch, from kin_class()
 hipError_t launch_step(bool f64, bool acc64, int block, int kin, const FitDev* fits,

@@ -1,0 +1,536 @@
+// The run kernel: several whole steps of one fit in one launch, for fits of
+// few observables (the rule is run_shape in m2m_internal.h). A block keeps
+// its particles for the whole launch (in registers where every thread has at
+// most one, else in its L2) and the blocks exchange only the tile sums: the
+// force of change of step k + 1 needs the residuals of step k, and nothing
+// else crosses blocks.
+#pragma once
+
+#include "m2m_device.h"
+
+namespace m2m {
+namespace {
+
+// The thread index as a value that the compiler knows nothing of: what is
+// addressed by it is addressed anew on every step, instead of holding address
+// registers through the particle loop (the FP64 kernels spilled 50 to 75).
+__device__ __forceinline__ int thread_here() {
+    int t = threadIdx.x;
+    asm volatile("" : "+v"(t));
+    return t;
+}
+
+// Particle i of an array: the byte offset in 32 unsigned bits, so that the
+// access takes the array's base in scalar registers and no 64-bit address is
+// formed per access (n is at most kRunMaxN).
+template <typename V>
+__device__ __forceinline__ G<V> elem(G<V> base, uint32_t i) {
+    return (G<V>)((G<char>)base + i * (uint32_t)sizeof(V));
+}
+
+// -------------------------------------------------------------- exchange ----
+// Every 64-bit word that blocks exchange carries 32 bits of data and the
+// 32-bit tag of the step it belongs to, and is written and read by relaxed
+// agent-scope atomics (which bypass the caches that are not shared). A reader
+// waits for the tag, so no word needs an order to any other and no fence is
+// taken: an agent-scope release would write back an L2 full of particles.
+// The tags of a context never repeat (the host counts them).
+//
+// Measured between 256 blocks of 1024 threads without particles: 3.6 us a
+// step for 160 columns this way (owners of 16 neighbouring columns, so that a
+// row's entries for one owner are four 64-byte lines), 5.4 with one column per
+// owner, 4.9 with rows, a flag each and 8-byte entries, 10.5 with FP64 atomics
+// into one vector; the two kernels of a step launched apart pay 7-9 us for
+// the finalize, the launch gaps and the tile set-up.
+using Word = uint64_t;
+
+__device__ __forceinline__ void put_word(G<Word> p, Word v) {
+    __hip_atomic_store((Word*)p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ Word get_word(G<const Word> p) {
+    return __hip_atomic_load((const Word*)p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ bool tagged(Word w, uint32_t tag) { return (uint32_t)(w >> 32) == tag; }
+
+// words of one value
+template <typename V>
+struct Words;
+template <>
+struct Words<float> {
+    static constexpr int n = 1;
+    __device__ static void put(G<Word> p, float v, uint32_t tag) {
+        put_word(p, (Word)__float_as_uint(v) | ((Word)tag << 32));
+    }
+    __device__ static bool get(G<const Word> p, uint32_t tag, float& v) {
+        const Word a = get_word(p);
+        v = __uint_as_float((uint32_t)a);
+        return tagged(a, tag);
+    }
+};
+template <>
+struct Words<double> {
+    static constexpr int n = 2;
+    __device__ static void put(G<Word> p, double v, uint32_t tag) {
+        const Word b = (Word)__double_as_longlong(v);
+        put_word(p, (b & 0xffffffffull) | ((Word)tag << 32));
+        put_word(p + 1, (b >> 32) | ((Word)tag << 32));
+    }
+    __device__ static bool get(G<const Word> p, uint32_t tag, double& v) {
+        const Word a = get_word(p), b = get_word(p + 1);
+        v = __longlong_as_double((long long)((a & 0xffffffffull) | (b << 32)));
+        return tagged(a, tag) && tagged(b, tag);
+    }
+};
+
+// A wait that has ended without its value (kRunWait, which only a block that
+// stopped for good can exceed): later waits are skipped, so that the launch
+// ends, and the fit reports the failure (error bit 1).
+struct Waiter {
+    int* dead;  // LDS
+    __device__ bool expired(uint64_t t0) const {
+        if (wall_clock64() - t0 < kRunWait) return false;
+        *dead = 1;
+        return true;
+    }
+};
+
+// the value at p once it carries the tag
+template <typename V>
+__device__ __forceinline__ V take(const Waiter& w, G<const Word> p, uint32_t tag) {
+    V v;
+    if (Words<V>::get(p, tag, v) || *w.dead) return v;
+    const uint64_t t0 = wall_clock64();
+    while (!Words<V>::get(p, tag, v))
+        if (w.expired(t0)) break;
+    return v;
+}
+
+// Sum over the rows r0, r0 + step, ... < n_rows of the entries at
+// base + row * stride (words), in that order, U of them in flight.
+template <int U>
+__device__ __forceinline__ double take_rows(const Waiter& w, G<const Word> base, size_t stride, int r0,
+                                            int step, int n_rows, uint32_t tag) {
+    double s = 0.0;
+    for (int r = r0; r < n_rows; r += U * step) {
+        double v[U];
+        bool ok[U];
+#pragma unroll
+        for (int k = 0; k < U; ++k) {
+            v[k] = 0.0;
+            ok[k] = r + k * step >= n_rows || Words<double>::get(base + (size_t)(r + k * step) * stride, tag, v[k]);
+        }
+#pragma unroll
+        for (int k = 0; k < U; ++k) {
+            if (!ok[k]) v[k] = take<double>(w, base + (size_t)(r + k * step) * stride, tag);
+            s += v[k];
+        }
+    }
+    return s;
+}
+
+// The start of a launch: every block counts itself in, and the waits of the
+// steps begin only once all have, i.e. are all running. A launch whose blocks
+// are not all running within kRunStart (another kernel holds the compute
+// units, or the stream owns too few of them) is called off by one of them:
+// all leave without having changed anything, and the last to leave does the
+// whole run alone. So every wait of the steps ends, whatever else the GPU runs.
+constexpr uint32_t kRunOff = 0x80000000u;
+
+__device__ __forceinline__ bool all_running(RunSync* s, uint32_t target) {
+    const uint64_t t0 = wall_clock64();
+    for (;;) {
+        uint32_t v = __hip_atomic_load(&s->start, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (v & kRunOff) return false;
+        if (v == target) return true;
+        if (wall_clock64() - t0 > kRunStart &&
+            __hip_atomic_compare_exchange_strong(&s->start, &v, v | kRunOff, __ATOMIC_RELAXED,
+                                                 __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+            return false;
+    }
+}
+
+// ------------------------------------------------------------ kept kernels ----
+// The kernels K_j of a particle after its push (what the deposit of step k
+// adds) are those of the force of change of step k + 1, at the same point. A
+// block keeps them in LDS, one slot per particle, instead of evaluating them
+// twice per step (two logarithms, the bins and the Gauss-Hermite functions:
+// about 90 of 270 vector instructions in FP32).
+template <typename T, int KIN>
+struct Kept {
+    static constexpr int KK = KIN & 7;
+    static constexpr int nv = (KK == kKinGH4 || KK == kKinGHN) ? KinSlots<KIN>::n : 0;
+    T* val;          // nv values per slot, slots values each
+    uint32_t* code;  // jr + 1 in 13 bits, jk + 1 above
+    int slots;
+
+    __device__ static int bytes(int slots) { return slots * (nv * (int)sizeof(T) + 4); }
+    __device__ void put(int at, const Kern<T, KIN>& k) const {
+        code[at] = (uint32_t)(k.jr + 1) | ((uint32_t)(k.jk + 1) << 13);
+#pragma unroll
+        for (int m = 0; m < nv; ++m)
+            if (m < k.kn) val[m * slots + at] = k.k[m];
+    }
+    __device__ Kern<T, KIN> get(int at, const Hot<T>& h, T vz) const {
+        Kern<T, KIN> k;
+        const uint32_t c = code[at];
+        k.jr = (int)(c & 0x1fffu) - 1;
+        k.jk = (int)(c >> 13) - 1;
+        k.kn = k.jk < 0 ? 0 : (KK == kKinGHN ? h.gh_nmax : KinSlots<KIN>::n);
+        if (nv == 0) k.k[0] = KK == kKinV2 ? vz * vz : T(1);
+#pragma unroll
+        for (int m = 0; m < nv; ++m)
+            if (m < k.kn) k.k[m] = val[m * slots + at];
+        return k;
+    }
+};
+
+// ---------------------------------------------------------------- reduce ----
+// Job q of a step: observable columns 16 q .. 16 q + 15 over all rows, then
+// what the finalize kernel does for them (smoothing, Delta, force table,
+// chi^2 part); one wave's 16 lanes per row group, the row groups added over
+// the wave and then over the waves, in a fixed order.
+template <typename T, int BLOCK>
+__device__ __forceinline__ void obs_job(const FitDev& fd, const RunArgs& ra, const Waiter& w, int q,
+                                        int n_rows, int ncol, uint32_t tag, int k, bool last,
+                                        double (*part)[kRunCols]) {
+    constexpr int RG = BLOCK / kRunCols, NW = BLOCK / 64;
+    const int t = thread_here(), lane = t & 63, wave = t >> 6;
+    const int col = q * kRunCols + (t & (kRunCols - 1));
+    const bool in = col < fd.J;
+    double yt0 = 0.0, sg = 1.0, Yj = 0.0;
+    if (t < kRunCols && in) {
+        yt0 = gmem(fd.ytil)[col];
+        sg = gmem(fd.sigma)[col];
+        Yj = gmem(fd.Y)[col];
+    }
+    const G<const Word> rows = gmem<const Word>(ra.rows);
+    double s = in ? take_rows<4>(w, rows + (size_t)col * 2, (size_t)ncol * 2, t / kRunCols, RG, n_rows, tag)
+                  : 0.0;
+    s += __shfl_xor(s, 16, 64);
+    s += __shfl_xor(s, 32, 64);
+    if (lane < kRunCols) part[wave][lane] = s;
+    __syncthreads();
+    if (wave == 0) {
+        double d2 = 0.0;
+        if (lane < kRunCols && in) {
+            double tot = 0.0;
+            for (int v = 0; v < NW; ++v) tot += part[v][lane];
+            const double yt = yt0 + fd.q * (tot - yt0);
+            const double d = (yt - Yj) / sg;
+            const T r = (T)(fd.foc_chi * d / sg);
+            Words<T>::put(gmem<Word>(ra.res) + (size_t)col * Words<T>::n, r, tag);
+            gmem(fd.ytil)[col] = yt;
+            if (last) {
+                gmem(fd.yv)[col] = tot;
+                gmem(fd.delta)[col] = d;
+                gmem<T>(fd.rp)[col] = r;
+            }
+            d2 = d * d;
+        }
+        for (int off = kRunCols / 2; off >= 1; off >>= 1) d2 += __shfl_xor(d2, off, 64);
+        if (lane == 0)
+            Words<double>::put(gmem<Word>(ra.parts) + ((size_t)k * ra.n_jobs + q) * 2, d2, tag);
+    }
+    __syncthreads();
+}
+
+// Cell job q of a refresh step: cells 16 q .. 16 q + 15, their weight sums
+// and counts over all rows, and the means that become the priors.
+template <typename T, int BLOCK>
+__device__ __forceinline__ void cell_job(const FitDev& fd, const RunArgs& ra, const Waiter& w, int q,
+                                         int n_rows, int ncol, uint32_t tag, double (*part)[kRunCols],
+                                         double (*part2)[kRunCols]) {
+    constexpr int RG = BLOCK / kRunCols, NW = BLOCK / 64;
+    const int t = thread_here(), lane = t & 63, wave = t >> 6;
+    const int c = q * kRunCols + (t & (kRunCols - 1));
+    const bool in = c < fd.C;
+    const G<const Word> rows = gmem<const Word>(ra.rows);
+    double s = 0.0, m = 0.0;
+    if (in) {
+        s = take_rows<2>(w, rows + (size_t)(fd.J + c) * 2, (size_t)ncol * 2, t / kRunCols, RG, n_rows, tag);
+        m = take_rows<2>(w, rows + (size_t)(fd.J + fd.C + c) * 2, (size_t)ncol * 2, t / kRunCols, RG,
+                         n_rows, tag);
+    }
+    for (int off = 16; off <= 32; off <<= 1) {
+        s += __shfl_xor(s, off, 64);
+        m += __shfl_xor(m, off, 64);
+    }
+    if (lane < kRunCols) {
+        part[wave][lane] = s;
+        part2[wave][lane] = m;
+    }
+    __syncthreads();
+    if (t < kRunCols && in) {
+        double tot = 0.0, cnt = 0.0;
+        for (int v = 0; v < NW; ++v) {
+            tot += part[v][lane];
+            cnt += part2[v][lane];
+        }
+        // the cell's mean weight, or the previous prior if it is empty
+        const double d = cnt > 0.0 ? tot / cnt : gmem(fd.gprior)[c];
+        gmem(fd.cdata)[c] = d;
+        gmem(fd.gprior)[c] = d;
+        gmem<T>(fd.ucell)[c] = (T)d;
+        Words<T>::put(gmem<Word>(ra.cell) + (size_t)c * Words<T>::n, (T)d, tag);
+    }
+    __syncthreads();
+}
+
+// ------------------------------------------------------------------- run ----
+// ra.n_steps steps of one fit over gridDim.x blocks. Block b takes the
+// particles in groups of 64 (one wave each): group (m G + b) for m = wave,
+// wave + NW, ..., so that every compute unit gets the same number of waves to
+// within one (blocks of 1024 consecutive particles left 300 007 FP64 particles
+// on 147 compute units for two rounds, or on 37 of 256 for the second).
+template <typename T, int BLOCK, int KIN>
+__global__ __launch_bounds__(BLOCK) void k_run(const FitDev fd, const RunArgs ra) {
+    extern __shared__ __align__(16) unsigned char lds_raw[];
+    constexpr int NW = BLOCK / 64;
+    __shared__ double part[NW][kRunCols], part2[NW][kRunCols];
+    __shared__ int flag, dead;
+    using A = double;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int n = (int)fd.n;
+    const uint32_t n_blocks = gridDim.x;
+    int b = (int)blockIdx.x, nb = (int)n_blocks;
+    if (tid == 0) {
+        (void)__hip_atomic_fetch_add(&ra.sync->start, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        dead = 0;
+    }
+
+    const G<T> __restrict__ X = gmem<T>(fd.x);
+    const G<T> __restrict__ Y = gmem<T>(fd.y);
+    const G<T> __restrict__ Z = gmem<T>(fd.z);
+    const G<T> __restrict__ VX = gmem<T>(fd.vx);
+    const G<T> __restrict__ VY = gmem<T>(fd.vy);
+    const G<T> __restrict__ VZ = gmem<T>(fd.vz);
+    const G<T> __restrict__ U = gmem<T>(fd.u);
+    const G<T> __restrict__ UH = gmem<T>(fd.uh);
+    const G<uint16_t> __restrict__ CI = gmem(fd.cidx);
+    const G<FitState> st = gmem(fd.st);
+    const int64_t kstep0 = st->kstep, tstep0 = st->tstep;
+    bool assign = st->assign_pending != 0;
+    const int32_t error0 = st->error;
+    const bool correct = ra.correct != 0;
+    const bool priors = correct && fd.entropy == 0 && fd.prior_every > 0;
+    // correction steps until the next refresh
+    int until = priors ? fd.prior_every - (int)(kstep0 % fd.prior_every) : 0;
+
+    // the first particles are requested before the set-up
+    int i0 = (wave * nb + b) * 64 + lane, istep = NW * nb * 64;
+    T nx = T(0), ny = T(0), nz = T(0), nvx = T(0), nvy = T(0), nvz = T(0), nu = T(0), nh = T(1);
+    auto load = [&](int i) {
+        nx = *elem<T>(X, (uint32_t)i);
+        ny = *elem<T>(Y, (uint32_t)i);
+        nz = *elem<T>(Z, (uint32_t)i);
+        nvx = *elem<T>(VX, (uint32_t)i);
+        nvy = *elem<T>(VY, (uint32_t)i);
+        nvz = *elem<T>(VZ, (uint32_t)i);
+        nu = *elem<T>(U, (uint32_t)i);
+        nh = *elem<T>(UH, (uint32_t)i);
+    };
+    if (i0 < n) load(i0);
+
+    const Hot<T> h = hot_of<T>(fd);
+    const int J = h.J, C = h.C, kp = h.kp, ncol = J + 2 * C;
+    Tabs<T, A> tb = carve<T, A>(lds_raw, J, kp, h.n_r, h.n_R, h.n_v, C);
+    const int priv = tid & (kp - 1);
+    {
+        const G<const T> rp = gmem<const T>(fd.rp);
+        for (int j = tid; j < J; j += BLOCK) tb.rp[j] = rp[j];
+        for (int j = tid; j < J * kp; j += BLOCK) tb.sum[j] = 0.0;
+        for (int j = tid; j < C; j += BLOCK) {
+            tb.csum[j] = 0.0;
+            tb.ccnt[j] = 0u;
+        }
+        const G<const T> re2 = gmem<const T>(fd.redge2);
+        for (int j = tid; j <= h.n_r; j += BLOCK) tb.re2[j] = re2[j];
+        const G<const T> Re2 = gmem<const T>(fd.Redge2);
+        for (int j = tid; j <= h.n_R; j += BLOCK) tb.Re2[j] = Re2[j];
+        const G<const T> ve = gmem<const T>(fd.vedge);
+        for (int j = tid; j <= h.n_v; j += BLOCK) tb.ve[j] = ve[j];
+        const G<const T> Vp = gmem<const T>(fd.Vp);
+        const G<const T> isp = gmem<const T>(fd.isp);
+        for (int j = tid; j < h.n_R; j += BLOCK) {
+            tb.Vp[j] = Vp[j];
+            tb.isp[j] = isp[j];
+        }
+    }
+    if (tid == 0) {
+        int how = 1;
+        if (!all_running(ra.sync, ra.start0 + n_blocks)) {
+            const uint32_t out =
+                __hip_atomic_fetch_add(&ra.sync->left, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            how = out == n_blocks - 1 ? 2 : 0;
+        }
+        flag = how;
+    }
+    __syncthreads();
+    const int how = __builtin_amdgcn_readfirstlane(flag);
+    if (how == 0) return;
+    const bool alone = how == 2;
+    if (alone) {
+        b = 0;
+        nb = 1;
+        i0 = tid;
+        istep = BLOCK;
+        if (i0 < n) load(i0);
+    }
+    const Waiter wt{&dead};
+    // at most one particle per thread: they stay in registers
+    const bool resident = n <= istep;
+    Kept<T, KIN> kept;
+    kept.slots = (n + istep - 1) / istep * BLOCK;
+    kept.val = reinterpret_cast<T*>(lds_raw + ra.keep_at);
+    kept.code = reinterpret_cast<uint32_t*>(kept.val + Kept<T, KIN>::nv * kept.slots);
+    const bool keep = !alone && ra.keep_bytes > 0;
+    bool assigned = false;  // some step of this launch wrote the priors
+
+    for (int k = 0; k < ra.n_steps; ++k) {
+        const uint32_t tag = ra.tag0 + 1u + (uint32_t)k;
+        const bool last = k == ra.n_steps - 1;
+        const bool refresh = priors && --until == 0;
+        if (refresh) until = fd.prior_every;
+        assigned |= assign;
+        // software pipeline: the loads of the next particle are in flight
+        // while the current one is computed
+        int at = tid;
+        for (int i = i0; i < n; i += istep, at += BLOCK) {
+            T x = nx, y = ny, z = nz, vx = nvx, vy = nvy, vz = nvz, u = nu, uh = nh;
+            if (i + istep < n) load(i + istep);
+            if (assign) {
+                // the prior of the particle's cell at the last refresh: of the
+                // previous step, or of an earlier launch
+                const int c = min((int)*elem<uint16_t>(CI, (uint32_t)i), C - 1);
+                if (k > 0)
+                    uh = take<T>(wt, gmem<const Word>(ra.cell) + (size_t)c * Words<T>::n, tag - 1u);
+                else
+                    uh = gmem<const T>(fd.ucell)[c];
+            }
+            if (correct) {
+                Kern<T, KIN> kk;
+                if (keep && k > 0)
+                    kk = kept.get(at, h, vz);
+                else
+                    kk = kernels<T, A, KIN>(h, tb, x, y, z, vz);
+                u = corrected_weight<T, A, KIN>(h, tb, kk, u, uh);
+            }
+            x += h.hdt * vx;
+            y += h.hdt * vy;
+            z += h.hdt * vz;
+            kick<T, true>(h, x, y, z, vx, vy, vz);
+            x += h.hdt * vx;
+            y += h.hdt * vy;
+            z += h.hdt * vz;
+            const Kern<T, KIN> kk = kernels<T, A, KIN>(h, tb, x, y, z, vz);
+            deposit<T, KIN>(h, tb, kk, u, priv);
+            if (keep) kept.put(at, kk);
+            if (refresh) {
+                const int c = cell_of<T>(h, x, y, z, vx, vy, vz);
+                atomicAdd(&tb.csum[c], (double)u);
+                atomicAdd(&tb.ccnt[c], 1u);
+                *elem<uint16_t>(CI, (uint32_t)i) = (uint16_t)c;
+            }
+            if (resident) {
+                nx = x;
+                ny = y;
+                nz = z;
+                nvx = vx;
+                nvy = vy;
+                nvz = vz;
+                nu = u;
+                nh = uh;
+            }
+            if (!resident || last) {
+                *elem<T>(X, (uint32_t)i) = x;
+                *elem<T>(Y, (uint32_t)i) = y;
+                *elem<T>(Z, (uint32_t)i) = z;
+                *elem<T>(VX, (uint32_t)i) = vx;
+                *elem<T>(VY, (uint32_t)i) = vy;
+                *elem<T>(VZ, (uint32_t)i) = vz;
+                if (correct) *elem<T>(U, (uint32_t)i) = u;
+                if (resident ? assigned : assign) *elem<T>(UH, (uint32_t)i) = uh;
+            }
+        }
+        // the first particle of the next step, requested before the exchange
+        if (!resident && !last && i0 < n) load(i0);
+        __syncthreads();
+        // this block's row of sums; the bins are cleared for the next step
+        const int t0 = thread_here();
+        const G<Word> row = gmem<Word>(ra.rows) + (size_t)b * ncol * 2;
+        for (int j = t0; j < J; j += BLOCK) {
+            double t = 0.0;
+            for (int g = 0; g < kp; ++g) {
+                t += tb.sum[j * kp + g];
+                tb.sum[j * kp + g] = 0.0;
+            }
+            Words<double>::put(row + (size_t)j * 2, t, tag);
+        }
+        if (refresh)
+            for (int j = t0; j < C; j += BLOCK) {
+                Words<double>::put(row + (size_t)(J + j) * 2, tb.csum[j], tag);
+                Words<double>::put(row + (size_t)(J + C + j) * 2, (double)tb.ccnt[j], tag);
+                tb.csum[j] = 0.0;
+                tb.ccnt[j] = 0u;
+            }
+        for (int q = b; q < ra.n_jobs; q += nb)
+            obs_job<T, BLOCK>(fd, ra, wt, q, nb, ncol, tag, k, last, part);
+        if (refresh)
+            // cell jobs from the last block down, away from the observable jobs
+            for (int q = nb - 1 - b; q < ra.n_cell_jobs; q += nb)
+                cell_job<T, BLOCK>(fd, ra, wt, q, nb, ncol, tag, part, part2);
+        if (!last) {
+            for (int j = t0; j < J; j += BLOCK)
+                tb.rp[j] = take<T>(wt, gmem<const Word>(ra.res) + (size_t)j * Words<T>::n, tag);
+            __syncthreads();
+        }
+        assign = refresh;
+    }
+
+    // the last block (it has the fewest particles) ends the run: chi^2 of every
+    // step from its jobs' parts in order, then the counters
+    if (tid == 0 && dead)
+        (void)__hip_atomic_fetch_or(&ra.sync->dead, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (b != nb - 1) return;
+    bool bad = false;
+    for (int k = tid; k < ra.n_steps; k += BLOCK) {
+        double c2 = 0.0;
+        const G<const Word> p = gmem<const Word>(ra.parts) + (size_t)k * ra.n_jobs * 2;
+        for (int q = 0; q < ra.n_jobs; ++q)
+            c2 += take<double>(wt, p + (size_t)q * 2, ra.tag0 + 1u + (uint32_t)k);
+        gmem(fd.chi2_hist)[(tstep0 + k) % kHistCap] = c2;
+        if (k == ra.n_steps - 1) st->chi2 = c2;
+        bad |= !isfinite(c2);
+    }
+    const int any_bad = __syncthreads_or(bad ? 1 : 0);
+    if (tid == 0) {
+        const uint32_t d = __hip_atomic_load(&ra.sync->dead, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (any_bad || dead || d) st->error = error0 | (any_bad ? 1 : 0) | ((dead || d) ? 2 : 0);
+        st->tstep = tstep0 + ra.n_steps;
+        if (correct) st->kstep = kstep0 + ra.n_steps;
+        st->steps_left = 0;
+        st->correct = correct ? 1 : 0;
+        st->assign_pending = assign ? 1 : 0;
+        if (alone) {
+            ra.sync->start = ra.start0 + n_blocks;
+            ra.sync->left = 0u;
+        }
+    }
+}
+
+template <typename T, int BLOCK>
+hipError_t launch_run_kin(int kin, const FitDev& fd, const RunArgs& ra, int blocks, size_t lds,
+                          hipStream_t s) {
+    switch (kin) {
+        case kKinNone: hipLaunchKernelGGL((k_run<T, BLOCK, kKinNone>), dim3(blocks), dim3(BLOCK), lds, s, fd, ra); break;
+        case kKinV2: hipLaunchKernelGGL((k_run<T, BLOCK, kKinV2>), dim3(blocks), dim3(BLOCK), lds, s, fd, ra); break;
+        case kKinGH4: hipLaunchKernelGGL((k_run<T, BLOCK, kKinGH4>), dim3(blocks), dim3(BLOCK), lds, s, fd, ra); break;
+        case kKinGHN: hipLaunchKernelGGL((k_run<T, BLOCK, kKinGHN>), dim3(blocks), dim3(BLOCK), lds, s, fd, ra); break;
+        case kKinLOSVD: hipLaunchKernelGGL((k_run<T, BLOCK, kKinLOSVD>), dim3(blocks), dim3(BLOCK), lds, s, fd, ra); break;
+        default: return hipErrorInvalidValue;
+    }
+    return hipGetLastError();
+}
+
+}  // namespace
+}  // namespace m2m

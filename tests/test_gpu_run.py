@@ -1,0 +1,219 @@
+"""Fits that step by the run kernel (several steps per launch, blocks that
+exchange their sums): at the edges of its launch shapes against the FP64
+oracle, and the launches around it: a launch that is called off, fits on
+several streams, steps captured into a graph, more steps than one launch takes.
+
+Tolerances are those of the other parity tests: weights to 1e-4 (FP32 state,
+particles the oracle never saw near an edge) and 1e-10 (FP64); two runs of the
+same kernels differ by the order of FP64 sums only."""
+
+import sys
+
+import numpy as np
+import pytest
+
+from m2m_testlib import cast, weight_errors
+from workloads import workload
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+
+def _say(*a):
+    print("[gpu-test]", *a, file=sys.stderr, flush=True)
+
+
+@pytest.fixture(scope="module")
+def Fit():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_1202_2355_amd import _abi
+    _abi.lib()
+    from paper_1202_2355_amd.fit import Fit
+    return Fit
+
+
+def _workload(kin, every=4):
+    """Workload 1 (FP64 v^2) or 2 (Gauss-Hermite) with a refresh every `every`
+    steps, or a variant of its layout."""
+    wl = workload(1 if kin in ("v2", "none") else 2)
+    lay = dict(wl.layout)
+    if kin == "none":
+        lay.update(kin="none", n_R=0)
+    if kin == "gh6":
+        lay["gh_nmax"] = 6
+    if kin == "losvd":
+        lay.update(kin="losvd", n_R=10, n_v=16, v_min=-2.0, v_max=2.0, gh_nmax=0)
+    return wl.with_(layout=lay, params=dict(wl.params, prior_every=every))
+
+
+def _targets(oracle, wl, parts, n):
+    """The fit's own initial observables with 5 % errors: data that any number
+    of particles can follow."""
+    V = S = None
+    if wl.layout["kin"] == "gh":
+        V, S = np.zeros(wl.layout["n_R"]), np.full(wl.layout["n_R"], 0.4)
+    Y = oracle.deposit(parts, np.ones(n), wl.layout, mass=wl.params["mass"], V_p=V, sigma_p=S)
+    scale = np.abs(Y).max()
+    return Y * (1.0 + 0.05 * np.sin(np.arange(Y.size))), 0.05 * np.abs(Y) + 1e-3 * scale + 1e-12, V, S
+
+
+def _fit(Fit, wl, parts, T, dtype, **kw):
+    f = Fit(wl.potential, wl.layout, wl.params, parts, dtype=dtype, **kw)
+    f.set_targets(*T)
+    return f
+
+
+# sizes: one particle; a ragged wave; the last of the small blocks and the
+# first above; one particle per thread and the first beyond; several per thread
+CASES = [("v2", "f64", 1, 4), ("gh", "f32", 1, 4), ("none", "f32", 63, 4), ("v2", "f32", 1025, 2),
+         ("gh6", "f64", 5003, 4), ("losvd", "f32", 8191, 4), ("losvd", "f64", 4097, 4),
+         ("gh", "f64", 32768, 4), ("gh", "f32", 32769, 4), ("v2", "f64", 131073, 4),
+         ("gh", "f32", 262145, 4), ("gh6", "f32", 300007, 4), ("gh", "f64", 300007, 5),
+         ("v2", "f32", 20011, 1), ("gh", "f32", 20011, 0)]
+
+
+@pytest.mark.parametrize("kin,dtype,n,every", CASES)
+def test_run_matches_oracle(oracle, Fit, kin, dtype, n, every):
+    """12 steps in calls of 1, 4 and 7 (refreshes inside and at the end of a
+    call, the assignment carried from one launch to the next)."""
+    wl = _workload(kin, every)
+    _say("run kernel", kin, dtype, n, "every", every)
+    parts = cast(wl.initial_particles(n=n, seed=60 + n % 17), dtype)
+    T = _targets(oracle, wl, parts, n)
+    f = _fit(Fit, wl, parts, T, dtype)
+    o = oracle.OracleFit(wl.potential, wl.layout, wl.params, parts, *T, track_flags=True,
+                         band=1e-5 if dtype == "f32" else 1e-12, nthreads=8)
+    for k in (1, 4, 7):
+        f.step(k)
+        o.step(k)
+    tol = 1e-4 if dtype == "f32" else 1e-10
+    st, ob, hist = f.particles(), f.observables(), f.chi2_history()
+    f.close()
+    r2, rmax, _, frac = weight_errors(st["u"], o.arr["u"], o.flag)
+    _say("rel2", r2, "max(unflagged)", rmax, "flagged", frac)
+    assert r2 <= tol and rmax <= tol
+    for c in ("x", "y", "z", "vx", "vy", "vz"):
+        np.testing.assert_allclose(st[c], o.arr[c], rtol=0,
+                                   atol=(2e-5 if dtype == "f32" else 1e-12) * max(1.0, np.abs(o.arr[c]).max()))
+    assert len(hist) == 12 and hist[-1] == ob["chi2"]
+    assert ob["chi2"] == pytest.approx(o.chi2, rel=1e-3 if dtype == "f32" else 1e-9)
+    if dtype == "f64":
+        np.testing.assert_allclose(ob["ytilde"], o.ytilde, rtol=1e-10, atol=1e-13)
+        np.testing.assert_allclose(st["uh"], o.arr["uhat"], rtol=1e-10)
+
+
+def test_more_steps_than_one_launch_takes(oracle, Fit):
+    wl = _workload("v2", 25)
+    n = 4001
+    _say("600 steps in one call", n)
+    parts = cast(wl.initial_particles(n=n, seed=5), "f64")
+    T = _targets(oracle, wl, parts, n)
+    a, b = (_fit(Fit, wl, parts, T, "f64") for _ in range(2))
+    a.step(600)
+    for k in (256, 1, 255, 88):
+        b.step(k)
+    np.testing.assert_allclose(a.chi2_history(), b.chi2_history(), rtol=1e-10)
+    assert len(a.chi2_history()) == 600
+    np.testing.assert_allclose(a.particles()["u"], b.particles()["u"], rtol=1e-10)
+    a.close()
+    b.close()
+
+
+@pytest.mark.parametrize("dtype,n", [("f64", 20_000), ("f32", 70_001)])
+def test_a_launch_that_is_called_off_is_done_by_one_block(oracle, Fit, dtype, n):
+    """The counter of a fit's launches marked as called off from the host: the
+    blocks of the next launch leave and the last of them does its steps alone;
+    the launches after it run as usual."""
+    from paper_1202_2355_amd import _abi as A
+    wl = _workload("v2", 4)
+    _say("called off", dtype, n)
+    parts = cast(wl.initial_particles(n=n, seed=8), dtype)
+    T = _targets(oracle, wl, parts, n)
+    a, b = (_fit(Fit, wl, parts, T, dtype) for _ in range(2))
+    # the run areas come last in the workspace: a fit that has none (a refresh
+    # on every step) has the same workspace up to there
+    at = A.m2m_workspace_bytes(wl.layout, dict(wl.params, prior_every=1), n, dtype)
+    assert at < A.m2m_workspace_bytes(wl.layout, wl.params, n, dtype)
+    start = b._ws[at:at + 4].view(torch.int32)
+    for f in (a, b):
+        f.step(3)
+    torch.cuda.synchronize()
+    blocks = int(start[0])
+    assert 0 < blocks <= 256
+    start += -(1 << 31)
+    for f in (a, b):
+        f.step(6)
+    torch.cuda.synchronize()
+    assert int(start[0]) == 2 * blocks
+    for f in (a, b):
+        f.step(5)
+    rtol = 1e-5 if dtype == "f32" else 1e-11
+    np.testing.assert_allclose(b.chi2_history(), a.chi2_history(), rtol=rtol)
+    pa, pb = a.particles(), b.particles()
+    for c in pa:
+        np.testing.assert_allclose(pb[c], pa[c], rtol=rtol, atol=1e-12)
+    a.close()
+    b.close()
+
+
+def test_fits_on_several_streams_and_threads(oracle, Fit):
+    """Three fits of different sizes, each stepped in turn by a thread of its
+    own on a stream of its own, against the same fits alone."""
+    import threading
+    wl = _workload("gh", 4)
+    ns = (3001, 40_009, 270_001)
+    _say("streams", ns)
+    made = []
+    for n in ns:
+        parts = cast(wl.initial_particles(n=n, seed=n), "f32")
+        made.append((parts, _targets(oracle, wl, parts, n)))
+    alone = []
+    for parts, T in made:
+        f = _fit(Fit, wl, parts, T, "f32")
+        f.step(40)
+        alone.append(f.particles()["u"])
+        f.close()
+    fits = [_fit(Fit, wl, parts, T, "f32", stream=torch.cuda.Stream()) for parts, T in made]
+
+    def work(f):
+        for _ in range(8):
+            f.step(5)
+
+    ts = [threading.Thread(target=work, args=(f,)) for f in fits]
+    for t in ts:
+        t.start()
+    for t in ts:
+        t.join()
+    for f, ref in zip(fits, alone):
+        np.testing.assert_allclose(f.particles()["u"], ref, rtol=1e-5)
+        f.close()
+
+
+def test_steps_captured_into_a_graph(oracle, Fit):
+    """Steps of a fit recorded into a caller's graph and replayed, with eager
+    steps between the replays."""
+    wl = _workload("v2", 4)
+    n = 9001
+    _say("captured steps", n)
+    parts = cast(wl.initial_particles(n=n, seed=3), "f64")
+    T = _targets(oracle, wl, parts, n)
+    s = torch.cuda.Stream()
+    a, b = _fit(Fit, wl, parts, T, "f64"), _fit(Fit, wl, parts, T, "f64", stream=s)
+    b.step(1)
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g, stream=s):
+        b.step(3)
+    a.step(1)
+    for _ in range(3):
+        with torch.cuda.stream(s):
+            g.replay()
+        b.step(2)
+        a.step(5)
+        torch.cuda.synchronize()
+        np.testing.assert_allclose(b.chi2_history(), a.chi2_history(), rtol=1e-10)
+    np.testing.assert_allclose(b.particles()["u"], a.particles()["u"], rtol=1e-10)
+    a.close()
+    b.close()
