@@ -25,10 +25,16 @@ constexpr int kGraphSteps = 32;     // M2M steps per captured graph of one fit
 constexpr int kBatchGraphSteps = 8; // of a batch (captured again when fits come and go)
 constexpr int kProfileMax = 4096;   // most steps one m2m_profile_step call times
 constexpr int kBatchProfileMax = 256;  // most steps one m2m_batch_profile call times
-// A fit of a batch whose tile rows of observable sums take at most this many
-// bytes is finalized by one block (every column and the end of its step, no
-// hand-over between blocks); larger ones by column jobs.
+// The fits of a launch are finalized by one block each (every column and the
+// end of its step, no hand-over between blocks) if they are many, have few
+// columns and their tile rows of observable sums take at most this many bytes;
+// else by column jobs. Measured us a step, whole fits against column jobs: 64
+// Gauss-Hermite fits in two groups 310 / 313, 10 such fits 69 / 51, 8 small ones
+// 20.5 / 17.2; one block takes 57 us for 2610 observables however few the
+// rows, the column jobs of 16 such fits 10 us.
 constexpr size_t kWholeFitMaxBytes = size_t(1) << 20;
+constexpr int kWholeFitMaxJobs = 8;  // columns / kFinCols
+constexpr size_t kWholeFitMinFits = 24;
 constexpr uint32_t kStateMagic = 0x4d324d31u;  // "M2M1"
 constexpr uint32_t kStateVersion = 2u;         // 2: with the FP64 prior grid
 constexpr double kPi = 3.14159265358979323846;
@@ -602,8 +608,8 @@ void split_tiles(int64_t n, int count, int fit, int row0, std::vector<Tile>& out
 }
 
 void fin_jobs(const WsLayout& w, int fit, int n_rows, std::vector<FinJob>& out) {
-    for (int b = 0; b < w.nbj; ++b) out.push_back(FinJob{fit, 0, b * kFinCols, n_rows});
-    for (int b = 0; b < w.ncj; ++b) out.push_back(FinJob{fit, 1, b * kFinCols, n_rows});
+    for (int b = 0; b < std::max(w.nbj, w.ncj); ++b)
+        out.push_back(FinJob{fit, 0, b * kFinCols, n_rows});
     for (int b = 0; b < w.npj; ++b) out.push_back(FinJob{fit, 2, b * kFinCols, n_rows});
 }
 
@@ -1575,15 +1581,16 @@ m2m_status fill_set(m2m_batch* b, LaunchSet& L, const std::vector<int>& members,
     int64_t tile = (ntot + room - 1) / room;
     tile = (tile + kSegAlign - 1) / kSegAlign * kSegAlign;
     size_t lds = 0;
-    // a launch's finalize is one block per fit when every fit's tile rows of
-    // observable sums are small enough, else column jobs for every fit
-    bool whole = true;
+    // a launch's finalize is one block per fit (see kWholeFitMaxBytes), or
+    // column jobs for every fit
+    bool whole = members.size() >= kWholeFitMinFits;
     std::vector<int> cnts(members.size());
     for (size_t f = 0; f < members.size(); ++f) {
         m2m_ctx* c = b->fits[members[f]];
         int cnt = (int)std::min<int64_t>((c->n + tile - 1) / tile, c->w.seg_cap);
         cnts[f] = std::max(1, cnt);
-        if ((size_t)cnts[f] * (size_t)c->w.J * 8 > kWholeFitMaxBytes) whole = false;
+        if ((size_t)cnts[f] * (size_t)c->w.J * 8 > kWholeFitMaxBytes || c->w.nbj > kWholeFitMaxJobs)
+            whole = false;
     }
     for (size_t f = 0; f < members.size(); ++f) {
         m2m_ctx* c = b->fits[members[f]];

@@ -160,7 +160,7 @@ __host__ __device__ inline Tile tile_of(int64_t n, int t, int count, int fit, in
 constexpr int32_t kFinWholeFit = 3;
 struct FinJob {
     int32_t fit;
-    int32_t kind;  // 0: observable columns, 1: cell columns, 2: potential columns, 3: all
+    int32_t kind;  // 0: observable and cell columns, 2: potential columns, 3: all
     int32_t col0;
     int32_t n_tiles;  // rows of the fit to reduce
 };
@@ -245,7 +245,7 @@ hipError_t launch_step_f32f(int block, int kin, const FitDev* fits, const Tile* 
                             const FitDev* one, int n_tiles, size_t lds, int32_t mode, hipStream_t s);
 // one fit, fd (a host copy of its description) passed by value: the step
 // over n_tiles tiles as tile_of splits it; the finalize jobs of that fit
-// (bin jobs, then cell jobs) over n_rows tile rows
+// (bin and cell columns, then potential columns) over n_rows tile rows
 hipError_t launch_step1(bool f64, bool acc64, int block, int kin, const FitDev& fd, int n_tiles,
                         size_t lds, int32_t mode, hipStream_t s);
 hipError_t launch_finalize1(bool f64, const FitDev& fd, int n_rows, int32_t mode, hipStream_t s);

@@ -17,6 +17,8 @@
 // specialized at compile time on the kind of kinematic observable.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+
 #include "m2m_device.h"
 
 namespace m2m {
@@ -25,8 +27,8 @@ namespace {
 // ------------------------------------------------------------- finalize ----
 // The reduction of a step: one block per job of kFinCols columns of one fit.
 //   column sums over the fit's tile rows in one fixed order: row group g
-//   (g < kFinWaves) adds rows g, g + kFinWaves, ... in row order, then the
-//   groups are added in order;
+//   (one wave of NW) adds rows g, g + NW, ... in row order, then the groups
+//   are added in order;
 //   observable columns: smoothing (eq. myts), Delta and chi^2 (eqs. delta,
 //   chi) and the force table; cell columns: the cell means that become the
 //   priors (Sec. 2.3.1);
@@ -71,43 +73,29 @@ __device__ __forceinline__ Flags flags_of(const FitDev& fd, const Snap& ss, int3
     return f;
 }
 
-// Row group g of one column: the sum of rows g, g + kFinWaves, ... in row
-// order (and of the matching count column for cells), U rows in flight (the
-// sum does not depend on U).
-template <int U>
-__device__ __forceinline__ void group_sum(const FitDev& fd, bool bins, int col, int n_tiles, int g,
-                                          double& acc, double& acc2) {
-    const size_t stride = (size_t)fd.row_len;
-    const int J = fd.J, C = fd.C;
-    if (bins) {
-        const G<const double> base = gmem<const double>(fd.partials) + col;
-        for (int t0 = g; t0 < n_tiles; t0 += U * kFinWaves) {
-            double v[U];
+// Row group g of NW of one column from base: the sum of rows g, g + NW, ... in
+// row order, U rows in flight (the sum does not depend on U).
+template <int U, int NW>
+__device__ __forceinline__ double group_sum(G<const double> base, size_t stride, int n_tiles, int g) {
+    double acc = 0.0;
+    for (int t0 = g; t0 < n_tiles; t0 += U * NW) {
+        double v[U];
 #pragma unroll
-            for (int k = 0; k < U; ++k) {
-                const int t = t0 + k * kFinWaves;
-                v[k] = (t < n_tiles) ? base[(size_t)t * stride] : 0.0;
-            }
-#pragma unroll
-            for (int k = 0; k < U; ++k) acc += v[k];
+        for (int k = 0; k < U; ++k) {
+            const int t = t0 + k * NW;
+            v[k] = (t < n_tiles) ? base[(size_t)t * stride] : 0.0;
         }
-    } else {
-        const G<const double> base = gmem<const double>(fd.partials) + J + col;
-        for (int t0 = g; t0 < n_tiles; t0 += U * kFinWaves) {
-            double v[U], w[U];
 #pragma unroll
-            for (int k = 0; k < U; ++k) {
-                const int t = t0 + k * kFinWaves;
-                v[k] = (t < n_tiles) ? base[(size_t)t * stride] : 0.0;
-                w[k] = (t < n_tiles) ? base[(size_t)t * stride + C] : 0.0;
-            }
-#pragma unroll
-            for (int k = 0; k < U; ++k) {
-                acc += v[k];
-                acc2 += w[k];
-            }
-        }
+        for (int k = 0; k < U; ++k) acc += v[k];
     }
+    return acc;
+}
+
+// A result that another block of the same launch reads: written through to
+// memory (agent-scope relaxed store), so that the ticket after it needs no
+// release (finalize_job).
+__device__ __forceinline__ void put_shared(double* p, double v) {
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 // Column epilogue of one job (one wave; lane = column offset): tot, tot2 are
@@ -133,7 +121,7 @@ __device__ __forceinline__ double column_epilogue(const FitDev& fd, bool bins, i
     } else if (!bins && col < fd.C) {
         // the cell's data: the mean weight, or the previous prior if empty
         const double d = (tot2 > 0.0) ? tot / tot2 : gmem(fd.gprior)[col];
-        gmem(fd.cdata)[col] = d;
+        put_shared(fd.cdata + col, d);
         if (!fd.smooth) {
             gmem(fd.gprior)[col] = d;
             gmem<T>(fd.ucell)[col] = (T)d;
@@ -142,16 +130,19 @@ __device__ __forceinline__ double column_epilogue(const FitDev& fd, bool bins, i
     if (bins && !f.observe) {
         // chi^2 of these columns: fixed-order butterfly over the wave
         for (int off = 32; off >= 1; off >>= 1) d2 += __shfl_xor(d2, off, 64);
-        if (lane == 0) gmem(fd.chi2_part)[col0 / kFinCols] = d2;
+        if (lane == 0) put_shared(fd.chi2_part + col0 / kFinCols, d2);
     }
     return d2;
 }
 
 // chi^2 from the parts of the bin jobs (one wave): lane l adds parts l,
-// l + 64, ... in order, then a fixed-order butterfly over the wave.
+// l + 64, ... in order, then a fixed-order butterfly over the wave. SHARED:
+// the parts were stored by other blocks of this launch (put_shared).
+template <bool SHARED>
 __device__ __forceinline__ double chi2_of_parts(const double* parts, int n, int lane) {
     double c = 0.0;
-    for (int b = lane; b < n; b += 64) c += parts[b];
+    for (int b = lane; b < n; b += 64)
+        c += SHARED ? __hip_atomic_load(parts + b, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : parts[b];
     for (int off = 32; off >= 1; off >>= 1) c += __shfl_xor(c, off, 64);
     return c;
 }
@@ -486,17 +477,23 @@ struct SmoothLds<false> {};
 // node table are compiled in only then); SMOOTH: some fit of the launch
 // smooths its prior grid.
 //
+// A job of kind 0 takes the observable columns from col0 and, in launches that
+// refresh the priors, the cell columns from col0 (cells have jobs of their own
+// nowhere: blocks that only counted themselves on 24 steps of 25 held the slots
+// of the others); a job of kind 2 takes potential columns. NW waves, each
+// adding every NW-th row.
+//
 // Every launched job of a fit takes one ticket, also the jobs with nothing
-// to do in this launch (cell columns on steps without a refresh, potential
-// columns on steps without a rebuild, observable columns in the modes that
-// reduce only cells or the potential). The job that takes the last ticket
+// to do in this launch (columns beyond the observables on steps without a
+// refresh, potential columns on steps without a rebuild). The job that takes the last ticket
 // ends the step and rewrites the fit's counters, so it can only do so once
 // every job has read them: a job that read the counters after the end of
 // the step would see the next step's schedule.
-template <typename T, bool SCF, bool SMOOTH>
+template <typename T, bool SCF, bool SMOOTH, int NW>
 __device__ __forceinline__ void finalize_job(const FitDev& fd, const FinJob& jb, int32_t mode) {
-    __shared__ double part[kFinWaves][kFinCols];
-    __shared__ double part2[kFinWaves][kFinCols];
+    static_assert(!SMOOTH || NW == kFinWaves, "prior smoothing needs kFinWaves waves");
+    __shared__ double part[NW][kFinCols];
+    __shared__ double part2[NW][kFinCols];
     __shared__ int last, sidx;
     __shared__ double smean;
     __shared__ SmoothLds<SMOOTH> sl;
@@ -506,18 +503,20 @@ __device__ __forceinline__ void finalize_job(const FitDev& fd, const FinJob& jb,
     const bool cells_mode = (mode & kModeCells) != 0;
     const bool observe = (mode & kModeObserve) != 0;
     const bool pot_mode = SCF && (mode & kModePot) != 0;
-    const bool bins = jb.kind == 0, pots = SCF && jb.kind == 2;
+    const bool main = jb.kind == 0, pots = SCF && jb.kind == 2;
     const int lane = threadIdx.x & 63;
     const int wave = threadIdx.x >> 6;
     const int col = jb.col0 + lane;
-    const bool in = col < (bins ? fd.J : pots ? fd.scf_P : fd.C);
+    const bool bins = main && jb.col0 < fd.J && !cells_mode && !pot_mode;
+    const size_t stride = (size_t)fd.row_len;
+    const G<const double> rows = gmem<const double>(fd.partials) + col;
 
     // observable columns: the rows and the smoothing inputs are requested
     // before the fit's state is known (their latency overlaps its load)
-    double acc = 0.0, acc2 = 0.0;
+    double acc = 0.0;
     double yt0 = 0.0, sg = 1.0, Yj = 0.0;
-    if (bins && !cells_mode && !pot_mode && in) {
-        group_sum<16>(fd, true, col, jb.n_tiles, wave, acc, acc2);
+    if (bins && col < fd.J) {
+        acc = group_sum<16, NW>(rows, stride, jb.n_tiles, wave);
         if (wave == 0 && !observe) {
             yt0 = gmem(fd.ytil)[col];
             sg = gmem(fd.sigma)[col];
@@ -529,53 +528,58 @@ __device__ __forceinline__ void finalize_job(const FitDev& fd, const FinJob& jb,
     // launch ends its step), and none takes a ticket
     if (step && ss.steps_left <= 0) return;
     const Flags f = flags_of<SCF>(fd, ss, mode);
-    // this job's work in this launch
-    const bool work = bins ? !(cells_mode || pot_mode) : (jb.kind == 1 ? f.refresh : (pots && f.pot));
-    if (work) {
-        // cell columns, read only on refresh steps; potential columns only on
-        // the steps that rebuild it
-        if (jb.kind == 1 && in) group_sum<8>(fd, false, col, jb.n_tiles, wave, acc, acc2);
-        if (pots && in) group_sum<16>(fd, true, fd.scf_col0 + col, jb.n_tiles, wave, acc, acc2);
+    const bool cells = main && f.refresh && jb.col0 < fd.C;
+    if (bins || (pots && f.pot)) {
+        const bool in = col < (bins ? fd.J : fd.scf_P);
+        if (!bins && in) acc = group_sum<16, NW>(rows + fd.scf_col0, stride, jb.n_tiles, wave);
         part[wave][lane] = acc;
-        part2[wave][lane] = acc2;
+        __syncthreads();
+        if (wave == 0) {
+            double tot = 0.0;
+            for (int w = 0; w < NW; ++w) tot += part[w][lane];
+            if (bins)
+                (void)column_epilogue<T>(fd, true, jb.col0, f, tot, 0.0, yt0, sg, Yj, lane);
+            else if (in)
+                put_shared(fd.scf_sum + col, tot);
+        }
+    }
+    if (cells) {
+        const bool in = col < fd.C;
+        __syncthreads();
+        part[wave][lane] = in ? group_sum<8, NW>(rows + fd.J, stride, jb.n_tiles, wave) : 0.0;
+        part2[wave][lane] = in ? group_sum<8, NW>(rows + fd.J + fd.C, stride, jb.n_tiles, wave) : 0.0;
         __syncthreads();
         if (wave == 0) {
             double tot = 0.0, tot2 = 0.0;
-            for (int w = 0; w < kFinWaves; ++w) {
+            for (int w = 0; w < NW; ++w) {
                 tot += part[w][lane];
                 tot2 += part2[w][lane];
             }
-            if (pots) {
-                if (in) gmem(fd.scf_sum)[col] = tot;
-            } else {
-                (void)column_epilogue<T>(fd, bins, jb.col0, f, tot, tot2, yt0, sg, Yj, lane);
-            }
+            (void)column_epilogue<T>(fd, false, jb.col0, f, tot, tot2, 0.0, 1.0, 0.0, lane);
         }
     }
     // the last job of this fit ends the step; in observe mode the same
     // hand-over runs on a separate counter and changes no state
-    const uint32_t n_part = (uint32_t)(fd.n_bin_jobs + fd.n_cell_jobs + fd.n_pot_jobs);
+    const uint32_t n_part = (uint32_t)(max(fd.n_bin_jobs, fd.n_cell_jobs) + fd.n_pot_jobs);
     uint32_t* ticket = observe ? &st->mticket : &st->ticket;
     __syncthreads();
     if (threadIdx.x == 0) {
-        // a job with results: release of them (wave 0 wrote them) with the
-        // count; acquire of the others' for the last job, passed on to its
-        // block by the barrier below. A job without results only counts
-        // itself: its reads of the counters have completed, as their values
-        // decided the branch that led here, so a relaxed add suffices (an
-        // agent-scope release would write back the whole L2 of its XCD); if
-        // it is the last, it acquires the others' results by a fence.
-        uint32_t prev;
-        if (work) {
-            prev = __hip_atomic_fetch_add(ticket, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
-        } else {
-            prev = __hip_atomic_fetch_add(ticket, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            if (prev == n_part - 1) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-        }
+        // The results that the last job reads (parts of chi^2, cell data,
+        // sums of the potential) were stored by this wave with put_shared:
+        // they are in memory once its store counter is zero, and the ticket
+        // follows. A release would write back the whole L2 of this XCD and an
+        // acquire drop its lines, once per job: with 16 fits of 2610
+        // observables (1168 jobs) the finalize took 31 us that way.
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        const uint32_t prev =
+            __hip_atomic_fetch_add(ticket, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         last = (prev == n_part - 1) ? 1 : 0;
     }
     __syncthreads();
     if (!last) return;
+    // the cell data and the potential's sums are read by plain loads
+    if ((SMOOTH && fd.smooth && f.refresh) || (SCF && f.pot))
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
     // a refresh with smoothing: the whole block smooths the prior grid, each
     // n_E x n_x grid alone (the first, then the L_z < 0 half if split)
     if constexpr (SMOOTH) {
@@ -592,7 +596,7 @@ __device__ __forceinline__ void finalize_job(const FitDev& fd, const FinJob& jb,
     if (wave != 0) return;
     const double chi2 = (cells_mode || pot_mode)
                             ? 0.0
-                            : chi2_of_parts(static_cast<const double*>(fd.chi2_part), fd.n_bin_jobs, lane);
+                            : chi2_of_parts<true>(fd.chi2_part, fd.n_bin_jobs, lane);
     if (lane != 0) return;
     *ticket = 0u;
     if (observe || pot_mode) return;
@@ -754,18 +758,20 @@ __device__ __forceinline__ void finalize_fit(const FitDev& fd, int n_rows, int32
     }
     if (SCF && f.pot) build_scf_table(fd);
     if (wave != 0) return;
-    const double chi2 = (cells_mode || pot_mode) ? 0.0 : chi2_of_parts(chi2p, nbj, lane);
+    const double chi2 = (cells_mode || pot_mode) ? 0.0 : chi2_of_parts<false>(chi2p, nbj, lane);
     if (lane != 0 || observe || pot_mode) return;
     end_step(fd, gst, f, ss, chi2);
 }
 
 // the column jobs of the fits of a table (batches of fits with many rows)
-template <typename T, bool SCF, bool SMOOTH>
-__global__ __launch_bounds__(kFinThreads) void k_finalize(const FitDev* __restrict__ fits,
-                                                         const FinJob* __restrict__ jobs,
-                                                         int32_t mode) {
+// NW = 4 waves a block (16 with smoothing): a batch has hundreds of jobs, and
+// blocks of 16 waves went one per compute unit, round after round
+template <typename T, bool SCF, bool SMOOTH, int NW>
+__global__ __launch_bounds__(NW * 64) void k_finalize(const FitDev* __restrict__ fits,
+                                                     const FinJob* __restrict__ jobs,
+                                                     int32_t mode) {
     const FinJob jb = jobs[blockIdx.x];
-    finalize_job<T, SCF, SMOOTH>(fits[jb.fit], jb, mode);
+    finalize_job<T, SCF, SMOOTH, NW>(fits[jb.fit], jb, mode);
 }
 
 // one block of NW waves per fit of a table, each reducing every column of
@@ -779,18 +785,17 @@ __global__ __launch_bounds__(NW * 64) void k_finalize_fits(const FitDev* __restr
     finalize_fit<T, SCF, SMOOTH, NW>(fits[jb.fit], jb.n_tiles, mode);
 }
 
-// one fit, its description passed by value: block b < n_bin_jobs takes bin
-// columns, then n_cell_jobs blocks cell columns, then n_pot_jobs blocks the
-// columns of the self-consistent potential, over n_rows tile rows
+// one fit, its description passed by value: the first blocks take bin and
+// cell columns, then n_pot_jobs blocks the columns of the self-consistent
+// potential, over n_rows tile rows
 template <typename T, bool SCF, bool SMOOTH>
 __global__ __launch_bounds__(kFinThreads) void k_finalize1(const FitDev fd, int32_t n_rows,
                                                           int32_t mode) {
     const int b = blockIdx.x;
-    const int nb = fd.n_bin_jobs, nc = fd.n_cell_jobs;
-    const int kind = b < nb ? 0 : (b < nb + nc ? 1 : 2);
-    const int base = kind == 0 ? 0 : (kind == 1 ? nb : nb + nc);
-    const FinJob jb{0, kind, (b - base) * kFinCols, n_rows};
-    finalize_job<T, SCF, SMOOTH>(fd, jb, mode);
+    const int nm = max(fd.n_bin_jobs, fd.n_cell_jobs);
+    const int kind = b < nm ? 0 : 2;
+    const FinJob jb{0, kind, (kind == 0 ? b : b - nm) * kFinCols, n_rows};
+    finalize_job<T, SCF, SMOOTH, kFinWaves>(fd, jb, mode);
 }
 
 
@@ -919,7 +924,7 @@ hipError_t launch_step1(bool f64, bool acc64, int block, int kin, const FitDev& 
 }
 
 namespace {
-constexpr int kFitWaves = 4;  // waves of a whole-fit finalize block without smoothing
+constexpr int kFitWaves = 4;  // waves of a batch's finalize blocks without smoothing
 
 template <bool SCF, bool SMOOTH>
 hipError_t launch_fin_t(bool f64, const FitDev* fits, const FinJob* jobs, const FitDev* one,
@@ -940,11 +945,12 @@ hipError_t launch_fin_t(bool f64, const FitDev* fits, const FinJob* jobs, const 
             hipLaunchKernelGGL((k_finalize_fits<float, SCF, SMOOTH, NW>), dim3(n_blocks),
                                dim3(NW * 64), 0, s, fits, jobs, mode);
     } else {
+        constexpr int NW = SMOOTH ? kFinWaves : kFitWaves;
         if (f64)
-            hipLaunchKernelGGL((k_finalize<double, SCF, SMOOTH>), dim3(n_blocks), dim3(kFinThreads), 0,
+            hipLaunchKernelGGL((k_finalize<double, SCF, SMOOTH, NW>), dim3(n_blocks), dim3(NW * 64), 0,
                                s, fits, jobs, mode);
         else
-            hipLaunchKernelGGL((k_finalize<float, SCF, SMOOTH>), dim3(n_blocks), dim3(kFinThreads), 0,
+            hipLaunchKernelGGL((k_finalize<float, SCF, SMOOTH, NW>), dim3(n_blocks), dim3(NW * 64), 0,
                                s, fits, jobs, mode);
     }
     return hipGetLastError();
@@ -972,7 +978,7 @@ hipError_t launch_finalize(bool f64, const FitDev* fits, int n_fits, const FinJo
 bool kin_scf(int kin) { return (kin & kKinScf) != 0; }
 
 hipError_t launch_finalize1(bool f64, const FitDev& fd, int n_rows, int32_t mode, hipStream_t s) {
-    const int n_jobs = fd.n_bin_jobs + fd.n_cell_jobs + fd.n_pot_jobs;
+    const int n_jobs = std::max(fd.n_bin_jobs, fd.n_cell_jobs) + fd.n_pot_jobs;
     return launch_fin_any(f64, fd.scf_nr > 0, fd.smooth != 0, nullptr, nullptr, &fd, n_jobs, n_rows,
                           mode, s, false);
 }
