@@ -260,12 +260,11 @@ m2m_status m2m_set_targets(m2m_ctx* ctx, int32_t J, const double* Y, const doubl
  * Fits of at most 1024 observables and 2^22 particles, with radial bins in an
  * analytic potential, no prior smoothing, no refresh on every single step and
  * FP64 bins (M2M_DEPOSIT_F64), take up to 256 steps per launch: one kernel
- * whose blocks exchange their sums. Its blocks wait for each other, so runs of
- * fits on different streams of one device are ordered one after another, and
- * while any fit is in a batch, or if the stream is being captured, the steps
- * are launched one by one (two kernels each) as for all other fits. A launch
- * whose blocks do not all start within 50 ms (the compute units are held by
- * other work) is done by one block alone. */
+ * whose blocks exchange their sums. Its blocks wait for each other, so runs on
+ * different streams of one device are ordered one after another. If the stream
+ * is being captured, the steps are launched one by one (two kernels each) as
+ * for all other fits. A launch whose blocks do not all start within 50 ms (the
+ * compute units are held by other work) is done by one block alone. */
 m2m_status m2m_step(m2m_ctx* ctx, int32_t n_steps, int32_t correct);
 
 /* Recompute the cell priors from the current state now (Sec. 2.3.1) and

@@ -175,17 +175,16 @@ constexpr uint64_t kRunWait = 1000000000; // 10 s: a wait within a run that fail
 
 // counters of the launches of a context
 struct RunSync {
-    uint32_t start;  // blocks that have started, over all launches (kRunOff: this one is called off)
-    uint32_t left;   // blocks that have left a launch that was called off
-    uint32_t dead;   // a wait ended without its value
+    uint32_t start;   // blocks that have started, over all launches (kRunOff: this one is called off)
+    uint32_t start0;  // the same before this launch
+    uint32_t tag0;    // tag of the last step done so
+    uint32_t left;    // blocks that have left a launch that was called off
+    uint32_t dead;    // a wait ended without its value
 };
 
 // Exchange areas in the fit's workspace: 64-bit words of 32 data and 32 tag
 // bits (m2m_run.h).
 struct RunArgs {
-    int32_t n_steps, correct;
-    uint32_t tag0;             // the steps' tags are tag0 + 1 .. tag0 + n_steps
-    uint32_t start0;           // sync->start before this launch
     int32_t keep_at, keep_bytes;  // LDS offset and size of the kept kernels (0: not kept)
     int32_t n_jobs, n_cell_jobs;  // ceil(J / kRunCols), ceil(C / kRunCols)
     RunSync* sync;
@@ -193,6 +192,20 @@ struct RunArgs {
     uint64_t *res;    // J entries of the force table, 1 word (FP32) or 2
     uint64_t *cell;   // C cell priors, the same
     uint64_t *parts;  // kRunMaxSteps x n_jobs parts of chi^2, 2 words each
+};
+
+// What one launch does: n_steps steps with the force of change on or off (a fit
+// of a batch: as many of them as it has left, with its own setting). known:
+// start0 and tag0 are the counters' values before the launch, else the
+// kernel reads them.
+struct RunCall {
+    int32_t n_steps, correct, known;
+    uint32_t start0, tag0;
+};
+
+// one block of a run of many fits: block b of nb of fit `fit`
+struct RunTile {
+    int32_t fit, b, nb, pad;
 };
 
 // Blocks and threads per block of a run over n particles of J observables: at
@@ -216,10 +229,16 @@ inline RunShape run_shape(int64_t n, bool f64, int J) {
     return RunShape{block, (int)(b < kRunMaxBlocks ? b : kRunMaxBlocks)};
 }
 
+// steps (at most kRunMaxSteps) of one fit over `blocks` blocks, or (tiles) of the
+// fits of a table, each up to the steps it has left
 hipError_t launch_run_f32(int block, int kin, const FitDev& fd, const RunArgs& ra, int blocks,
-                          size_t lds, hipStream_t s);
+                          size_t lds, const RunCall& call, hipStream_t s);
 hipError_t launch_run_f64(int block, int kin, const FitDev& fd, const RunArgs& ra, int blocks,
-                          size_t lds, hipStream_t s);
+                          size_t lds, const RunCall& call, hipStream_t s);
+hipError_t launch_runs_f32(int block, int kin, const FitDev* fits, const RunArgs* ras,
+                           const RunTile* tiles, int blocks, size_t lds, int n_steps, hipStream_t s);
+hipError_t launch_runs_f64(int block, int kin, const FitDev* fits, const RunArgs* ras,
+                           const RunTile* tiles, int blocks, size_t lds, int n_steps, hipStream_t s);
 
 // ---- launchers (m2m_kernels.hip) ------------------------------------------
 // kin: kinematic kind of every fit in the launch, from kin_class()

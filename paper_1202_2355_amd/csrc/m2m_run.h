@@ -6,6 +6,8 @@
 // else crosses blocks.
 #pragma once
 
+#include <type_traits>
+
 #include "m2m_device.h"
 
 namespace m2m {
@@ -277,13 +279,17 @@ __device__ __forceinline__ void cell_job(const FitDev& fd, const RunArgs& ra, co
 }
 
 // ------------------------------------------------------------------- run ----
-// ra.n_steps steps of one fit over gridDim.x blocks. Block b takes the
-// particles in groups of 64 (one wave each): group (m G + b) for m = wave,
+// Steps of one fit over n_blocks blocks, by block b. Block b takes the
+// particles in groups of 64 (one wave each): group (m n_blocks + b) for m = wave,
 // wave + NW, ..., so that every compute unit gets the same number of waves to
 // within one (blocks of 1024 consecutive particles left 300 007 FP64 particles
 // on 147 compute units for two rounds, or on 37 of 256 for the second).
-template <typename T, int BLOCK, int KIN>
-__global__ __launch_bounds__(BLOCK) void k_run(const FitDev fd, const RunArgs ra) {
+// KNOWN: the launch's start0 and tag0 come with the call; OWN: a fit of a
+// batch, with its own steps left and setting (both at compile time: as branches
+// at the start of the kernel they cost a launch of one step 0.6-0.9 of 12.4 us).
+template <typename T, int BLOCK, int KIN, bool KNOWN, bool OWN>
+__device__ __forceinline__ void run_fit(const FitDev& fd, const RunArgs& ra, int b,
+                                        const uint32_t n_blocks, const RunCall& call) {
     extern __shared__ __align__(16) unsigned char lds_raw[];
     constexpr int NW = BLOCK / 64;
     __shared__ double part[NW][kRunCols], part2[NW][kRunCols];
@@ -291,8 +297,16 @@ __global__ __launch_bounds__(BLOCK) void k_run(const FitDev fd, const RunArgs ra
     using A = double;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int n = (int)fd.n;
-    const uint32_t n_blocks = gridDim.x;
-    int b = (int)blockIdx.x, nb = (int)n_blocks;
+    int nb = (int)n_blocks;
+    const G<FitState> st = gmem(fd.st);
+    const G<RunSync> sync = gmem(ra.sync);
+    int n_steps = call.n_steps;
+    if (OWN) {
+        n_steps = min(n_steps, (int)st->steps_left);
+        if (n_steps <= 0) return;  // uniform: the fit is idle
+    }
+    const uint32_t start0 = KNOWN ? call.start0 : sync->start0;
+    const uint32_t tag0 = KNOWN ? call.tag0 : sync->tag0;
     if (tid == 0) {
         (void)__hip_atomic_fetch_add(&ra.sync->start, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         dead = 0;
@@ -307,11 +321,11 @@ __global__ __launch_bounds__(BLOCK) void k_run(const FitDev fd, const RunArgs ra
     const G<T> __restrict__ U = gmem<T>(fd.u);
     const G<T> __restrict__ UH = gmem<T>(fd.uh);
     const G<uint16_t> __restrict__ CI = gmem(fd.cidx);
-    const G<FitState> st = gmem(fd.st);
     const int64_t kstep0 = st->kstep, tstep0 = st->tstep;
     bool assign = st->assign_pending != 0;
     const int32_t error0 = st->error;
-    const bool correct = ra.correct != 0;
+    const bool correct = OWN ? st->correct != 0 : call.correct != 0;
+    const int32_t left0 = OWN ? st->steps_left : n_steps;
     const bool priors = correct && fd.entropy == 0 && fd.prior_every > 0;
     // correction steps until the next refresh
     int until = priors ? fd.prior_every - (int)(kstep0 % fd.prior_every) : 0;
@@ -358,7 +372,7 @@ __global__ __launch_bounds__(BLOCK) void k_run(const FitDev fd, const RunArgs ra
     }
     if (tid == 0) {
         int how = 1;
-        if (!all_running(ra.sync, ra.start0 + n_blocks)) {
+        if (!all_running(ra.sync, start0 + n_blocks)) {
             const uint32_t out =
                 __hip_atomic_fetch_add(&ra.sync->left, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             how = out == n_blocks - 1 ? 2 : 0;
@@ -386,9 +400,9 @@ __global__ __launch_bounds__(BLOCK) void k_run(const FitDev fd, const RunArgs ra
     const bool keep = !alone && ra.keep_bytes > 0;
     bool assigned = false;  // some step of this launch wrote the priors
 
-    for (int k = 0; k < ra.n_steps; ++k) {
-        const uint32_t tag = ra.tag0 + 1u + (uint32_t)k;
-        const bool last = k == ra.n_steps - 1;
+    for (int k = 0; k < n_steps; ++k) {
+        const uint32_t tag = tag0 + 1u + (uint32_t)k;
+        const bool last = k == n_steps - 1;
         const bool refresh = priors && --until == 0;
         if (refresh) until = fd.prior_every;
         assigned |= assign;
@@ -493,43 +507,82 @@ __global__ __launch_bounds__(BLOCK) void k_run(const FitDev fd, const RunArgs ra
         (void)__hip_atomic_fetch_or(&ra.sync->dead, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     if (b != nb - 1) return;
     bool bad = false;
-    for (int k = tid; k < ra.n_steps; k += BLOCK) {
+    for (int k = tid; k < n_steps; k += BLOCK) {
         double c2 = 0.0;
         const G<const Word> p = gmem<const Word>(ra.parts) + (size_t)k * ra.n_jobs * 2;
         for (int q = 0; q < ra.n_jobs; ++q)
-            c2 += take<double>(wt, p + (size_t)q * 2, ra.tag0 + 1u + (uint32_t)k);
+            c2 += take<double>(wt, p + (size_t)q * 2, tag0 + 1u + (uint32_t)k);
         gmem(fd.chi2_hist)[(tstep0 + k) % kHistCap] = c2;
-        if (k == ra.n_steps - 1) st->chi2 = c2;
+        if (k == n_steps - 1) st->chi2 = c2;
         bad |= !isfinite(c2);
     }
     const int any_bad = __syncthreads_or(bad ? 1 : 0);
     if (tid == 0) {
         const uint32_t d = __hip_atomic_load(&ra.sync->dead, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         if (any_bad || dead || d) st->error = error0 | (any_bad ? 1 : 0) | ((dead || d) ? 2 : 0);
-        st->tstep = tstep0 + ra.n_steps;
-        if (correct) st->kstep = kstep0 + ra.n_steps;
-        st->steps_left = 0;
+        st->tstep = tstep0 + n_steps;
+        if (correct) st->kstep = kstep0 + n_steps;
+        st->steps_left = left0 - n_steps;
         st->correct = correct ? 1 : 0;
         st->assign_pending = assign ? 1 : 0;
+        sync->tag0 = tag0 + (uint32_t)n_steps;
+        sync->start0 = start0 + n_blocks;
         if (alone) {
-            ra.sync->start = ra.start0 + n_blocks;
-            ra.sync->left = 0u;
+            sync->start = start0 + n_blocks;
+            sync->left = 0u;
         }
     }
 }
 
-template <typename T, int BLOCK>
-hipError_t launch_run_kin(int kin, const FitDev& fd, const RunArgs& ra, int blocks, size_t lds,
-                          hipStream_t s) {
+template <typename T, int BLOCK, int KIN, bool KNOWN>
+__global__ __launch_bounds__(BLOCK) void k_run(const FitDev fd, const RunArgs ra,
+                                               const RunCall call) {
+    run_fit<T, BLOCK, KIN, KNOWN, false>(fd, ra, (int)blockIdx.x, gridDim.x, call);
+}
+
+// the fits of a table, each over its own blocks (no fit waits for another)
+template <typename T, int BLOCK, int KIN>
+__global__ __launch_bounds__(BLOCK) void k_runs(const FitDev* __restrict__ fits,
+                                                const RunArgs* __restrict__ ras,
+                                                const RunTile* __restrict__ tiles, int32_t n_steps) {
+    const RunTile t = tiles[blockIdx.x];
+    run_fit<T, BLOCK, KIN, false, true>(fits[t.fit], ras[t.fit], t.b, (uint32_t)t.nb, RunCall{n_steps, 1, 0, 0u, 0u});
+}
+
+// f(the kind of kinematic observables as a compile-time constant)
+template <typename F>
+hipError_t with_kin(int kin, F&& f) {
     switch (kin) {
-        case kKinNone: hipLaunchKernelGGL((k_run<T, BLOCK, kKinNone>), dim3(blocks), dim3(BLOCK), lds, s, fd, ra); break;
-        case kKinV2: hipLaunchKernelGGL((k_run<T, BLOCK, kKinV2>), dim3(blocks), dim3(BLOCK), lds, s, fd, ra); break;
-        case kKinGH4: hipLaunchKernelGGL((k_run<T, BLOCK, kKinGH4>), dim3(blocks), dim3(BLOCK), lds, s, fd, ra); break;
-        case kKinGHN: hipLaunchKernelGGL((k_run<T, BLOCK, kKinGHN>), dim3(blocks), dim3(BLOCK), lds, s, fd, ra); break;
-        case kKinLOSVD: hipLaunchKernelGGL((k_run<T, BLOCK, kKinLOSVD>), dim3(blocks), dim3(BLOCK), lds, s, fd, ra); break;
+        case kKinNone: f(std::integral_constant<int, kKinNone>()); break;
+        case kKinV2: f(std::integral_constant<int, kKinV2>()); break;
+        case kKinGH4: f(std::integral_constant<int, kKinGH4>()); break;
+        case kKinGHN: f(std::integral_constant<int, kKinGHN>()); break;
+        case kKinLOSVD: f(std::integral_constant<int, kKinLOSVD>()); break;
         default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
+}
+
+template <typename T, int BLOCK>
+hipError_t launch_run_t(int kin, const FitDev& fd, const RunArgs& ra, int blocks, size_t lds,
+                        const RunCall& call, hipStream_t s) {
+    return with_kin(kin, [&](auto K) {
+        if (call.known)
+            hipLaunchKernelGGL((k_run<T, BLOCK, decltype(K)::value, true>), dim3(blocks), dim3(BLOCK),
+                               lds, s, fd, ra, call);
+        else
+            hipLaunchKernelGGL((k_run<T, BLOCK, decltype(K)::value, false>), dim3(blocks), dim3(BLOCK),
+                               lds, s, fd, ra, call);
+    });
+}
+
+template <typename T, int BLOCK>
+hipError_t launch_runs_t(int kin, const FitDev* fits, const RunArgs* ras, const RunTile* tiles,
+                         int blocks, size_t lds, int n_steps, hipStream_t s) {
+    return with_kin(kin, [&](auto K) {
+        hipLaunchKernelGGL((k_runs<T, BLOCK, decltype(K)::value>), dim3(blocks), dim3(BLOCK), lds, s,
+                           fits, ras, tiles, n_steps);
+    });
 }
 
 }  // namespace

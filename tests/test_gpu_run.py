@@ -217,3 +217,62 @@ def test_steps_captured_into_a_graph(oracle, Fit):
     np.testing.assert_allclose(b.particles()["u"], a.particles()["u"], rtol=1e-10)
     a.close()
     b.close()
+
+
+def test_batches_that_run(oracle, Fit):
+    """Two batches of uneven fits (one particle to more than a compute unit's
+    share) with different numbers of steps, each stepped by a thread of its own
+    on its own stream, against the fits alone; a fit that has left a batch
+    steps on alone."""
+    import threading
+    from paper_1202_2355_amd.batch import Batch
+    plans = [("gh", "f32", [(1, 9), (700, 30), (20_011, 17), (260_001, 30), (33_000, 4)]),
+             ("v2", "f64", [(5003, 21), (90_001, 30), (63, 30)])]
+    ref, todo = [], []
+    for kin, dtype, sizes in plans:
+        wl = _workload(kin, 4)
+        for n, steps in sizes:
+            parts = cast(wl.initial_particles(n=n, seed=n % 1000), dtype)
+            T = _targets(oracle, wl, parts, n)
+            f = _fit(Fit, wl, parts, T, dtype)
+            for k in (steps, 6):
+                f.step(k)
+            ref.append((f.particles(), f.chi2_history()))
+            f.close()
+            todo.append((wl, parts, T, dtype, steps))
+    _say("batches that run", plans)
+    for rep in range(2):
+        work, fits, at = [], [], 0
+        for kin, dtype, sizes in plans:
+            s = torch.cuda.Stream()
+            b = Batch(max_fits=8, stream=s)
+            mine = []
+            for wl, parts, T, _, steps in todo[at:at + len(sizes)]:
+                f = _fit(Fit, wl, parts, T, dtype, stream=s)
+                assert b.admit(f, steps)
+                mine.append(f)
+            at += len(sizes)
+            fits += mine
+            work.append((b, len(sizes)))
+
+        def go(b, count):
+            left = count
+            while left:
+                b.run(7)
+                done, left = b.poll() if rep else b.poll_lagged()
+
+        ts = [threading.Thread(target=go, args=w) for w in work]
+        for t in ts:
+            t.start()
+        for t in ts:
+            t.join()
+        for (b, _) in work:
+            b.close()
+        for f, (p, h), (_, _, _, dtype, _) in zip(fits, ref, todo):
+            f.step(6)
+            tol = 1e-5 if dtype == "f32" else 1e-10
+            got = f.particles()
+            np.testing.assert_allclose(got["u"], p["u"], rtol=tol)
+            np.testing.assert_allclose(got["uh"], p["uh"], rtol=tol)
+            np.testing.assert_allclose(f.chi2_history(), h, rtol=10 * tol, atol=1e-12)
+            f.close()
