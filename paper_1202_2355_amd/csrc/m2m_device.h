@@ -29,6 +29,17 @@ __device__ __forceinline__ G<T> gmem(void* p) {
     return (G<T>)static_cast<T*>(p);
 }
 
+// Has v (loaded before) in its register here. The compiler waits for a load at
+// the first use of its result, with a counter that memory accesses leave in
+// order: where that use comes after later stores, or after a branch of which
+// one side loaded, the wait takes those with it. Using the value earlier, at
+// the right place, keeps the other accesses in flight (particle loops of
+// step_tile and run_fit).
+template <typename T>
+__device__ __forceinline__ void settle(T& v) {
+    asm volatile("" : "+v"(v));
+}
+
 // ------------------------------------------------------------- math --------
 // FP32: the hardware transcendental and reciprocal instructions (about 1 ulp;
 // arguments here are never denormal). FP64: the correctly rounded library.

@@ -420,6 +420,7 @@ __device__ __forceinline__ void run_fit(const FitDev& fd, const RunArgs& ra, int
                     uh = take<T>(wt, gmem<const Word>(ra.cell) + (size_t)c * Words<T>::n, tag - 1u);
                 else
                     uh = gmem<const T>(fd.ucell)[c];
+                settle(uh);
             }
             if (correct) {
                 Kern<T, KIN> kk;
@@ -445,6 +446,14 @@ __device__ __forceinline__ void run_fit(const FitDev& fd, const RunArgs& ra, int
                 atomicAdd(&tb.ccnt[c], 1u);
                 *elem<uint16_t>(CI, (uint32_t)i) = (uint16_t)c;
             }
+            settle(nx);  // the next particle, before the stores
+            settle(ny);
+            settle(nz);
+            settle(nvx);
+            settle(nvy);
+            settle(nvz);
+            settle(nu);
+            settle(nh);
             if (resident) {
                 nx = x;
                 ny = y;

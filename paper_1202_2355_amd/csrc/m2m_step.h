@@ -180,7 +180,10 @@ __device__ __forceinline__ void step_tile(const FitDev& fd, const Tile& tl, int3
         }
         // the prior of the particle's cell at the last refresh (same
         // phase-space point: no push in between)
-        if (assign) uh = ucell[min((int)CI[i], C - 1)];
+        if (assign) {
+            uh = ucell[min((int)CI[i], C - 1)];
+            settle(uh);  // else every step waits here for the next particle too
+        }
         // force of change at z^k with the residuals of step k
         if (correct)
             u = corrected_weight<T, A, KIN>(h, tb, kernels<T, A, KIN>(h, tb, x, y, z, vz), u, uh);
@@ -216,6 +219,16 @@ __device__ __forceinline__ void step_tile(const FitDev& fd, const Tile& tl, int3
             atomicAdd(&tb.ccnt[c], 1u);
             CI[i] = (uint16_t)c;
         }
+        // the next particle has arrived by now; waited for here, before the
+        // stores, and not with them at the top of the loop
+        settle(nx);
+        settle(ny);
+        settle(nz);
+        settle(nvx);
+        settle(nvy);
+        settle(nvz);
+        settle(nu);
+        settle(nh);
         if (push && wt) {
             put_wt(X + i, x);
             put_wt(Y + i, y);
