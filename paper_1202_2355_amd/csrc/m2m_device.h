@@ -29,6 +29,16 @@ __device__ __forceinline__ G<T> gmem(void* p) {
     return (G<T>)static_cast<T*>(p);
 }
 
+// Element i of an array, with a byte offset of 32 unsigned bits: the access
+// takes the array's base in scalar registers, and no 64-bit address is formed
+// per access (two vector instructions, 15 times per particle). Offsets are within
+// a tile, or (interleaved tiles, runs) within a fit of fewer than 2^30 FP32 or
+// 2^29 FP64 particles.
+template <typename V>
+__device__ __forceinline__ G<V> elem(G<V> base, int i) {
+    return (G<V>)((G<char>)base + (uint32_t)i * (uint32_t)sizeof(V));
+}
+
 // Has v (loaded before) in its register here. The compiler waits for a load at
 // the first use of its result, with a counter that memory accesses leave in
 // order: where that use comes after later stores, or after a branch of which

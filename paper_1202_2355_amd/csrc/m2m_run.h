@@ -22,14 +22,6 @@ __device__ __forceinline__ int thread_here() {
     return t;
 }
 
-// Particle i of an array: the byte offset in 32 unsigned bits, so that the
-// access takes the array's base in scalar registers and no 64-bit address is
-// formed per access (n is at most kRunMaxN).
-template <typename V>
-__device__ __forceinline__ G<V> elem(G<V> base, uint32_t i) {
-    return (G<V>)((G<char>)base + i * (uint32_t)sizeof(V));
-}
-
 // -------------------------------------------------------------- exchange ----
 // Every 64-bit word that blocks exchange carries 32 bits of data and the
 // 32-bit tag of the step it belongs to, and is written and read by relaxed
@@ -334,14 +326,14 @@ __device__ __forceinline__ void run_fit(const FitDev& fd, const RunArgs& ra, int
     int i0 = (wave * nb + b) * 64 + lane, istep = NW * nb * 64;
     T nx = T(0), ny = T(0), nz = T(0), nvx = T(0), nvy = T(0), nvz = T(0), nu = T(0), nh = T(1);
     auto load = [&](int i) {
-        nx = *elem<T>(X, (uint32_t)i);
-        ny = *elem<T>(Y, (uint32_t)i);
-        nz = *elem<T>(Z, (uint32_t)i);
-        nvx = *elem<T>(VX, (uint32_t)i);
-        nvy = *elem<T>(VY, (uint32_t)i);
-        nvz = *elem<T>(VZ, (uint32_t)i);
-        nu = *elem<T>(U, (uint32_t)i);
-        nh = *elem<T>(UH, (uint32_t)i);
+        nx = *elem<T>(X, i);
+        ny = *elem<T>(Y, i);
+        nz = *elem<T>(Z, i);
+        nvx = *elem<T>(VX, i);
+        nvy = *elem<T>(VY, i);
+        nvz = *elem<T>(VZ, i);
+        nu = *elem<T>(U, i);
+        nh = *elem<T>(UH, i);
     };
     if (i0 < n) load(i0);
 
@@ -415,7 +407,7 @@ __device__ __forceinline__ void run_fit(const FitDev& fd, const RunArgs& ra, int
             if (assign) {
                 // the prior of the particle's cell at the last refresh: of the
                 // previous step, or of an earlier launch
-                const int c = min((int)*elem<uint16_t>(CI, (uint32_t)i), C - 1);
+                const int c = min((int)*elem<uint16_t>(CI, i), C - 1);
                 if (k > 0)
                     uh = take<T>(wt, gmem<const Word>(ra.cell) + (size_t)c * Words<T>::n, tag - 1u);
                 else
@@ -444,7 +436,7 @@ __device__ __forceinline__ void run_fit(const FitDev& fd, const RunArgs& ra, int
                 const int c = cell_of<T>(h, x, y, z, vx, vy, vz);
                 atomicAdd(&tb.csum[c], (double)u);
                 atomicAdd(&tb.ccnt[c], 1u);
-                *elem<uint16_t>(CI, (uint32_t)i) = (uint16_t)c;
+                *elem<uint16_t>(CI, i) = (uint16_t)c;
             }
             settle(nx);  // the next particle, before the stores
             settle(ny);
@@ -465,14 +457,14 @@ __device__ __forceinline__ void run_fit(const FitDev& fd, const RunArgs& ra, int
                 nh = uh;
             }
             if (!resident || last) {
-                *elem<T>(X, (uint32_t)i) = x;
-                *elem<T>(Y, (uint32_t)i) = y;
-                *elem<T>(Z, (uint32_t)i) = z;
-                *elem<T>(VX, (uint32_t)i) = vx;
-                *elem<T>(VY, (uint32_t)i) = vy;
-                *elem<T>(VZ, (uint32_t)i) = vz;
-                if (correct) *elem<T>(U, (uint32_t)i) = u;
-                if (resident ? assigned : assign) *elem<T>(UH, (uint32_t)i) = uh;
+                *elem<T>(X, i) = x;
+                *elem<T>(Y, i) = y;
+                *elem<T>(Z, i) = z;
+                *elem<T>(VX, i) = vx;
+                *elem<T>(VY, i) = vy;
+                *elem<T>(VZ, i) = vz;
+                if (correct) *elem<T>(U, i) = u;
+                if (resident ? assigned : assign) *elem<T>(UH, i) = uh;
             }
         }
         // the first particle of the next step, requested before the exchange

@@ -51,14 +51,14 @@ __device__ __forceinline__ void step_tile(const FitDev& fd, const Tile& tl, int3
     int i = il ? tl.row * BLOCK + (int)threadIdx.x : (int)threadIdx.x;
     T nx = T(0), ny = T(0), nz = T(0), nvx = T(0), nvy = T(0), nvz = T(0), nu = T(0), nh = T(1);
     if (i < len) {
-        nx = X[i];
-        ny = Y[i];
-        nz = Z[i];
-        nvx = VX[i];
-        nvy = VY[i];
-        nvz = VZ[i];
-        nu = U[i];
-        if (step) nh = UH[i];
+        nx = *elem(X, i);
+        ny = *elem(Y, i);
+        nz = *elem(Z, i);
+        nvx = *elem(VX, i);
+        nvy = *elem(VY, i);
+        nvz = *elem(VZ, i);
+        nu = *elem(U, i);
+        if (step) nh = *elem(UH, i);
     }
 
     const G<const FitState> st = gmem<const FitState>(fd.st);
@@ -159,29 +159,29 @@ __device__ __forceinline__ void step_tile(const FitDev& fd, const Tile& tl, int3
         const int inext = i + istep;
         if (inext < len) {
             if constexpr (nt) {
-                nx = __builtin_nontemporal_load(X + inext);
-                ny = __builtin_nontemporal_load(Y + inext);
-                nz = __builtin_nontemporal_load(Z + inext);
-                nvx = __builtin_nontemporal_load(VX + inext);
-                nvy = __builtin_nontemporal_load(VY + inext);
-                nvz = __builtin_nontemporal_load(VZ + inext);
-                nu = __builtin_nontemporal_load(U + inext);
-                if (need_uh) nh = __builtin_nontemporal_load(UH + inext);
+                nx = __builtin_nontemporal_load(elem(X, inext));
+                ny = __builtin_nontemporal_load(elem(Y, inext));
+                nz = __builtin_nontemporal_load(elem(Z, inext));
+                nvx = __builtin_nontemporal_load(elem(VX, inext));
+                nvy = __builtin_nontemporal_load(elem(VY, inext));
+                nvz = __builtin_nontemporal_load(elem(VZ, inext));
+                nu = __builtin_nontemporal_load(elem(U, inext));
+                if (need_uh) nh = __builtin_nontemporal_load(elem(UH, inext));
             } else {
-                nx = X[inext];
-                ny = Y[inext];
-                nz = Z[inext];
-                nvx = VX[inext];
-                nvy = VY[inext];
-                nvz = VZ[inext];
-                nu = U[inext];
-                if (need_uh) nh = UH[inext];
+                nx = *elem(X, inext);
+                ny = *elem(Y, inext);
+                nz = *elem(Z, inext);
+                nvx = *elem(VX, inext);
+                nvy = *elem(VY, inext);
+                nvz = *elem(VZ, inext);
+                nu = *elem(U, inext);
+                if (need_uh) nh = *elem(UH, inext);
             }
         }
         // the prior of the particle's cell at the last refresh (same
         // phase-space point: no push in between)
         if (assign) {
-            uh = ucell[min((int)CI[i], C - 1)];
+            uh = ucell[min((int)*elem(CI, i), C - 1)];
             settle(uh);  // else every step waits here for the next particle too
         }
         // force of change at z^k with the residuals of step k
@@ -217,7 +217,7 @@ __device__ __forceinline__ void step_tile(const FitDev& fd, const Tile& tl, int3
             const int c = cell_of<T>(h, x, y, z, vx, vy, vz);
             atomicAdd(&tb.csum[c], (double)u);
             atomicAdd(&tb.ccnt[c], 1u);
-            CI[i] = (uint16_t)c;
+            *elem(CI, i) = (uint16_t)c;
         }
         // the next particle has arrived by now; waited for here, before the
         // stores, and not with them at the top of the loop
@@ -230,32 +230,32 @@ __device__ __forceinline__ void step_tile(const FitDev& fd, const Tile& tl, int3
         settle(nu);
         settle(nh);
         if (push && wt) {
-            put_wt(X + i, x);
-            put_wt(Y + i, y);
-            put_wt(Z + i, z);
-            put_wt(VX + i, vx);
-            put_wt(VY + i, vy);
-            put_wt(VZ + i, vz);
-            if (correct) put_wt(U + i, u);
-            if (assign) put_wt(UH + i, uh);
+            put_wt(elem(X, i), x);
+            put_wt(elem(Y, i), y);
+            put_wt(elem(Z, i), z);
+            put_wt(elem(VX, i), vx);
+            put_wt(elem(VY, i), vy);
+            put_wt(elem(VZ, i), vz);
+            if (correct) put_wt(elem(U, i), u);
+            if (assign) put_wt(elem(UH, i), uh);
         } else if (nt && push) {
-            __builtin_nontemporal_store(x, X + i);
-            __builtin_nontemporal_store(y, Y + i);
-            __builtin_nontemporal_store(z, Z + i);
-            __builtin_nontemporal_store(vx, VX + i);
-            __builtin_nontemporal_store(vy, VY + i);
-            __builtin_nontemporal_store(vz, VZ + i);
-            if (correct) __builtin_nontemporal_store(u, U + i);
-            if (assign) __builtin_nontemporal_store(uh, UH + i);
+            __builtin_nontemporal_store(x, elem(X, i));
+            __builtin_nontemporal_store(y, elem(Y, i));
+            __builtin_nontemporal_store(z, elem(Z, i));
+            __builtin_nontemporal_store(vx, elem(VX, i));
+            __builtin_nontemporal_store(vy, elem(VY, i));
+            __builtin_nontemporal_store(vz, elem(VZ, i));
+            if (correct) __builtin_nontemporal_store(u, elem(U, i));
+            if (assign) __builtin_nontemporal_store(uh, elem(UH, i));
         } else if (push) {
-            X[i] = x;
-            Y[i] = y;
-            Z[i] = z;
-            VX[i] = vx;
-            VY[i] = vy;
-            VZ[i] = vz;
-            if (correct) U[i] = u;
-            if (assign) UH[i] = uh;
+            *elem(X, i) = x;
+            *elem(Y, i) = y;
+            *elem(Z, i) = z;
+            *elem(VX, i) = vx;
+            *elem(VY, i) = vy;
+            *elem(VZ, i) = vz;
+            if (correct) *elem(U, i) = u;
+            if (assign) *elem(UH, i) = uh;
         }
     }
     __syncthreads();
