@@ -305,7 +305,9 @@ struct WsLayout {
     size_t st, fd, tiles, jobs, redge2, rmesh, Redge2, vedge, Vp, isp, rp, ucell, lctab, cidx;
     size_t cdata, gprior, scf_rho, scf_sum, scf_tab, sm_basis;
     size_t Y, sigma, yv, ytil, delta, obs, hist, chi2p, partials, total;
-    size_t run, run_sync, run_rows, run_res, run_cell, run_parts;  // run kernel: exchange areas
+    size_t tail, otab;  // after what batched steps use: GH tables of an observation
+    bool run;           // the run kernel's exchange areas, last:
+    size_t run_sync, run_rows, run_res, run_cell, run_parts;
     int seg_cap, row_len, nbj, ncj, npj, J, C, P;  // P: interval sums of the expansion
 };
 
@@ -388,8 +390,10 @@ WsLayout plan(const m2m_obs_layout& L, const m2m_params& P, int64_t n, bool f64,
     w.scf_tab = take(8 * (size_t)std::max(w.P, 1));
     // eigendecomposition of the smoothing penalty (both L_z halves share it)
     w.sm_basis = take(P.smooth ? 8 * smooth_basis_len(P.n_E, P.n_x) : 8);
-    w.run = o;
-    if (cell_index && run_kind(L, P, n)) {
+    w.tail = o;
+    w.otab = take(cell_index && L.kin == M2M_KIN_GH ? w.rp - w.Vp : 0);
+    w.run = cell_index && run_kind(L, P, n);
+    if (w.run) {
         const size_t jobs = (size_t)(w.J + kRunCols - 1) / kRunCols, vw = f64 ? 16 : 8;
         w.run_sync = take(sizeof(RunSync));
         w.run_rows = take(16 * (size_t)run_shape(n, f64, w.J).blocks * (size_t)(w.J + 2 * w.C));
@@ -581,6 +585,60 @@ hipError_t copy_sync(hipStream_t s, void* dst, const void* src, size_t n, hipMem
     return e == hipSuccess ? hipStreamSynchronize(s) : e;
 }
 
+// Pinned host memory for the length of one call that waits for its results: the
+// kernels write into it, where a copy to the caller's pageable array took 9 us
+// of a 56 us observation. At most kPinSlots blocks of kPinBytes exist in a
+// process; a call that finds none free, or needs more, copies instead. Freed
+// with the last context (freeing waits for the whole device).
+constexpr int kPinSlots = 4;
+constexpr size_t kPinBytes = 128 << 10;
+struct PinPool {
+    std::mutex mu;
+    std::vector<void*> idle;
+    int made = 0;
+    int64_t contexts = 0;
+};
+PinPool& pins() {
+    static PinPool* p = new PinPool();  // never destroyed: contexts may outlive statics
+    return *p;
+}
+struct Pinned {
+    void* p = nullptr;
+    explicit Pinned(size_t bytes) {
+        if (bytes > kPinBytes) return;
+        PinPool& g = pins();
+        std::lock_guard<std::mutex> lock(g.mu);
+        if (!g.idle.empty()) {
+            p = g.idle.back();
+            g.idle.pop_back();
+        } else if (g.made < kPinSlots) {
+            g.idle.reserve(kPinSlots);
+            if (hipHostMalloc(&p, kPinBytes, hipHostMallocPortable | hipHostMallocMapped) == hipSuccess)
+                ++g.made;
+            else {
+                p = nullptr;
+                (void)hipGetLastError();
+            }
+        }
+    }
+    ~Pinned() {
+        if (!p) return;
+        PinPool& g = pins();
+        std::lock_guard<std::mutex> lock(g.mu);
+        g.idle.push_back(p);  // reserved
+    }
+    Pinned(const Pinned&) = delete;
+    Pinned& operator=(const Pinned&) = delete;
+};
+void count_context(int d) {
+    PinPool& g = pins();
+    std::lock_guard<std::mutex> lock(g.mu);
+    if ((g.contexts += d) > 0) return;
+    for (void* q : g.idle) (void)hipHostFree(q);
+    g.made -= (int)g.idle.size();
+    g.idle.clear();
+}
+
 m2m_status upload(m2m_ctx* c, size_t off, const std::vector<double>& v) {
     std::vector<unsigned char> b = c->f64 ? as_bytes<double>(v) : as_bytes<float>(v);
     if (b.empty()) return M2M_OK;
@@ -741,7 +799,7 @@ void forget_run(int dev, const void* owner) {
 hipError_t count_run(m2m_ctx* c, int32_t n_steps, int blocks, hipStream_t st) {
     hipError_t e = hipSuccess;
     if (c->run_tag > 0xffffffffu - (uint32_t)kRunMaxSteps || c->run_start > 0x40000000u) {
-        e = hipMemsetAsync(c->ws + c->w.run, 0, c->w.total - c->w.run, st);
+        e = hipMemsetAsync(c->ws + c->w.run_sync, 0, c->w.total - c->w.run_sync, st);
         c->run_tag = 0;
         c->run_start = 0;
         c->run_known = e == hipSuccess;
@@ -1046,7 +1104,7 @@ m2m_status m2m_create(const m2m_potential* pot, const m2m_obs_layout* layout,
     // ---- run kernel: one block of it per compute unit has to fit
     if (hipGetDevice(&c->dev) != hipSuccess) return bail(M2M_EDEVICE);
     c->run_sh = run_shape(n, c->f64, w.J);
-    c->run = w.total > w.run && c->acc64 && g_interleave < 0 && c->dev >= 0 && c->dev < kRunDevices &&
+    c->run = w.run && c->acc64 && g_interleave < 0 && c->dev >= 0 && c->dev < kRunDevices &&
              c->run_sh.blocks <= n_cus() && c->lds + kRunStaticLds <= max_lds();
     if (c->run) {
         c->run_args.n_jobs = (w.J + kRunCols - 1) / kRunCols;
@@ -1115,6 +1173,7 @@ m2m_status m2m_create(const m2m_potential* pot, const m2m_obs_layout* layout,
         copy_sync(c->stream, c->jobs, jb.data(), sizeof(FinJob) * jb.size(), hipMemcpyHostToDevice) != hipSuccess ||
         copy_sync(c->stream, c->fd_dev, &f, sizeof(FitDev), hipMemcpyHostToDevice) != hipSuccess)
         return bail(M2M_EDEVICE);
+    count_context(1);
     *out = c;
     return M2M_OK;
 }
@@ -1281,21 +1340,46 @@ m2m_status m2m_observe(m2m_ctx* c, const double* V_p, const double* sigma_p, dou
     if (c->batch) return fail(c, M2M_ESTATE, "fit is in a batch");
     if (m2m_status w_ = after_batch(c); w_ != M2M_OK) return w_;
     const bool tmp = c->lay.kin == M2M_KIN_GH && V_p && sigma_p;
-    m2m_status s = sync(c);
-    if (s != M2M_OK) return s;
+    // Given GH centres go into tables of their own, and the call waits once, at
+    // its end: five waits (two uploads before, two after to put the fit's centres
+    // back, one download) took 57 us where this takes 47 (4194304 particles,
+    // 2610 observables), of which the kernels are 30.
+    const size_t obs = 8 * (size_t)c->w.J, tab = tmp ? c->w.rp - c->w.Vp : 0;
+    Pinned pin(obs + tab);
+    std::vector<unsigned char> own(pin.p ? 0 : tab);
+    unsigned char* t = pin.p ? static_cast<unsigned char*>(pin.p) + obs : own.data();
+    FitDev f = c->fd;
+    if (pin.p) f.obs_out = static_cast<double*>(pin.p);
     if (tmp) {
-        std::vector<double> V(V_p, V_p + c->fd.n_R), S(sigma_p, sigma_p + c->fd.n_R);
-        for (int p = 0; p < c->fd.n_R; ++p)
-            if (!is_fin(V[p]) || !is_fin(S[p]) || !(S[p] > 0))
+        const int nR = c->fd.n_R;
+        for (int q = 0; q < nR; ++q)
+            if (!is_fin(V_p[q]) || !is_fin(sigma_p[q]) || !(sigma_p[q] > 0))
                 return fail(c, M2M_EINVAL, "V_p, sigma_p must be finite with sigma_p > 0");
-        if ((s = upload_gh(c, V, S)) != M2M_OK) return s;
+        const size_t isp = c->w.isp - c->w.Vp;
+        for (int q = 0; q < nR; ++q) {
+            if (c->f64) {
+                reinterpret_cast<double*>(t)[q] = V_p[q];
+                reinterpret_cast<double*>(t + isp)[q] = 1.0 / sigma_p[q];
+            } else {
+                reinterpret_cast<float*>(t)[q] = (float)V_p[q];
+                reinterpret_cast<float*>(t + isp)[q] = (float)(1.0 / sigma_p[q]);
+            }
+        }
+        f.Vp = c->ws + c->w.otab;
+        f.isp = c->ws + c->w.otab + isp;
     }
-    M2M_HIP(c, launch_step1(c->f64, c->acc64, c->block, c->kin, c->fd, c->n_tiles, c->lds,
-                           kModeObserve, c->stream));
-    M2M_HIP(c, launch_finalize1(c->f64, c->fd, c->n_tiles, kModeObserve, c->stream));
-    if ((s = sync(c)) != M2M_OK) return s;
-    M2M_HIP(c, copy_sync(c->stream, y, c->fd.obs_out, 8 * (size_t)c->w.J, hipMemcpyDeviceToHost));
-    if (tmp && (s = upload_gh(c, c->Vp, c->sp)) != M2M_OK) return s;
+    hipError_t e = tmp ? hipMemcpyAsync(f.Vp, t, tab, hipMemcpyHostToDevice, c->stream) : hipSuccess;
+    if (e == hipSuccess)
+        e = launch_step1(c->f64, c->acc64, c->block, c->kin, f, c->n_tiles, c->lds, kModeObserve,
+                         c->stream);
+    if (e == hipSuccess) e = launch_finalize1(c->f64, f, c->n_tiles, kModeObserve, c->stream);
+    if (e == hipSuccess && !pin.p)
+        e = hipMemcpyAsync(y, f.obs_out, obs, hipMemcpyDeviceToHost, c->stream);
+    // also after an error: what was queued uses the tables and the results' place
+    const hipError_t ended = hipStreamSynchronize(c->stream);
+    M2M_HIP(c, e);
+    M2M_HIP(c, ended);
+    if (pin.p) std::memcpy(y, pin.p, obs);
     return M2M_OK;
 }
 
@@ -1476,6 +1560,7 @@ m2m_status m2m_destroy(m2m_ctx* c) {
     if (c->cap) (void)hipStreamDestroy(c->cap);
     if (c->own_ws) (void)hipFree(c->ws);
     delete c;
+    count_context(-1);
     return M2M_OK;
 }
 
@@ -1555,8 +1640,8 @@ struct m2m_batch {
 namespace {
 
 size_t footprint(const m2m_ctx* c) {
-    // without the run kernel's areas, which no batched step uses
-    return (size_t)c->n * 8 * (c->f64 ? 8 : 4) + c->w.run;
+    // without what no batched step needs (a run's exchange areas)
+    return (size_t)c->n * 8 * (c->f64 ? 8 : 4) + c->w.tail;
 }
 
 hipError_t grow(void** p, size_t* cap, size_t need) {
