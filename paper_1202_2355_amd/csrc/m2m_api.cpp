@@ -521,6 +521,7 @@ struct m2m_ctx {
     bool acc64 = true;
     bool wt = false;  // write-through particle stores (kModeWriteThrough)
     bool il = false;  // interleaved tiles in the step kernel (kModeInterleave)
+    bool back = false;  // the next of its steps takes them backwards (kModeBack)
     int dev = 0;      // the device the context was created on
     bool run = false; // steps by the run kernel (see use_run)
     RunShape run_sh{};
@@ -732,10 +733,10 @@ m2m_status refresh_potential(m2m_ctx* c) {
 
 // One M2M step: the step kernel over all tiles, then the finalize.
 hipError_t launch_one_step(m2m_ctx* c, hipStream_t s) {
+    const int32_t il = c->il ? kModeInterleave | (c->back ? kModeBack : 0) : 0;
+    c->back = !c->back;
     hipError_t e = launch_step1(c->f64, c->acc64, c->block, c->kin, c->fd, c->n_tiles, c->lds,
-                               kModeStep | (c->wt ? kModeWriteThrough : 0) |
-                                   (c->il ? kModeInterleave : 0),
-                               s);
+                               kModeStep | (c->wt ? kModeWriteThrough : 0) | il, s);
     if (e == hipSuccess) e = launch_finalize1(c->f64, c->fd, c->n_tiles, kModeStep, s);
     return e;
 }

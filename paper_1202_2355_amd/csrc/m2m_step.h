@@ -47,10 +47,19 @@ __device__ __forceinline__ void step_tile(const FitDev& fd, const Tile& tl, int3
     const G<T> __restrict__ UH = gmem<T>(fd.uh) + off;
     const G<uint16_t> __restrict__ CI = gmem(fd.cidx) + off;
     const int len = (int)(il ? fd.n : tl.end - tl.begin);
-    const int istep = il ? tl.n_rows * BLOCK : BLOCK;
+    int istep = il ? tl.n_rows * BLOCK : BLOCK;
     int i = il ? tl.row * BLOCK + (int)threadIdx.x : (int)threadIdx.x;
+    if (il && (mode & kModeBack)) {
+        // the tile's chunks from the last to the first: a lane past the end of
+        // the array (in the last chunk) begins one chunk earlier, and the index
+        // goes negative, so above len as unsigned, at the end
+        const int last = (len - 1) / BLOCK;
+        if (last >= tl.row) i += (last - tl.row) / tl.n_rows * istep;
+        if (i >= len) i -= istep;
+        istep = -istep;
+    }
     T nx = T(0), ny = T(0), nz = T(0), nvx = T(0), nvy = T(0), nvz = T(0), nu = T(0), nh = T(1);
-    if (i < len) {
+    if ((unsigned)i < (unsigned)len) {
         nx = *elem(X, i);
         ny = *elem(Y, i);
         nz = *elem(Z, i);
@@ -154,10 +163,10 @@ __device__ __forceinline__ void step_tile(const FitDev& fd, const Tile& tl, int3
 
     // software pipeline: the loads of the next particle are in flight while
     // the current one is computed
-    for (; i < len; i += istep) {
+    for (; (unsigned)i < (unsigned)len; i += istep) {
         T x = nx, y = ny, z = nz, vx = nvx, vy = nvy, vz = nvz, u = nu, uh = nh;
         const int inext = i + istep;
-        if (inext < len) {
+        if ((unsigned)inext < (unsigned)len) {
             if constexpr (nt) {
                 nx = __builtin_nontemporal_load(elem(X, inext));
                 ny = __builtin_nontemporal_load(elem(Y, inext));
