@@ -332,11 +332,16 @@ constexpr int kRunMaxJ = 1024;
 constexpr int64_t kRunMaxN = int64_t(1) << 22;
 
 // The run kernel is built for fits with radial bins in an analytic potential
-// and no smoothing of the priors. A refresh on every step is left out too: the
-// rows of two refreshes in a row would share one buffer.
+// (with smoothed priors: grids of at least two cells). A refresh on every step is
+// left out too: the rows of two refreshes in a row would share one buffer.
 bool run_kind(const m2m_obs_layout& L, const m2m_params& P, int64_t n) {
-    return L.dens == M2M_DENS_BINS && P.scf_nr == 0 && !P.smooth && P.prior_every != 1 &&
-           num_obs(L) <= kRunMaxJ && n <= kRunMaxN;
+    return L.dens == M2M_DENS_BINS && P.scf_nr == 0 && !(P.smooth && P.n_E * P.n_x < 2) &&
+           P.prior_every != 1 && num_obs(L) <= kRunMaxJ && n <= kRunMaxN;
+}
+
+// LDS of the run kernel's smoothing: two grids
+size_t run_smooth_lds(const m2m_params& P) {
+    return P.smooth ? 16 * (size_t)P.n_E * (size_t)P.n_x : 0;
 }
 
 // cell_index = false: no per-particle cell index (observation only)
@@ -399,7 +404,8 @@ WsLayout plan(const m2m_obs_layout& L, const m2m_params& P, int64_t n, bool f64,
         w.run_rows = take(16 * (size_t)run_shape(n, f64, w.J).blocks * (size_t)(w.J + 2 * w.C));
         w.run_res = take(vw * (size_t)w.J);
         w.run_cell = take(vw * (size_t)w.C);
-        w.run_parts = take(16 * jobs * (size_t)kRunMaxSteps);
+        w.run_parts = take(16 * jobs * (size_t)kRunMaxSteps +
+                           (P.smooth ? 8 * (6 * (size_t)w.C + 2 * (2 + 6 * (size_t)kSmoothMaxPoints)) : 0));
     }
     w.total = o;
     return w;
@@ -816,9 +822,10 @@ m2m_status launch_run(m2m_ctx* c, int32_t n_steps, int32_t correct) {
     const RunCall call{n_steps, correct ? 1 : 0, c->run_known ? 1 : 0,
                        c->run_start - (uint32_t)c->run_sh.blocks, c->run_tag - (uint32_t)n_steps};
     const hipError_t e = ordered_run(c->dev, c, c->stream, [&] {
-        return (c->f64 ? launch_run_f64 : launch_run_f32)(
-            c->run_sh.block, c->kin, c->fd, c->run_args, c->run_sh.blocks,
-            c->lds + (size_t)c->run_args.keep_bytes, call, c->stream);
+        const auto launch = c->par.smooth ? (c->f64 ? launch_run_smooth_f64 : launch_run_smooth_f32)
+                                          : (c->f64 ? launch_run_f64 : launch_run_f32);
+        return launch(c->run_sh.block, c->kin, c->fd, c->run_args, c->run_sh.blocks,
+                      (size_t)run_smooth_at(c->run_args) + run_smooth_lds(c->par), call, c->stream);
     });
     if (e != hipSuccess) c->run_known = false;  // counted, but not run
     if (e != hipSuccess) return hip_fail(c, e, "run of steps");
@@ -832,7 +839,7 @@ int32_t kept_bytes(const m2m_ctx* c, int block, int blocks) {
     const int64_t slots = (c->n + per - 1) / per * block;
     const int vals = c->lay.kin != M2M_KIN_GH ? 0 : (c->lay.gh_nmax == 4 ? 4 : kMaxGH);
     const size_t kept = (size_t)slots * (vals * (c->f64 ? 8u : 4u) + 4u);
-    return c->lds + kept + kRunStaticLds <= max_lds() ? (int32_t)kept : 0;
+    return c->lds + kept + run_smooth_lds(c->par) + 8 + kRunStaticLds <= max_lds() ? (int32_t)kept : 0;
 }
 
 // Capture n repetitions of body(stream) on the capture stream, instantiate
@@ -1106,7 +1113,7 @@ m2m_status m2m_create(const m2m_potential* pot, const m2m_obs_layout* layout,
     if (hipGetDevice(&c->dev) != hipSuccess) return bail(M2M_EDEVICE);
     c->run_sh = run_shape(n, c->f64, w.J);
     c->run = w.run && c->acc64 && g_interleave < 0 && c->dev >= 0 && c->dev < kRunDevices &&
-             c->run_sh.blocks <= n_cus() && c->lds + kRunStaticLds <= max_lds();
+             c->run_sh.blocks <= n_cus() && c->lds + run_smooth_lds(c->par) + 8 + kRunStaticLds <= max_lds();
     if (c->run) {
         c->run_args.n_jobs = (w.J + kRunCols - 1) / kRunCols;
         c->run_args.n_cell_jobs = (w.C + kRunCols - 1) / kRunCols;
@@ -1825,7 +1832,7 @@ m2m_status run_fits(m2m_batch* b) {
     int64_t ntot = 0;
     int want = 0, least = 0;
     for (m2m_ctx* c : b->fits) {
-        if (!c->run || c->dev != b->fits[0]->dev) return M2M_OK;
+        if (!c->run || c->par.smooth || c->dev != b->fits[0]->dev) return M2M_OK;
         ntot += c->n;
         want += c->run_sh.blocks;
         least += (c->run_args.n_jobs + 2) / 3;

@@ -198,8 +198,14 @@ struct RunArgs {
     uint64_t *rows;   // blocks x (J + 2 C) sums, 2 words each
     uint64_t *res;    // J entries of the force table, 1 word (FP32) or 2
     uint64_t *cell;   // C cell priors, the same
-    uint64_t *parts;  // kRunMaxSteps x n_jobs parts of chi^2, 2 words each
+    // kRunMaxSteps x n_jobs parts of chi^2, 2 words each; where the priors are
+    // smoothed 6 C words and 2 + 6 kSmoothMaxPoints per grid half follow
+    uint64_t *parts;
 };
+// LDS offset of the prior smoothing's two grids (FP64)
+__host__ __device__ inline int run_smooth_at(const RunArgs& a) {
+    return (a.keep_at + a.keep_bytes + 7) & ~7;
+}
 
 // What one launch does: n_steps steps with the force of change on or off (a fit
 // of a batch: as many of them as it has left, with its own setting). known:
@@ -242,6 +248,11 @@ hipError_t launch_run_f32(int block, int kin, const FitDev& fd, const RunArgs& r
                           size_t lds, const RunCall& call, hipStream_t s);
 hipError_t launch_run_f64(int block, int kin, const FitDev& fd, const RunArgs& ra, int blocks,
                           size_t lds, const RunCall& call, hipStream_t s);
+// the same of a fit whose priors are smoothed
+hipError_t launch_run_smooth_f32(int block, int kin, const FitDev& fd, const RunArgs& ra, int blocks,
+                                 size_t lds, const RunCall& call, hipStream_t s);
+hipError_t launch_run_smooth_f64(int block, int kin, const FitDev& fd, const RunArgs& ra, int blocks,
+                                 size_t lds, const RunCall& call, hipStream_t s);
 hipError_t launch_runs_f32(int block, int kin, const FitDev* fits, const RunArgs* ras,
                            const RunTile* tiles, int blocks, size_t lds, int n_steps, hipStream_t s);
 hipError_t launch_runs_f64(int block, int kin, const FitDev* fits, const RunArgs* ras,

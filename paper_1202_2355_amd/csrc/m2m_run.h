@@ -9,6 +9,7 @@
 #include <type_traits>
 
 #include "m2m_device.h"
+#include "m2m_smooth.h"
 
 namespace m2m {
 namespace {
@@ -228,12 +229,26 @@ __device__ __forceinline__ void obs_job(const FitDev& fd, const RunArgs& ra, con
     __syncthreads();
 }
 
+// The exchange areas of the smoothing (kSmWords words): the cells' data, their
+// transform and the smoothed priors (C values each), then per grid half the mean of the
+// data and the scores of the three search stages.
+struct SmWords {
+    G<Word> data, what, prior, mean, score;
+};
+__device__ __forceinline__ SmWords sm_words(const RunArgs& ra, int C, int half) {
+    const G<Word> p = gmem<Word>(ra.parts) + (size_t)ra.n_jobs * kRunMaxSteps * 2;
+    const G<Word> h = p + (size_t)C * 6 + (size_t)half * (2 + 3 * kSmoothMaxPoints * 2);
+    return SmWords{p, p + (size_t)C * 2, p + (size_t)C * 4, h, h + 2};
+}
+
 // Cell job q of a refresh step: cells 16 q .. 16 q + 15, their weight sums
-// and counts over all rows, and the means that become the priors.
-template <typename T, int BLOCK>
+// and counts over all rows, and the means that become the priors or (SMOOTH)
+// the data of their smoothing. ptag: the launch's last refresh before this one
+// (0: none), whose smoothed priors another block may have written.
+template <typename T, int BLOCK, bool SMOOTH>
 __device__ __forceinline__ void cell_job(const FitDev& fd, const RunArgs& ra, const Waiter& w, int q,
-                                         int n_rows, int ncol, uint32_t tag, double (*part)[kRunCols],
-                                         double (*part2)[kRunCols]) {
+                                         int n_rows, int ncol, uint32_t tag, uint32_t ptag,
+                                         double (*part)[kRunCols], double (*part2)[kRunCols]) {
     constexpr int RG = BLOCK / kRunCols, NW = BLOCK / 64;
     const int t = thread_here(), lane = t & 63, wave = t >> 6;
     const int c = q * kRunCols + (t & (kRunCols - 1));
@@ -261,13 +276,207 @@ __device__ __forceinline__ void cell_job(const FitDev& fd, const RunArgs& ra, co
             cnt += part2[v][lane];
         }
         // the cell's mean weight, or the previous prior if it is empty
-        const double d = cnt > 0.0 ? tot / cnt : gmem(fd.gprior)[c];
-        gmem(fd.cdata)[c] = d;
-        gmem(fd.gprior)[c] = d;
-        gmem<T>(fd.ucell)[c] = (T)d;
-        Words<T>::put(gmem<Word>(ra.cell) + (size_t)c * Words<T>::n, (T)d, tag);
+        if constexpr (SMOOTH) {
+            const SmWords sw = sm_words(ra, fd.C, 0);
+            const double d = cnt > 0.0 ? tot / cnt
+                             : ptag   ? take<double>(w, sw.prior + (size_t)c * 2, ptag)
+                                      : gmem(fd.gprior)[c];
+            gmem(fd.cdata)[c] = d;
+            Words<double>::put(sw.data + (size_t)c * 2, d, tag);
+        } else {
+            const double d = cnt > 0.0 ? tot / cnt : gmem(fd.gprior)[c];
+            gmem(fd.cdata)[c] = d;
+            gmem(fd.gprior)[c] = d;
+            gmem<T>(fd.ucell)[c] = (T)d;
+            Words<T>::put(gmem<Word>(ra.cell) + (size_t)c * Words<T>::n, (T)d, tag);
+        }
     }
     __syncthreads();
+}
+
+// ------------------------------------------------------------- smoothing ----
+// 10^x for the search's lambdas, within 1e-14 for |x| < 30: 2^k e^r with
+// |r| <= ln(2) / 2, e^r by its Taylor polynomial of degree 14 (remainder 1e-19)
+// over 14!, the coefficients 14! / n! made on the way. The library's exp10 kept
+// its coefficients in registers through the whole step loop: 16 of 128 spilled,
+// and 24 steps of 600 000 FP32 particles with one refresh took 332 us, so 285.
+__device__ __forceinline__ double pow10_of(double x) {
+    const double k = rint(x * 3.32192809488736234787);
+    const double r = fma(x, 3.32192809488736234787, -k) * 0.693147180559945309417;
+    double e = 1.0, c = 1.0;
+#pragma unroll 1
+    for (int n = 14; n >= 1; --n) {
+        c *= n;
+        e = fma(e, r, c);
+    }
+    return ldexp(e / c, (int)k);
+}
+
+// The thin-plate smoothing of one prior grid (the method and its search are
+// described at the finalize kernel's smooth_priors), its n cells from `base`,
+// over the blocks of a run. One block reads the basis (four matrices of (n/4)^2,
+// 2 MB for 50 x 20 cells) twice at what one compute unit can have in flight and
+// scores three stages of up to 65 lambdas alone: 100 us a refresh. Here
+//   transform   a job of 16 outputs per block, from the tagged data,
+//   search      one wave per lambda on as few blocks as hold them, the scores
+//               tagged; every block that goes on finds the minimum itself,
+//   back        one wave per row of the basis, the rows of the four parities of a
+//               cell quadruple in four neighbouring waves, which then hold
+//               everything that its cells need.
+// Six exchanges, 32 us a refresh in all (200 003 FP32 particles, 50 x 20 cells: 52
+// steps 959 us by the step and finalize kernels, 408 so). The areas are free again at the next refresh,
+// at least two steps later: no block is past the step between them before
+// all have left this one.
+template <typename T, int BLOCK>
+__device__ __forceinline__ void run_smooth(const FitDev& fd, const RunArgs& ra, const Waiter& w, int half,
+                                           int b, int nb, uint32_t tag, unsigned char* lds,
+                                           double (*part)[kRunCols], int* pick) {
+    constexpr int RG = BLOCK / kRunCols, NW = BLOCK / 64, QPB = NW / 4;
+    const int t = thread_here(), lane = t & 63, wave = t >> 6;
+    // as values that the compiler knows nothing of, so that nothing is derived
+    // from them before the step loop and held through it
+    int nE = fd.n_E, nx = fd.n_x, base = half * fd.cell_half;
+    asm volatile("" : "+s"(nE), "+s"(nx), "+s"(base));
+    const int n = nE * nx;
+    const G<const double> basis = gmem<const double>(fd.sm_basis);
+    const SmBlocks B = sm_blocks(nE, nx);
+    const SmWords sw = sm_words(ra, fd.C, half);
+    const G<Word> data = sw.data + (size_t)base * 2, what = sw.what + (size_t)base * 2;
+    double* sa = reinterpret_cast<double*>(lds);
+    double* sb = sa + n;
+
+    // transform: w^ = Q_b^T (folded data), jobs of 16 outputs of one parity block
+    const int j1 = (B.o1 + 15) / 16, j2 = j1 + (B.o2 - B.o1 + 15) / 16,
+              j3 = j2 + (B.o3 - B.o2 + 15) / 16, jobs = j3 + (B.o4 - B.o3 + 15) / 16;
+    if (b < jobs) {
+        for (int c = t; c < n; c += BLOCK) sb[c] = take<double>(w, data + (size_t)c * 2, tag);
+        __syncthreads();
+        if (b == 0 && wave == 0) {
+            double sm = 0.0;
+            for (int c = lane; c < n; c += 64) sm += sb[c];
+            for (int off = 32; off >= 1; off >>= 1) sm += __shfl_xor(sm, off, 64);
+            if (lane == 0) Words<double>::put(sw.mean, sm / n, tag);
+        }
+        for (int c = t; c < n; c += BLOCK)
+            sa[c] = fold_cell(B, nE, nx, c, [&](int q) { return sb[q]; });
+        __syncthreads();
+        for (int q = b; q < jobs; q += nb) {
+            const int bb = q < j1 ? 0 : (q < j2 ? 1 : (q < j3 ? 2 : 3));
+            const int o0 = B.off(bb), m = B.off(bb + 1) - o0;
+            const int o = (q - (bb == 0 ? 0 : (bb == 1 ? j1 : (bb == 2 ? j2 : j3)))) * 16 + (t & 15);
+            double s = 0.0;
+            if (o < m) {
+                const G<const double> Q = basis + B.qoff(bb) + o;
+                int r = t >> 4;
+                for (; r + 3 * RG < m; r += 4 * RG) {
+                    double v[4];
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) v[u] = Q[(size_t)(r + u * RG) * m];
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) s = fma(v[u], sa[o0 + r + u * RG], s);
+                }
+                for (; r < m; r += RG) s = fma(Q[(size_t)r * m], sa[o0 + r], s);
+            }
+            s += __shfl_xor(s, 16, 64);
+            s += __shfl_xor(s, 32, 64);
+            if (lane < kRunCols) part[wave][lane] = s;
+            __syncthreads();
+            if (t < kRunCols && o < m) {
+                double tot = 0.0;
+                for (int v = 0; v < NW; ++v) tot += part[v][lane];
+                Words<double>::put(what + (size_t)(o0 + o) * 2, tot, tag);
+            }
+            __syncthreads();
+        }
+    }
+
+    // search, by the blocks that score lambdas and those that transform back
+    const int quads = B.mE0 * B.mX0, scorers = (max(fd.sm_k1, 65) + NW - 1) / NW;
+    if (b >= scorers && b * QPB >= quads) return;
+    for (int c = t; c < n; c += BLOCK) {
+        sa[c] = basis[c];  // eigenvalues
+        sb[c] = take<double>(w, what + (size_t)c * 2, tag);
+    }
+    __syncthreads();
+    // stage 0: sm_k1 points lo + 0.25 i; stages 1 and 2: 65 points lo + (hi - lo) i / 64
+    double lo = fd.sm_plo, hi = 0.0;
+    int best = 0;
+#pragma unroll 1
+    for (int st = 0; st < 3; ++st) {
+        const int npts = st == 0 ? fd.sm_k1 : 65;
+        const G<Word> sc = sw.score + (size_t)st * kSmoothMaxPoints * 2;
+        for (int i = b * NW + wave; i < npts; i += nb * NW) {
+            const double lam = pow10_of(st == 0 ? lo + 0.25 * i : lo + (hi - lo) * i / 64.0);
+            double out;
+            gcv_points<1>(sa, sb, n, lane, &lam, &out);
+            if (lane == 0) Words<double>::put(sc + (size_t)i * 2, out, tag);
+        }
+        if (wave == 0) {
+            int bi = npts;
+            double bg = 0.0;
+            for (int i = lane; i < npts; i += 64) {
+                const double g = take<double>(w, sc + (size_t)i * 2, tag);
+                if (bi == npts || g < bg) {
+                    bg = g;
+                    bi = i;
+                }
+            }
+            for (int off = 32; off >= 1; off >>= 1) {
+                const double og = __shfl_xor(bg, off, 64);
+                const int oi = __shfl_xor(bi, off, 64);
+                if (oi < npts && (bi == npts || og < bg || (og == bg && oi < bi))) {
+                    bg = og;
+                    bi = oi;
+                }
+            }
+            if (lane == 0) *pick = bi < npts ? bi : 0;
+        }
+        __syncthreads();
+        best = __builtin_amdgcn_readfirstlane(*pick);
+        __syncthreads();
+        if (st == 2) break;
+        // the next stage: between the neighbours of the best point
+        const double from = lo;
+        const int i0 = best > 0 ? best - 1 : 0, i1 = best < npts - 1 ? best + 1 : npts - 1;
+        lo = st == 0 ? from + 0.25 * i0 : from + (hi - from) * i0 / 64.0;
+        hi = st == 0 ? from + 0.25 * i1 : from + (hi - from) * i1 / 64.0;
+    }
+    if (b * QPB >= quads) return;
+    const double lam = pow10_of(lo + (hi - lo) * best / 64.0);
+    for (int c = t; c < n; c += BLOCK) sa[c] = sb[c] / (1.0 + lam * sa[c]);
+    __syncthreads();
+
+    // back: wave 4 s + bb takes row (i, j) of parity block bb for slot s's
+    // quadruple of cells (i, j), (i, nx-1-j), (nE-1-i, j), (nE-1-i, nx-1-j)
+    const int bb = wave & 3, pE = bb >> 1, pX = bb & 1;
+    for (int q0 = b * QPB; q0 < quads; q0 += nb * QPB) {
+        const int q = q0 + (wave >> 2), i = q / B.mX0, j = q - i * B.mX0;
+        double s = 0.0;
+        if (q < quads && i < B.mE(pE) && j < B.mX(pX)) {
+            const int o0 = B.off(bb), m = B.off(bb + 1) - o0;
+            const G<const double> Q = basis + B.qoff(bb) + (size_t)(i * B.mX(pX) + j) * m;
+            for (int k = lane; k < m; k += 64) s = fma(Q[k], sa[o0 + k], s);
+        }
+        for (int off = 32; off >= 1; off >>= 1) s += __shfl_xor(s, off, 64);
+        if (lane == 0) part[wave >> 2][bb] = s;
+        __syncthreads();
+        if (t < 4 * QPB && q0 + (t >> 2) < quads) {
+            const int qq = q0 + (t >> 2), qi = qq / B.mX0, qj = qq - qi * B.mX0;
+            const int k = (t & 2) ? nE - 1 - qi : qi, l = (t & 1) ? nx - 1 - qj : qj;
+            if (!((t & 2) && k == qi) && !((t & 1) && l == qj)) {
+                const double floor_v = 1e-3 * take<double>(w, sw.mean, tag);
+                const double v = fmax(unfold_cell(B, nE, nx, k, l, [&](int p, int, int) {
+                                          return part[t >> 2][p];
+                                      }), floor_v);
+                const int c = base + k * nx + l;
+                gmem(fd.gprior)[c] = v;
+                gmem<T>(fd.ucell)[c] = (T)v;
+                Words<double>::put(sw.prior + (size_t)c * 2, v, tag);
+                Words<T>::put(gmem<Word>(ra.cell) + (size_t)c * Words<T>::n, (T)v, tag);
+            }
+        }
+        __syncthreads();
+    }
 }
 
 // ------------------------------------------------------------------- run ----
@@ -279,7 +488,8 @@ __device__ __forceinline__ void cell_job(const FitDev& fd, const RunArgs& ra, co
 // KNOWN: the launch's start0 and tag0 come with the call; OWN: a fit of a
 // batch, with its own steps left and setting (both at compile time: as branches
 // at the start of the kernel they cost a launch of one step 0.6-0.9 of 12.4 us).
-template <typename T, int BLOCK, int KIN, bool KNOWN, bool OWN>
+// SMOOTH: the priors are smoothed at every refresh.
+template <typename T, int BLOCK, int KIN, bool KNOWN, bool OWN, bool SMOOTH>
 __device__ __forceinline__ void run_fit(const FitDev& fd, const RunArgs& ra, int b,
                                         const uint32_t n_blocks, const RunCall& call) {
     extern __shared__ __align__(16) unsigned char lds_raw[];
@@ -391,6 +601,7 @@ __device__ __forceinline__ void run_fit(const FitDev& fd, const RunArgs& ra, int
     kept.code = reinterpret_cast<uint32_t*>(kept.val + Kept<T, KIN>::nv * kept.slots);
     const bool keep = !alone && ra.keep_bytes > 0;
     bool assigned = false;  // some step of this launch wrote the priors
+    uint32_t ptag = 0u;     // the last refresh of this launch
 
     for (int k = 0; k < n_steps; ++k) {
         const uint32_t tag = tag0 + 1u + (uint32_t)k;
@@ -493,7 +704,12 @@ __device__ __forceinline__ void run_fit(const FitDev& fd, const RunArgs& ra, int
         if (refresh)
             // cell jobs from the last block down, away from the observable jobs
             for (int q = nb - 1 - b; q < ra.n_cell_jobs; q += nb)
-                cell_job<T, BLOCK>(fd, ra, wt, q, nb, ncol, tag, part, part2);
+                cell_job<T, BLOCK, SMOOTH>(fd, ra, wt, q, nb, ncol, tag, ptag, part, part2);
+        if (SMOOTH && refresh) {
+            for (int half = 0; half <= (fd.cell_flags & 1); ++half)
+                run_smooth<T, BLOCK>(fd, ra, wt, half, b, nb, tag, lds_raw + run_smooth_at(ra), part, &flag);
+            ptag = tag;
+        }
         if (!last) {
             for (int j = t0; j < J; j += BLOCK)
                 tb.rp[j] = take<T>(wt, gmem<const Word>(ra.res) + (size_t)j * Words<T>::n, tag);
@@ -535,10 +751,10 @@ __device__ __forceinline__ void run_fit(const FitDev& fd, const RunArgs& ra, int
     }
 }
 
-template <typename T, int BLOCK, int KIN, bool KNOWN>
+template <typename T, int BLOCK, int KIN, bool KNOWN, bool SMOOTH>
 __global__ __launch_bounds__(BLOCK) void k_run(const FitDev fd, const RunArgs ra,
                                                const RunCall call) {
-    run_fit<T, BLOCK, KIN, KNOWN, false>(fd, ra, (int)blockIdx.x, gridDim.x, call);
+    run_fit<T, BLOCK, KIN, KNOWN, false, SMOOTH>(fd, ra, (int)blockIdx.x, gridDim.x, call);
 }
 
 // the fits of a table, each over its own blocks (no fit waits for another)
@@ -547,7 +763,7 @@ __global__ __launch_bounds__(BLOCK) void k_runs(const FitDev* __restrict__ fits,
                                                 const RunArgs* __restrict__ ras,
                                                 const RunTile* __restrict__ tiles, int32_t n_steps) {
     const RunTile t = tiles[blockIdx.x];
-    run_fit<T, BLOCK, KIN, false, true>(fits[t.fit], ras[t.fit], t.b, (uint32_t)t.nb, RunCall{n_steps, 1, 0, 0u, 0u});
+    run_fit<T, BLOCK, KIN, false, true, false>(fits[t.fit], ras[t.fit], t.b, (uint32_t)t.nb, RunCall{n_steps, 1, 0, 0u, 0u});
 }
 
 // f(the kind of kinematic observables as a compile-time constant)
@@ -564,16 +780,20 @@ hipError_t with_kin(int kin, F&& f) {
     return hipGetLastError();
 }
 
-template <typename T, int BLOCK>
+// SMOOTH: built without KNOWN only (a step of such a fit is rarely launched alone)
+template <typename T, int BLOCK, bool SMOOTH>
 hipError_t launch_run_t(int kin, const FitDev& fd, const RunArgs& ra, int blocks, size_t lds,
                         const RunCall& call, hipStream_t s) {
     return with_kin(kin, [&](auto K) {
-        if (call.known)
-            hipLaunchKernelGGL((k_run<T, BLOCK, decltype(K)::value, true>), dim3(blocks), dim3(BLOCK),
-                               lds, s, fd, ra, call);
-        else
-            hipLaunchKernelGGL((k_run<T, BLOCK, decltype(K)::value, false>), dim3(blocks), dim3(BLOCK),
-                               lds, s, fd, ra, call);
+        constexpr int kind = decltype(K)::value;
+        if constexpr (!SMOOTH)
+            if (call.known) {
+                hipLaunchKernelGGL((k_run<T, BLOCK, kind, true, false>), dim3(blocks), dim3(BLOCK), lds,
+                                   s, fd, ra, call);
+                return;
+            }
+        hipLaunchKernelGGL((k_run<T, BLOCK, kind, false, SMOOTH>), dim3(blocks), dim3(BLOCK), lds, s, fd,
+                           ra, call);
     });
 }
 

@@ -5,8 +5,8 @@ namespace m2m {
 
 hipError_t launch_run_f32(int block, int kin, const FitDev& fd, const RunArgs& ra, int blocks,
                           size_t lds, const RunCall& call, hipStream_t s) {
-    if (block == 512) return launch_run_t<float, 512>(kin, fd, ra, blocks, lds, call, s);
-    if (block == 1024) return launch_run_t<float, 1024>(kin, fd, ra, blocks, lds, call, s);
+    if (block == 512) return launch_run_t<float, 512, false>(kin, fd, ra, blocks, lds, call, s);
+    if (block == 1024) return launch_run_t<float, 1024, false>(kin, fd, ra, blocks, lds, call, s);
     return hipErrorInvalidValue;
 }
 

@@ -5,7 +5,7 @@ namespace m2m {
 
 hipError_t launch_run_f64(int block, int kin, const FitDev& fd, const RunArgs& ra, int blocks,
                           size_t lds, const RunCall& call, hipStream_t s) {
-    if (block == 512) return launch_run_t<double, 512>(kin, fd, ra, blocks, lds, call, s);
+    if (block == 512) return launch_run_t<double, 512, false>(kin, fd, ra, blocks, lds, call, s);
     return hipErrorInvalidValue;
 }
 
