@@ -995,17 +995,25 @@ m2m_status m2m_create(const m2m_potential* pot, const m2m_obs_layout* layout,
     c->kin = kin_class(c->lay.kin, c->lay.gh_nmax, c->lay.dens, c->par.scf_nr > 0);
     c->w = plan(c->lay, c->par, n, c->f64);
     const WsLayout& w = c->w;
-    const int kpriv = g_kpriv_cap > 0 ? std::min(private_copies(c->f64, w.J), g_kpriv_cap)
-                                      : private_copies(c->f64, w.J);
     c->acc64 = c->f64 || g_deposit == M2M_DEPOSIT_F64;
     c->wt = (size_t)n * 8 * (c->f64 ? 8 : 4) <= kWriteThroughMax;
     // interleaved particle indices are 32-bit: n + n_tiles * block stays below 2^31
     c->il = (g_interleave < 0 ? (size_t)n * 8 * (c->f64 ? 8 : 4) > kStreamMin : g_interleave == 1) &&
             n < (int64_t(1) << 30);
-    c->lds = step_lds_bytes(c->f64, c->acc64, w.J, radial_intervals(c->lay),
-                            c->lay.kin == M2M_KIN_NONE ? 0 : c->lay.n_R,
-                            c->lay.kin == M2M_KIN_LOSVD ? c->lay.n_v : 0, kpriv, w.C,
-                            c->par.scf_nr, c->par.scf_lmax);
+    const auto lds_of = [&](int copies) {
+        return step_lds_bytes(c->f64, c->acc64, w.J, radial_intervals(c->lay),
+                              c->lay.kin == M2M_KIN_NONE ? 0 : c->lay.n_R,
+                              c->lay.kin == M2M_KIN_LOSVD ? c->lay.n_v : 0, copies, w.C,
+                              c->par.scf_nr, c->par.scf_lmax);
+    };
+    // spherical harmonics deposit 2 (l_max + 1)^2 values per particle: with
+    // a block that has a compute unit to itself anyway, more copies
+    const int few = private_copies(w.J, 48 << 10);
+    const bool many = c->lay.dens == M2M_DENS_ALM && !c->f64 && c->block == 1024 && n >= (1 << 18);
+    int kpriv = many ? private_copies(w.J, 112 << 10) : few;
+    if (g_kpriv_cap > 0) kpriv = std::min(kpriv, g_kpriv_cap);
+    while (kpriv > few && lds_of(kpriv) > max_lds()) kpriv >>= 1;
+    c->lds = lds_of(kpriv);
     if (c->lds > max_lds()) {
         delete c;
         return M2M_EUNSUPPORTED;
@@ -2335,8 +2343,8 @@ extern "C" m2m_status m2m_observe_noalloc(const m2m_obs_layout* layout, double m
     if (w.rp - w.redge2 > kNoAllocStage)
         return na_fail(M2M_ENOMEM, "observation tables exceed the %zu-byte staging area",
                        kNoAllocStage);
-    const int kpriv = g_kpriv_cap > 0 ? std::min(private_copies(f64, w.J), g_kpriv_cap)
-                                      : private_copies(f64, w.J);
+    const int few = private_copies(w.J, 48 << 10);
+    const int kpriv = g_kpriv_cap > 0 ? std::min(few, g_kpriv_cap) : few;
     const bool acc64 = f64 || g_deposit == M2M_DEPOSIT_F64;
     const size_t lds = step_lds_bytes(f64, acc64, w.J, radial_intervals(L), nR,
                                       L.kin == M2M_KIN_LOSVD ? L.n_v : 0, kpriv, w.C, 0, 0);

@@ -305,6 +305,6 @@ hipError_t launch_residuals(bool f64, const FitDev* fit, hipStream_t s);
 size_t step_lds_bytes(bool f64, bool acc64, int J, int n_r, int n_R, int n_v, int kpriv, int C,
                       int scf_nr, int scf_lmax);
 int kin_class(int kin, int gh_nmax, int dens, bool scf);
-int private_copies(bool f64, int J);
+int private_copies(int J, size_t bytes);
 
 }  // namespace m2m

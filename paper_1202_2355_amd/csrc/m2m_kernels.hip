@@ -789,12 +789,15 @@ size_t step_lds_bytes(bool f64, bool acc64, int J, int n_r, int n_R, int n_v, in
     return ((bins + tabs + scf + 15) / 16) * 16;
 }
 
-// Private bin copies: as many as fit in 48 KiB of LDS, at most 8.
-int private_copies(bool f64, int J) {
-    (void)f64;
-    const size_t per = (size_t)J * 8;
+// Private bin copies: as many as fit in `bytes` of LDS, at most 8. 48 KiB leave room
+// for a second block; 112 KiB pay where the deposits bound the step (spherical
+// harmonics: the adds of 64 lanes to one (l, m) of their mesh intervals collide). l = 4
+// with Gauss-Hermite (1620 observables), 2 copies / 8, us a step: 1e6 particles
+// 62.2 / 50.5, 6e5 43.9 / 38.5, 3e5 30.1 / 28.9, 1e5 20.9 / 22.1 (the copies are
+// cleared and added once per tile).
+int private_copies(int J, size_t bytes) {
     int k = 8;
-    while (k > 1 && per * (size_t)k > 48 * 1024) k >>= 1;
+    while (k > 1 && 8 * (size_t)J * (size_t)k > bytes) k >>= 1;
     return k;
 }
 
