@@ -308,7 +308,7 @@ struct WsLayout {
     size_t tail, otab;  // after what batched steps use: GH tables of an observation
     bool run;           // the run kernel's exchange areas, last:
     size_t run_sync, run_rows, run_res, run_cell, run_parts;
-    int seg_cap, row_len, nbj, ncj, npj, J, C, P;  // P: interval sums of the expansion
+    int seg_cap, seg_lean, row_len, nbj, ncj, npj, J, C, P;  // P: interval sums of the expansion
 };
 
 // entries of the node table of the self-consistent potential
@@ -316,15 +316,36 @@ size_t scf_table_len(const m2m_params& P) {
     return P.scf_nr > 0 ? (size_t)P.scf_nr * (size_t)((P.scf_lmax + 1) * (P.scf_lmax + 1)) * 2 : 0;
 }
 
-int seg_cap_of(int64_t n, int row_len) {
-    // at least ~1024 particles per tile, and partial rows of at most
-    // 16 bytes per particle (half the FP32 particle state)
+// Most tiles of a fit, without what fills the chip at the cost of larger
+// partial rows: at least 1024 particles per tile, and rows of at most 16 bytes
+// per particle (half the FP32 particle state).
+int seg_cap_lean(int64_t n, int row_len) {
     const int64_t by_n = (n + 1023) / 1024;
     const int64_t by_mem = (16 * n) / ((int64_t)row_len * 8);
     int64_t cap = std::min(by_n, std::max<int64_t>(by_mem, 1));
     cap = std::max<int64_t>(1, std::min<int64_t>(cap, 4096));
     cap = std::min<int64_t>(cap, std::max<int64_t>(1, n / kSegAlign));
     return (int)cap;
+}
+
+// Most tiles of a fit. The rows of a fit of many observables and prior cells are
+// long (54 KB for the 2610 + 2 x 2048 of the LOSVD layout), and 16 bytes per particle
+// let 1e5 particles have 29 of them, so 29 of 256 compute units. A fit may therefore
+// have up to 160 tiles of at least 1024 particles, and where a particle costs much
+// (FP64 state, spherical harmonics, self-consistent potential) 256 of at least 256, in
+// 16 MiB of rows.
+// Measured us a step, before and with tiles of at least 1024, 512, 256, 128:
+// LOSVD FP32 2e4 particles 18.2 14.8 14.6 14.5 15.4, 1e5 17.7 15.5 16.0 17.3 17.5;
+// FP64 2e4 44.3 25.3 21.4 19.8 20.0; l = 4 harmonics with Gauss-Hermite 2e4 35.7
+// 25.2 20.0 17.3 16.3, 1e5 36.4 25.7 21.1 20.9 20.7; expansion 2e4 26.4 21.1 18.8
+// 18.0 18.3. LOSVD FP32 with at most 96, 160, 256 tiles: 2e5 16.9 16.3 16.6, 4e5 18.7
+// 17.9 18.8 (119 tiles before: 18.8).
+int seg_cap_of(int64_t n, int row_len, bool dear) {
+    const int64_t per = dear ? 256 : 1024, most = dear ? 256 : 160;
+    const int64_t more = std::min<int64_t>({(n + per - 1) / per, most,
+                                            (int64_t(16) << 20) / ((int64_t)row_len * 8),
+                                            std::max<int64_t>(1, n / kSegAlign)});
+    return std::max(seg_cap_lean(n, row_len), (int)more);
 }
 
 // Most observables and particles of fits that step by the run kernel.
@@ -356,7 +377,9 @@ WsLayout plan(const m2m_obs_layout& L, const m2m_params& P, int64_t n, bool f64,
     w.nbj = (w.J + kFinCols - 1) / kFinCols;
     w.ncj = (w.C + kFinCols - 1) / kFinCols;
     w.npj = (w.P + kFinCols - 1) / kFinCols;
-    w.seg_cap = seg_cap_of(n, w.row_len);
+    w.seg_lean = seg_cap_lean(n, w.row_len);
+    w.seg_cap = cell_index ? seg_cap_of(n, w.row_len, f64 || L.dens == M2M_DENS_ALM || P.scf_nr > 0)
+                           : w.seg_lean;
     size_t o = 0;
     auto take = [&](size_t bytes) {
         const size_t at = o;
@@ -1656,8 +1679,12 @@ struct m2m_batch {
 namespace {
 
 size_t footprint(const m2m_ctx* c) {
-    // without what no batched step needs (a run's exchange areas)
-    return (size_t)c->n * 8 * (c->f64 ? 8 : 4) + c->w.tail;
+    // without what no batched step needs (a run's exchange areas), and without
+    // the rows beyond 16 bytes per particle (at most 16 MiB)
+    const auto rows = [&](int cap) {
+        return align_up(8 * (size_t)cap * (size_t)c->w.row_len, 256) + align_up(sizeof(Tile) * (size_t)cap, 256);
+    };
+    return (size_t)c->n * 8 * (c->f64 ? 8 : 4) + c->w.tail - (rows(c->w.seg_cap) - rows(c->w.seg_lean));
 }
 
 hipError_t grow(void** p, size_t* cap, size_t need) {
@@ -1780,10 +1807,22 @@ m2m_status fill_set(m2m_batch* b, LaunchSet& L, const std::vector<int>& members,
     // column jobs for every fit
     bool whole = members.size() >= kWholeFitMinFits;
     std::vector<int> cnts(members.size());
+    // tiles of a fit: lean rows, or where these leave compute units idle as many
+    // tiles as bring the set to five eighths of the units (a set shares them with
+    // another). Measured us a step of 3, 8, 12 LOSVD fits of 5e4 FP32 particles: lean
+    // rows 21.8 23.5 25.1, filled to 128 18.8 21.6 24.3, to 192 18.6 22.7 24.2; with
+    // every tile of seg_cap 19.5 23.1 27.6, and 12 of 1.5e5 55 instead of 36.
+    const auto tiles_of = [](const m2m_ctx* c, int64_t size, int cap) {
+        return std::max(1, (int)std::min<int64_t>((c->n + size - 1) / size, cap));
+    };
+    int lean = 0;
+    for (int m : members) lean += tiles_of(b->fits[m], tile, b->fits[m]->w.seg_lean);
+    const int fill = std::max(1, n_cus() * 5 / 8);
+    const int64_t wide = std::max(tile, (ntot + fill - 1) / fill);
     for (size_t f = 0; f < members.size(); ++f) {
         m2m_ctx* c = b->fits[members[f]];
-        int cnt = (int)std::min<int64_t>((c->n + tile - 1) / tile, c->w.seg_cap);
-        cnts[f] = std::max(1, cnt);
+        cnts[f] = tiles_of(c, tile, c->w.seg_lean);
+        if (lean < fill) cnts[f] = std::max(cnts[f], tiles_of(c, wide, c->w.seg_cap));
         if ((size_t)cnts[f] * (size_t)c->w.J * 8 > kWholeFitMaxBytes || c->w.nbj > kWholeFitMaxJobs)
             whole = false;
     }
