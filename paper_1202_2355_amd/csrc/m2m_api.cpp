@@ -348,8 +348,14 @@ int seg_cap_of(int64_t n, int row_len, bool dear) {
     return std::max(seg_cap_lean(n, row_len), (int)more);
 }
 
-// Most observables and particles of fits that step by the run kernel.
-constexpr int kRunMaxJ = 1024;
+// Most observables and particles of fits that step by the run kernel (above
+// kRunShortJ only for calls of more than two steps: a launch clears and ends the
+// exchange of more columns). 2610 observables, us a step, step and finalize
+// kernels / run kernel: FP32 2e4 particles 13.8 / 10.9, 1e5 14.8 / 10.2, 8e5 20.9 /
+// 17.7, 4e6 51.2 / 44.6, FP64 1e5 23.3 / 13.8, 8e5 43.3 / 29.1; a call of one, two, four
+// steps of 1e5 FP32 particles 27.8 / 32.0, 42.4 / 41.0, 74.9 / 59.3.
+constexpr int kRunMaxJ = 4096;
+constexpr int kRunShortJ = 1024;
 constexpr int64_t kRunMaxN = int64_t(1) << 22;
 
 // The run kernel is built for fits with radial bins in an analytic potential
@@ -793,8 +799,8 @@ bool capturing(hipStream_t s) {
 // captured. Beside a batch that keeps the GPU full (64 fits, streams on
 // hardware queues of their own) 64 steps of 4001 / 10^6 particles took 0.5 /
 // 1.3 ms this way and 4.0 / 6.2 ms by one launch per step.
-bool use_run(const m2m_ctx* c) {
-    return c->run && !capturing(c->stream);
+bool use_run(const m2m_ctx* c, int32_t n_steps) {
+    return c->run && (c->w.J <= kRunShortJ || n_steps > 2) && !capturing(c->stream);
 }
 
 // go() launches a run on stream st, ordered after the last run of another
@@ -1265,7 +1271,7 @@ m2m_status m2m_step(m2m_ctx* c, int32_t n_steps, int32_t correct) {
     if (n_steps < 0) return fail(c, M2M_EINVAL, "n_steps must be >= 0");
     if (n_steps == 0) return M2M_OK;
     c->may_assign = true;
-    if (use_run(c)) {
+    if (use_run(c, n_steps)) {
         for (int32_t done = 0; done < n_steps; done += kRunMaxSteps)
             if (m2m_status s = launch_run(c, std::min(n_steps - done, kRunMaxSteps), correct); s != M2M_OK)
                 return s;
@@ -1666,7 +1672,7 @@ struct m2m_batch {
     bool smooth = false;  // some fit smooths its prior grid
     bool graphs = false;  // steps replayed from captured graphs (else launched directly)
     // the fits step by the run kernel (run_fits): its tables and launch shape
-    bool run = false;
+    bool run = false, run_many = false;
     int run_block = 0, run_blocks = 0, dev = 0;
     size_t run_lds = 0;
     std::vector<int> run_nb;  // blocks per fit
@@ -1871,10 +1877,11 @@ constexpr int kRunMaxFits = 32;
 // run, or where that exceeds the compute units a share by particles, and
 // always a third of its reduction jobs. Measured us a step: 8 FP32
 // Gauss-Hermite fits of 4.7e5 particles together 20.5 -> 8.1, 10 of 2.6e6
-// 69 -> 30 (two groups of step and finalize kernels before).
+// 69 -> 30 (two groups of step and finalize kernels before); 3 LOSVD fits of 5e4
+// FP32 particles 18.9 -> 12.6, 4 of 4e5 32.8 -> 24.8.
 m2m_status run_fits(m2m_batch* b) {
     const int nf = (int)b->fits.size();
-    b->run = false;
+    b->run = b->run_many = false;
     if (nf < 1 || nf > kRunMaxFits || g_batch_graphs) return M2M_OK;
     int64_t ntot = 0;
     int want = 0, least = 0;
@@ -1883,6 +1890,7 @@ m2m_status run_fits(m2m_batch* b) {
         ntot += c->n;
         want += c->run_sh.blocks;
         least += (c->run_args.n_jobs + 2) / 3;
+        b->run_many |= c->w.J > kRunShortJ;
     }
     const int room = std::min(kRunMaxBlocks, n_cus());
     if (ntot > kRunMaxN || least + nf > room) return M2M_OK;
@@ -2123,7 +2131,7 @@ m2m_status m2m_batch_run(m2m_batch* b, int32_t steps_per_launch) {
         if (s != M2M_OK) return s;
     }
     if (b->fits.empty() || steps_per_launch == 0) return M2M_OK;
-    if (b->run && !capturing(b->stream)) {
+    if (b->run && (!b->run_many || steps_per_launch > 2) && !capturing(b->stream)) {
         hipError_t e = hipSuccess;
         for (int32_t done = 0; done < steps_per_launch && e == hipSuccess; done += kRunMaxSteps) {
             const int k = std::min(steps_per_launch - done, kRunMaxSteps);

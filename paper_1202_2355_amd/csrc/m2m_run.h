@@ -1,6 +1,5 @@
-// The run kernel: several whole steps of one fit in one launch, for fits of
-// few observables (the rule is run_shape in m2m_internal.h). A block keeps
-// its particles for the whole launch (in registers where every thread has at
+// The run kernel: several whole steps of one fit in one launch (its launch shape is
+// run_shape in m2m_internal.h). A block keeps its particles for the whole launch (in registers where every thread has at
 // most one, else in its L2) and the blocks exchange only the tile sums: the
 // force of change of step k + 1 needs the residuals of step k, and nothing
 // else crosses blocks.
@@ -523,14 +522,11 @@ __device__ __forceinline__ void run_fit(const FitDev& fd, const RunArgs& ra, int
     const G<T> __restrict__ U = gmem<T>(fd.u);
     const G<T> __restrict__ UH = gmem<T>(fd.uh);
     const G<uint16_t> __restrict__ CI = gmem(fd.cidx);
-    const int64_t kstep0 = st->kstep, tstep0 = st->tstep;
     bool assign = st->assign_pending != 0;
-    const int32_t error0 = st->error;
     const bool correct = OWN ? st->correct != 0 : call.correct != 0;
-    const int32_t left0 = OWN ? st->steps_left : n_steps;
     const bool priors = correct && fd.entropy == 0 && fd.prior_every > 0;
     // correction steps until the next refresh
-    int until = priors ? fd.prior_every - (int)(kstep0 % fd.prior_every) : 0;
+    int until = priors ? fd.prior_every - (int)(st->kstep % fd.prior_every) : 0;
 
     // the first particles are requested before the set-up
     int i0 = (wave * nb + b) * 64 + lane, istep = NW * nb * 64;
@@ -723,16 +719,33 @@ __device__ __forceinline__ void run_fit(const FitDev& fd, const RunArgs& ra, int
     if (tid == 0 && dead)
         (void)__hip_atomic_fetch_or(&ra.sync->dead, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     if (b != nb - 1) return;
+    // the counters as they were before the launch, read again here: held through
+    // the step loop they cost its scalar registers
+    FitState* own = fd.st;
+    asm volatile("" : "+s"(own));
+    const G<FitState> se = gmem(own);
+    const int64_t kstep0 = se->kstep, tstep0 = se->tstep;
+    const int32_t error0 = se->error, left0 = OWN ? se->steps_left : n_steps;
+    // up to 16 lanes a step, so that the steps take one pass: one lane per step
+    // read 164 parts (2610 observables) in turn, 31 us at the end of every launch
     bool bad = false;
-    for (int k = tid; k < n_steps; k += BLOCK) {
-        double c2 = 0.0;
-        const G<const Word> p = gmem<const Word>(ra.parts) + (size_t)k * ra.n_jobs * 2;
-        for (int q = 0; q < ra.n_jobs; ++q)
-            c2 += take<double>(wt, p + (size_t)q * 2, tag0 + 1u + (uint32_t)k);
+    const uint64_t* parts = ra.parts;
+    int jobs = ra.n_jobs;
+    asm volatile("" : "+s"(parts), "+s"(jobs));
+    int lanes = 16;
+    while (lanes > 1 && n_steps * lanes > BLOCK) lanes >>= 1;
+    const int te = thread_here(), k = te / lanes;
+    double c2 = 0.0;
+    if (k < n_steps)
+        c2 = take_rows<4>(wt, gmem<const Word>(parts) + (size_t)k * jobs * 2, 2, te & (lanes - 1), lanes,
+                          jobs, tag0 + 1u + (uint32_t)k);
+    for (int off = lanes / 2; off >= 1; off >>= 1) c2 += __shfl_xor(c2, off, 64);
+    if (k < n_steps && (te & (lanes - 1)) == 0) {
         gmem(fd.chi2_hist)[(tstep0 + k) % kHistCap] = c2;
         if (k == n_steps - 1) st->chi2 = c2;
-        bad |= !isfinite(c2);
+        bad = !isfinite(c2);
     }
+    static_assert(BLOCK >= kRunMaxSteps, "one thread per step");
     const int any_bad = __syncthreads_or(bad ? 1 : 0);
     if (tid == 0) {
         const uint32_t d = __hip_atomic_load(&ra.sync->dead, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
