@@ -131,7 +131,9 @@
  *   M2M_EINVAL, allocation failure M2M_ENOMEM, a failing HIP call
  *   M2M_EDEVICE, a call out of order M2M_ESTATE. Asynchronous calls report
  *   device-side problems (a non-finite chi^2) at the next synchronizing call
- *   (m2m_get_*, m2m_observe, m2m_batch_poll) as M2M_ENONFINITE.
+ *   (m2m_get_*, m2m_observe, m2m_batch_poll) as M2M_ENONFINITE. A launch of
+ *   steps that did not complete on the device is reported as M2M_EDEVICE
+ *   by every m2m_get_* call and by the poll that hands the fit back.
  *   m2m_last_error gives a message for the last failure on a context.
  *   A context is not thread-safe; distinct contexts are independent.
  */

@@ -743,8 +743,15 @@ m2m_status flush_assign(m2m_ctx* c) {
     return M2M_OK;
 }
 
+// A run of steps that did not complete: the weights and the history are not
+// those of the fit (error bits of the fit's state).
+m2m_status device_status(m2m_ctx* c, int32_t error) {
+    if (error & 2) return fail(c, M2M_EDEVICE, "a run of steps did not complete on the device");
+    return M2M_OK;
+}
+
 m2m_status error_status(m2m_ctx* c, const FitState& s) {
-    if (s.error & 2) return fail(c, M2M_EDEVICE, "a run of steps did not complete on the device");
+    if (m2m_status d = device_status(c, s.error); d != M2M_OK) return d;
     if (s.error & 1) return fail(c, M2M_ENONFINITE, "chi^2 became non-finite");
     return M2M_OK;
 }
@@ -1377,7 +1384,7 @@ m2m_status m2m_get_chi2_history(m2m_ctx* c, double* out, int32_t max, int32_t* n
         out[k] = ring[(size_t)(t % kHistCap)];
     }
     *n_out = (int32_t)take;
-    return M2M_OK;
+    return device_status(c, st.error);
 }
 
 m2m_status m2m_observe(m2m_ctx* c, const double* V_p, const double* sigma_p, double* y) {
@@ -1460,6 +1467,9 @@ m2m_status m2m_get_state(m2m_ctx* c, void* host_blob, size_t* bytes) {
     std::memcpy(p, &h, sizeof h);
     p += sizeof h;
     M2M_HIP(c, copy_sync(c->stream, p, c->st, sizeof(FitState), hipMemcpyDeviceToHost));
+    FitState st{};
+    std::memcpy(&st, p, sizeof st);
+    if ((s = device_status(c, st.error)) != M2M_OK) return s;  // nothing worth keeping
     p += sizeof(FitState);
     double* const dev[5] = {c->fd.ytil, c->fd.yv, c->fd.delta, c->fd.Y, c->fd.sigma};
     for (double* d : dev) {
@@ -2033,18 +2043,19 @@ hipError_t snapshot(m2m_batch* b) {
 m2m_status collect(m2m_batch* b, const std::vector<m2m_ctx*>& fits, const int32_t* flags,
                    m2m_ctx** done, int32_t max_done, int32_t* n_done) {
     std::vector<m2m_ctx*> gone;
-    bool bad = false;
+    bool bad = false, dev = false;
     for (size_t f = 0; f < fits.size() && *n_done < max_done; ++f) {
         m2m_ctx* c = fits[f];
         if (!c || c->batch != b || flags[2 * f] > 0) continue;
         done[(*n_done)++] = c;
         gone.push_back(c);
-        if (flags[2 * f + 1] & 1) {
+        if (device_status(c, flags[2 * f + 1]) != M2M_OK) {
+            dev = true;
+        } else if (flags[2 * f + 1] & 1) {
             c->err = "chi^2 became non-finite";
             bad = true;
         }
     }
-    bool dev = false;
     for (m2m_ctx* c : gone) {
         b->fits.erase(std::find(b->fits.begin(), b->fits.end(), c));
         if (retire(b, c) != hipSuccess) dev = true;
