@@ -8,6 +8,7 @@
 #include <type_traits>
 
 #include "m2m_device.h"
+#include "m2m_pow10.h"
 #include "m2m_smooth.h"
 
 namespace m2m {
@@ -294,23 +295,6 @@ __device__ __forceinline__ void cell_job(const FitDev& fd, const RunArgs& ra, co
 }
 
 // ------------------------------------------------------------- smoothing ----
-// 10^x for the search's lambdas, within 1e-14 for |x| < 30: 2^k e^r with
-// |r| <= ln(2) / 2, e^r by its Taylor polynomial of degree 14 (remainder 1e-19)
-// over 14!, the coefficients 14! / n! made on the way. The library's exp10 kept
-// its coefficients in registers through the whole step loop: 16 of 128 spilled,
-// and 24 steps of 600 000 FP32 particles with one refresh took 332 us, so 285.
-__device__ __forceinline__ double pow10_of(double x) {
-    const double k = rint(x * 3.32192809488736234787);
-    const double r = fma(x, 3.32192809488736234787, -k) * 0.693147180559945309417;
-    double e = 1.0, c = 1.0;
-#pragma unroll 1
-    for (int n = 14; n >= 1; --n) {
-        c *= n;
-        e = fma(e, r, c);
-    }
-    return ldexp(e / c, (int)k);
-}
-
 // The thin-plate smoothing of one prior grid (the method and its search are
 // described at the finalize kernel's smooth_priors), its n cells from `base`,
 // over the blocks of a run. One block reads the basis (four matrices of (n/4)^2,
