@@ -262,8 +262,10 @@ m2m_status m2m_set_targets(m2m_ctx* ctx, int32_t J, const double* Y, const doubl
  * Fits of at most 4096 observables (above 1024 in calls of more than two steps)
  * and 2^22 particles, with radial bins in an analytic potential, no refresh on
  * every single step and FP64 bins (M2M_DEPOSIT_F64), take up to 256 steps per
- * launch: one kernel whose blocks exchange their sums. Its blocks wait for each other, so runs on
- * different streams of one device are ordered one after another. If the stream
+ * launch: one kernel whose blocks exchange their sums. Its blocks wait for each
+ * other, so such launches on different streams of one device are ordered one
+ * after another where they need more than 256 blocks together (and after
+ * nothing else on those streams). If the stream
  * is being captured, the steps are launched one by one (two kernels each) as
  * for all other fits. A launch whose blocks do not all start within 50 ms (the
  * compute units are held by other work) is done by one block alone. */

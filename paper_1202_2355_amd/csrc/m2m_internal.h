@@ -243,20 +243,23 @@ inline RunShape run_shape(int64_t n, bool f64, int J) {
 }
 
 // steps (at most kRunMaxSteps) of one fit over `blocks` blocks, or (tiles) of the
-// fits of a table, each up to the steps it has left
+// fits of a table, each up to the steps it has left; done (or NULL): an event
+// that the launch itself completes
 hipError_t launch_run_f32(int block, int kin, const FitDev& fd, const RunArgs& ra, int blocks,
-                          size_t lds, const RunCall& call, hipStream_t s);
+                          size_t lds, const RunCall& call, hipStream_t s, hipEvent_t done);
 hipError_t launch_run_f64(int block, int kin, const FitDev& fd, const RunArgs& ra, int blocks,
-                          size_t lds, const RunCall& call, hipStream_t s);
+                          size_t lds, const RunCall& call, hipStream_t s, hipEvent_t done);
 // the same of a fit whose priors are smoothed
 hipError_t launch_run_smooth_f32(int block, int kin, const FitDev& fd, const RunArgs& ra, int blocks,
-                                 size_t lds, const RunCall& call, hipStream_t s);
+                                 size_t lds, const RunCall& call, hipStream_t s, hipEvent_t done);
 hipError_t launch_run_smooth_f64(int block, int kin, const FitDev& fd, const RunArgs& ra, int blocks,
-                                 size_t lds, const RunCall& call, hipStream_t s);
+                                 size_t lds, const RunCall& call, hipStream_t s, hipEvent_t done);
 hipError_t launch_runs_f32(int block, int kin, const FitDev* fits, const RunArgs* ras,
-                           const RunTile* tiles, int blocks, size_t lds, int n_steps, hipStream_t s);
+                           const RunTile* tiles, int blocks, size_t lds, int n_steps, hipStream_t s,
+                           hipEvent_t done);
 hipError_t launch_runs_f64(int block, int kin, const FitDev* fits, const RunArgs* ras,
-                           const RunTile* tiles, int blocks, size_t lds, int n_steps, hipStream_t s);
+                           const RunTile* tiles, int blocks, size_t lds, int n_steps, hipStream_t s,
+                           hipEvent_t done);
 
 // ---- launchers (m2m_kernels.hip) ------------------------------------------
 // kin: kinematic kind of every fit in the launch, from kin_class()

@@ -4,8 +4,8 @@
 namespace m2m {
 
 hipError_t launch_run_smooth_f64(int block, int kin, const FitDev& fd, const RunArgs& ra, int blocks,
-                                size_t lds, const RunCall& call, hipStream_t s) {
-    if (block == 512) return launch_run_t<double, 512, true>(kin, fd, ra, blocks, lds, call, s);
+                                size_t lds, const RunCall& call, hipStream_t s, hipEvent_t done) {
+    if (block == 512) return launch_run_t<double, 512, true>(kin, fd, ra, blocks, lds, call, s, done);
     return hipErrorInvalidValue;
 }
 

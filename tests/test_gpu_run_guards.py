@@ -1,5 +1,6 @@
 """The run kernel (several steps of a fit in one launch) around its edges: what
-is reported of a launch that did not complete."""
+is reported of a launch that did not complete, and what the runs of several
+streams wait for."""
 
 import sys
 
@@ -60,3 +61,64 @@ def test_a_run_that_did_not_complete_is_a_device_error(oracle, Fit, lagged):
     f._ws[ERROR_AT:ERROR_AT + 4].view(torch.int32).zero_()
     assert np.isfinite(f.chi2_history()).all() and f.get_state()
     f.close()
+
+
+def test_runs_wait_for_runs_only(oracle, Fit):
+    """Other work on a stream that has stepped a fit holds up no fit of another
+    stream: a step there ends while a kernel enqueued behind the first fit's
+    steps still runs. Both before and after, steps in turn give what each fit
+    gives alone."""
+    n = (40_009, 270_001)  # 40 and 256 blocks
+    alone = []
+    for k in n:
+        f = _made(oracle, Fit, "gh", "f32", k)
+        f.step(22)
+        alone.append(f.particles()["u"])
+        f.close()
+    fits = [_made(oracle, Fit, "gh", "f32", k, stream=torch.cuda.Stream()) for k in n]
+    _say("two streams", n)
+
+    def in_turn():
+        for _ in range(5):
+            for f in fits:
+                f.step(2)
+
+    in_turn()
+    fits[0].step(1)
+    busy = torch.cuda.Event()
+    with torch.cuda.stream(fits[0].stream):
+        torch.cuda._sleep(int(1e8))  # tens of ms at least
+        busy.record()
+    fits[1].step(1)
+    fits[1].stream.synchronize()
+    assert not busy.query()
+    fits[1].step(1)
+    fits[0].step(1)
+    in_turn()
+    for f, u in zip(fits, alone):
+        np.testing.assert_allclose(f.particles()["u"], u, rtol=1e-5)
+        f.close()
+
+
+def test_many_streams_share_the_slots(oracle, Fit):
+    """Fits of 16 to 256 blocks on streams of their own, calls of one to nine
+    steps in a changing order."""
+    n = (1001, 4003, 20_011, 33_001, 90_001, 262_147, 16_001, 50_021)
+    rng = np.random.default_rng(3)
+    alone, fits = [], []
+    for k in n:
+        f = _made(oracle, Fit, "gh", "f32", k)
+        f.step(60)
+        alone.append(f.particles()["u"])
+        f.close()
+        fits.append(_made(oracle, Fit, "gh", "f32", k, stream=torch.cuda.Stream()))
+    _say("many streams", n)
+    left = [60] * len(n)
+    while any(left):
+        k = int(rng.choice([j for j in range(len(n)) if left[j]]))
+        m = min(left[k], int(rng.integers(1, 10)))
+        fits[k].step(m)
+        left[k] -= m
+    for f, u in zip(fits, alone):
+        np.testing.assert_allclose(f.particles()["u"], u, rtol=1e-5)
+        f.close()
