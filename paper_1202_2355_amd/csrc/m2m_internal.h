@@ -72,7 +72,7 @@ struct FitState {
     int32_t steps_left;      // steps still to run; kernels skip the fit at 0
     int32_t correct;         // force of change on (1) or relaxation (0)
     int32_t assign_pending;  // fresh cell priors wait to be assigned
-    int32_t error;           // bit 0: non-finite chi^2 seen
+    int32_t error;           // bit 0: non-finite chi^2 seen, bit 1: a run did not complete
     uint32_t ticket;         // finalize: blocks done this launch
     uint32_t mticket;        // the same in observe mode
     double chi2;             // chi^2 after the last step
@@ -178,7 +178,7 @@ constexpr int kRunMaxSteps = 256;   // steps per launch
 constexpr int kRunMaxBlocks = 256;  // one block per compute unit
 constexpr size_t kRunStaticLds = 2 * 16 * kRunCols * 8 + 256;  // its static LDS (16 waves), rounded up
 constexpr uint64_t kRunStart = 5000000;   // 50 ms (100 MHz counter): see all_running
-constexpr uint64_t kRunWait = 1000000000; // 10 s: a wait within a run that failed
+constexpr uint32_t kRunWait = 1000000000; // 10 s: a wait within a run that failed
 
 // counters of the launches of a context
 struct RunSync {
@@ -186,7 +186,7 @@ struct RunSync {
     uint32_t start0;  // the same before this launch
     uint32_t tag0;    // tag of the last step done so
     uint32_t left;    // blocks that have left a launch that was called off
-    uint32_t dead;    // a wait ended without its value
+    uint32_t wait;    // longest wait within a run, 100 MHz ticks (0: kRunWait)
 };
 
 // Exchange areas in the fit's workspace: 64-bit words of 32 data and 32 tag

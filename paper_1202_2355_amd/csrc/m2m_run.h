@@ -80,16 +80,20 @@ struct Words<double> {
 };
 
 // A wait that has ended without its value (kRunWait, which only a block that
-// stopped for good can exceed): later waits are skipped, so that the launch
-// ends, and the fit reports the failure (error bit 1).
+// stopped for good can exceed): the block's later waits are skipped, so that the
+// launch ends, and the fit reports the failure (error bit 1).
 struct Waiter {
-    int* dead;  // LDS
-    __device__ bool expired(uint64_t t0) const {
-        if (wall_clock64() - t0 < kRunWait) return false;
-        *dead = 1;
+    uint32_t* dead;  // LDS: set by such a wait; and the longest wait
+    __device__ bool expired(uint64_t t0, uint32_t most) const {
+        if (wall_clock64() - t0 < most) return false;
+        dead[0] = 1;
         return true;
     }
 };
+
+__device__ __forceinline__ void add_error(G<FitState> st, int32_t bits) {
+    (void)__hip_atomic_fetch_or((int32_t*)&st->error, bits, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
 
 // the value at p once it carries the tag
 template <typename V>
@@ -97,8 +101,9 @@ __device__ __forceinline__ V take(const Waiter& w, G<const Word> p, uint32_t tag
     V v;
     if (Words<V>::get(p, tag, v) || *w.dead) return v;
     const uint64_t t0 = wall_clock64();
+    const uint32_t most = w.dead[1];
     while (!Words<V>::get(p, tag, v))
-        if (w.expired(t0)) break;
+        if (w.expired(t0, most)) break;
     return v;
 }
 
@@ -465,6 +470,23 @@ __device__ __forceinline__ void run_smooth(const FitDev& fd, const RunArgs& ra, 
 }
 
 // ------------------------------------------------------------------- run ----
+// memory that nothing writes during a launch (scalar loads)
+template <typename V>
+using Const = const __attribute__((address_space(4))) V*;
+
+template <typename F, typename R>
+struct LateArgs {
+    F fd;
+    R ra;
+};
+
+// the arguments of k_run
+struct RunParams {
+    FitDev fd;
+    RunArgs ra;
+    RunCall call;
+};
+
 // Steps of one fit over n_blocks blocks, by block b. Block b takes the
 // particles in groups of 64 (one wave each): group (m n_blocks + b) for m = wave,
 // wave + NW, ..., so that every compute unit gets the same number of waves to
@@ -474,13 +496,18 @@ __device__ __forceinline__ void run_smooth(const FitDev& fd, const RunArgs& ra, 
 // batch, with its own steps left and setting (both at compile time: as branches
 // at the start of the kernel they cost a launch of one step 0.6-0.9 of 12.4 us).
 // SMOOTH: the priors are smoothed at every refresh.
-template <typename T, int BLOCK, int KIN, bool KNOWN, bool OWN, bool SMOOTH>
+// late(): where fd and ra are in memory, as addresses that the compiler knows nothing
+// of: what the end of the launch needs is read again there, as everything held
+// through the step loop costs its scalar registers (they spill to lanes, and
+// reading ten of them back per particle took 100 steps of 10^6 from 1154 to 1179 us).
+template <typename T, int BLOCK, int KIN, bool KNOWN, bool OWN, bool SMOOTH, typename Late>
 __device__ __forceinline__ void run_fit(const FitDev& fd, const RunArgs& ra, int b,
-                                        const uint32_t n_blocks, const RunCall& call) {
+                                        const uint32_t n_blocks, const RunCall& call, Late late) {
     extern __shared__ __align__(16) unsigned char lds_raw[];
     constexpr int NW = BLOCK / 64;
     __shared__ double part[NW][kRunCols], part2[NW][kRunCols];
-    __shared__ int flag, dead;
+    __shared__ int flag;
+    __shared__ uint32_t dead[2];
     using A = double;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int n = (int)fd.n;
@@ -496,7 +523,9 @@ __device__ __forceinline__ void run_fit(const FitDev& fd, const RunArgs& ra, int
     const uint32_t tag0 = KNOWN ? call.tag0 : sync->tag0;
     if (tid == 0) {
         (void)__hip_atomic_fetch_add(&ra.sync->start, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        dead = 0;
+        const uint32_t most = sync->wait;
+        dead[0] = 0;
+        dead[1] = most ? most : kRunWait;
     }
 
     const G<T> __restrict__ X = gmem<T>(fd.x);
@@ -574,7 +603,7 @@ __device__ __forceinline__ void run_fit(const FitDev& fd, const RunArgs& ra, int
         istep = BLOCK;
         if (i0 < n) load(i0);
     }
-    const Waiter wt{&dead};
+    const Waiter wt{dead};
     // at most one particle per thread: they stay in registers
     const bool resident = n <= istep;
     Kept<T, KIN> kept;
@@ -700,60 +729,58 @@ __device__ __forceinline__ void run_fit(const FitDev& fd, const RunArgs& ra, int
         assign = refresh;
     }
 
+    // every block reports its own waits: the last one may be done before
+    const auto la = late();
+    const G<FitState> se = gmem(la.fd->st);
+    if (tid == 0 && dead[0]) add_error(se, 2);
     // the last block (it has the fewest particles) ends the run: chi^2 of every
     // step from its jobs' parts in order, then the counters
-    if (tid == 0 && dead)
-        (void)__hip_atomic_fetch_or(&ra.sync->dead, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     if (b != nb - 1) return;
-    // the counters as they were before the launch, read again here: held through
-    // the step loop they cost its scalar registers
-    FitState* own = fd.st;
-    asm volatile("" : "+s"(own));
-    const G<FitState> se = gmem(own);
     const int64_t kstep0 = se->kstep, tstep0 = se->tstep;
-    const int32_t error0 = se->error, left0 = OWN ? se->steps_left : n_steps;
+    const int32_t left0 = OWN ? se->steps_left : n_steps;
     // up to 16 lanes a step, so that the steps take one pass: one lane per step
     // read 164 parts (2610 observables) in turn, 31 us at the end of every launch
     bool bad = false;
-    const uint64_t* parts = ra.parts;
-    int jobs = ra.n_jobs;
-    asm volatile("" : "+s"(parts), "+s"(jobs));
+    const int jobs = la.ra->n_jobs;
     int lanes = 16;
     while (lanes > 1 && n_steps * lanes > BLOCK) lanes >>= 1;
     const int te = thread_here(), k = te / lanes;
     double c2 = 0.0;
     if (k < n_steps)
-        c2 = take_rows<4>(wt, gmem<const Word>(parts) + (size_t)k * jobs * 2, 2, te & (lanes - 1), lanes,
+        c2 = take_rows<4>(wt, gmem<const Word>(la.ra->parts) + (size_t)k * jobs * 2, 2, te & (lanes - 1), lanes,
                           jobs, tag0 + 1u + (uint32_t)k);
     for (int off = lanes / 2; off >= 1; off >>= 1) c2 += __shfl_xor(c2, off, 64);
     if (k < n_steps && (te & (lanes - 1)) == 0) {
-        gmem(fd.chi2_hist)[(tstep0 + k) % kHistCap] = c2;
-        if (k == n_steps - 1) st->chi2 = c2;
+        gmem(la.fd->chi2_hist)[(tstep0 + k) % kHistCap] = c2;
+        if (k == n_steps - 1) se->chi2 = c2;
         bad = !isfinite(c2);
     }
     static_assert(BLOCK >= kRunMaxSteps, "one thread per step");
     const int any_bad = __syncthreads_or(bad ? 1 : 0);
     if (tid == 0) {
-        const uint32_t d = __hip_atomic_load(&ra.sync->dead, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        if (any_bad || dead || d) st->error = error0 | (any_bad ? 1 : 0) | ((dead || d) ? 2 : 0);
-        st->tstep = tstep0 + n_steps;
-        if (correct) st->kstep = kstep0 + n_steps;
-        st->steps_left = left0 - n_steps;
-        st->correct = correct ? 1 : 0;
-        st->assign_pending = assign ? 1 : 0;
-        sync->tag0 = tag0 + (uint32_t)n_steps;
-        sync->start0 = start0 + n_blocks;
+        if (any_bad || dead[0]) add_error(se, (any_bad ? 1 : 0) | (dead[0] ? 2 : 0));
+        se->tstep = tstep0 + n_steps;
+        if (correct) se->kstep = kstep0 + n_steps;
+        se->steps_left = left0 - n_steps;
+        se->correct = correct ? 1 : 0;
+        se->assign_pending = assign ? 1 : 0;
+        const G<RunSync> sy = gmem(la.ra->sync);
+        sy->tag0 = tag0 + (uint32_t)n_steps;
+        sy->start0 = start0 + n_blocks;
         if (alone) {
-            sync->start = start0 + n_blocks;
-            sync->left = 0u;
+            sy->start = start0 + n_blocks;
+            sy->left = 0u;
         }
     }
 }
 
 template <typename T, int BLOCK, int KIN, bool KNOWN, bool SMOOTH>
-__global__ __launch_bounds__(BLOCK) void k_run(const FitDev fd, const RunArgs ra,
-                                               const RunCall call) {
-    run_fit<T, BLOCK, KIN, KNOWN, false, SMOOTH>(fd, ra, (int)blockIdx.x, gridDim.x, call);
+__global__ __launch_bounds__(BLOCK) void k_run(const RunParams P) {
+    run_fit<T, BLOCK, KIN, KNOWN, false, SMOOTH>(P.fd, P.ra, (int)blockIdx.x, gridDim.x, P.call, [] {
+        auto p = (Const<RunParams>)__builtin_amdgcn_kernarg_segment_ptr();
+        asm volatile("" : "+s"(p));
+        return LateArgs<Const<FitDev>, Const<RunArgs>>{&p->fd, &p->ra};
+    });
 }
 
 // the fits of a table, each over its own blocks (no fit waits for another)
@@ -762,7 +789,13 @@ __global__ __launch_bounds__(BLOCK) void k_runs(const FitDev* __restrict__ fits,
                                                 const RunArgs* __restrict__ ras,
                                                 const RunTile* __restrict__ tiles, int32_t n_steps) {
     const RunTile t = tiles[blockIdx.x];
-    run_fit<T, BLOCK, KIN, false, true, false>(fits[t.fit], ras[t.fit], t.b, (uint32_t)t.nb, RunCall{n_steps, 1, 0, 0u, 0u});
+    run_fit<T, BLOCK, KIN, false, true, false>(
+        fits[t.fit], ras[t.fit], t.b, (uint32_t)t.nb, RunCall{n_steps, 1, 0, 0u, 0u}, [=] {
+            // the index, not the tables' addresses: these stay known as read only
+            int f = t.fit;
+            asm volatile("" : "+s"(f));
+            return LateArgs<const FitDev*, const RunArgs*>{fits + f, ras + f};
+        });
 }
 
 // f(the kind of kinematic observables as a compile-time constant)
@@ -799,10 +832,10 @@ hipError_t launch_run_t(int kin, const FitDev& fd, const RunArgs& ra, int blocks
         constexpr int kind = decltype(K)::value;
         if constexpr (!SMOOTH)
             if (call.known) {
-                launch_blocks(k_run<T, BLOCK, kind, true, false>, blocks, BLOCK, lds, s, done, fd, ra, call);
+                launch_blocks(k_run<T, BLOCK, kind, true, false>, blocks, BLOCK, lds, s, done, RunParams{fd, ra, call});
                 return;
             }
-        launch_blocks(k_run<T, BLOCK, kind, false, SMOOTH>, blocks, BLOCK, lds, s, done, fd, ra, call);
+        launch_blocks(k_run<T, BLOCK, kind, false, SMOOTH>, blocks, BLOCK, lds, s, done, RunParams{fd, ra, call});
     });
 }
 

@@ -16,6 +16,8 @@ torch = pytest.importorskip("torch")
 
 # byte offset of the error bits in the workspace (FitState comes first)
 ERROR_AT = 28
+# of the longest wait within a run, in the counters of its launches
+WAIT_IN_SYNC = 16
 
 
 @pytest.fixture(scope="module")
@@ -32,6 +34,46 @@ def _made(oracle, Fit, kin, dtype, n, every=4, **kw):
     wl = _workload(kin, every)
     parts = cast(wl.initial_particles(n=n, seed=n % 97), dtype)
     return _fit(Fit, wl, parts, _targets(oracle, wl, parts, n), dtype, **kw)
+
+
+def _sync(f, at):
+    """The counters of a fit's launches: they come last in the workspace, and a fit
+    with a refresh on every step has the same workspace up to there."""
+    from paper_1202_2355_amd import _abi as A
+    base = A.m2m_workspace_bytes(f.layout, dict(f.params, prior_every=1), f.n, f.dtype)
+    return f._ws[base + at:base + at + 4].view(torch.int32)
+
+
+@pytest.mark.parametrize("kin,dtype,n", [("gh", "f32", 40_009), ("losvd", "f64", 20_011)])
+def test_a_wait_without_its_value_fails_one_launch_only(oracle, Fit, kin, dtype, n):
+    """The longest wait of a fit's launches set to 10 ns from the host: the next
+    launch ends and is reported; a saved state taken up again steps as before."""
+    from paper_1202_2355_amd import _abi as A
+    _say("short wait", kin, dtype, n)
+    a, b = (_made(oracle, Fit, kin, dtype, n) for _ in range(2))
+    for f in (a, b):
+        f.step(5)
+    good, parts = b.get_state(), {k: v.clone() for k, v in b.t.items()}
+    wait = _sync(b, WAIT_IN_SYNC)
+    assert int(wait[0]) == 0
+    wait.fill_(1)
+    b.step(6)
+    with pytest.raises(A.M2MError) as e:
+        b.observables()
+    assert e.value.status == A.M2M_EDEVICE
+    wait.zero_()
+    b.set_state(good)
+    for k, v in parts.items():
+        b.t[k].copy_(v)
+    for f in (a, b):
+        f.step(6)
+    tol = 1e-5 if dtype == "f32" else 1e-10
+    np.testing.assert_allclose(b.chi2_history(), a.chi2_history(), rtol=10 * tol)
+    pa, pb = a.particles(), b.particles()
+    for c in pa:
+        np.testing.assert_allclose(pb[c], pa[c], rtol=tol, atol=1e-12)
+    a.close()
+    b.close()
 
 
 @pytest.mark.parametrize("lagged", [False, True])
