@@ -268,7 +268,7 @@ m2m_status m2m_set_targets(m2m_ctx* ctx, int32_t J, const double* Y, const doubl
  * nothing else on those streams). If the stream
  * is being captured, the steps are launched one by one (two kernels each) as
  * for all other fits. A launch whose blocks do not all start within 50 ms (the
- * compute units are held by other work) is done by one block alone. */
+ * compute units are held by other work) is done by the blocks that did. */
 m2m_status m2m_step(m2m_ctx* ctx, int32_t n_steps, int32_t correct);
 
 /* Recompute the cell priors from the current state now (Sec. 2.3.1) and

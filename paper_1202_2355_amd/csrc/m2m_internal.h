@@ -177,16 +177,21 @@ constexpr int kRunCols = 16;        // columns per reduction job
 constexpr int kRunMaxSteps = 256;   // steps per launch
 constexpr int kRunMaxBlocks = 256;  // one block per compute unit
 constexpr size_t kRunStaticLds = 2 * 16 * kRunCols * 8 + 256;  // its static LDS (16 waves), rounded up
-constexpr uint64_t kRunStart = 5000000;   // 50 ms (100 MHz counter): see all_running
-constexpr uint32_t kRunWait = 1000000000; // 10 s: a wait within a run that failed
+constexpr uint32_t kRunWait = 1000000000; // 10 s (100 MHz counter): a wait within a run that failed
+// How long a launch waits for blocks that have not started: 50 ms, and 0.1 ms times
+// the blocks wanted for each that runs after a launch that was called off.
+constexpr uint32_t kRunStart = 5000000, kRunAgain = 10000;
 
 // counters of the launches of a context
 struct RunSync {
-    uint32_t start;   // blocks that have started, over all launches (kRunOff: this one is called off)
-    uint32_t start0;  // the same before this launch
-    uint32_t tag0;    // tag of the last step done so
-    uint32_t left;    // blocks that have left a launch that was called off
-    uint32_t wait;    // longest wait within a run, 100 MHz ticks (0: kRunWait)
+    // low half: blocks that have started, over all launches, and kRunOff once this
+    // launch is called off; high half: the blocks that had started by then
+    uint64_t start;
+    uint32_t start0;    // the low half before this launch
+    uint32_t left;      // blocks that have left a launch that was called off
+    uint32_t tag0;      // tag of the last step done so
+    uint32_t wait;      // longest wait within a run, 100 MHz ticks (0: kRunWait)
+    uint32_t patience;  // 1 + kRunAgain after a launch that was called off, 0 after another
 };
 
 // Exchange areas in the fit's workspace: 64-bit words of 32 data and 32 tag

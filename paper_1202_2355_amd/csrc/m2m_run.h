@@ -132,23 +132,46 @@ __device__ __forceinline__ double take_rows(const Waiter& w, G<const Word> base,
 
 // The start of a launch: every block counts itself in, and the waits of the
 // steps begin only once all have, i.e. are all running. A launch whose blocks
-// are not all running within kRunStart (another kernel holds the compute
-// units, or the stream owns too few of them) is called off by one of them:
-// all leave without having changed anything, and the last to leave does the
-// whole run alone. So every wait of the steps ends, whatever else the GPU runs.
+// are not all running within its patience (another kernel holds the compute
+// units, or the stream owns too few of them) is called off by one of them: the
+// blocks that have started by then do the run among themselves, and those that
+// start later leave. So every wait of the steps ends, whatever else the GPU runs,
+// and a run slows down as the compute units it gets. Blocks may start when the run
+// is long done, so the counters that they read are changed by the last block to
+// leave. (Had no block started, the last one to leave would do the run alone.)
 constexpr uint32_t kRunOff = 0x80000000u;
 
-__device__ __forceinline__ bool all_running(RunSync* s, uint32_t target) {
+// the word that counts the blocks, once all `n` have started or the launch is
+// called off; v: a value of it from after this block's own count
+__device__ __forceinline__ uint64_t all_running(RunSync* s, uint32_t start0, uint32_t n, uint32_t patience) {
     const uint64_t t0 = wall_clock64();
     for (;;) {
-        uint32_t v = __hip_atomic_load(&s->start, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        if (v & kRunOff) return false;
-        if (v == target) return true;
-        if (wall_clock64() - t0 > kRunStart &&
-            __hip_atomic_compare_exchange_strong(&s->start, &v, v | kRunOff, __ATOMIC_RELAXED,
-                                                 __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
-            return false;
+        uint64_t v = __hip_atomic_load(&s->start, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        const uint32_t low = (uint32_t)v, here = low - start0;
+        if ((low & kRunOff) || here == n) return v;
+        const uint64_t t = wall_clock64() - t0;
+        if (patience ? t * here >= (uint64_t)(patience - 1) * n : t > kRunStart) {
+            const uint64_t off = v | kRunOff | ((uint64_t)here << 32);
+            if (__hip_atomic_compare_exchange_strong(&s->start, &v, off, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                                     __HIP_MEMORY_SCOPE_AGENT))
+                return off;
+        }
     }
+}
+
+// one more block has left a launch that was called off: true for the last
+__device__ __forceinline__ bool leave_run(G<RunSync> s, uint32_t n) {
+    return __hip_atomic_fetch_add((uint32_t*)&s->left, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == n - 1;
+}
+
+// the counters after a launch of n_steps steps whose blocks have all left
+__device__ __forceinline__ void ready_again(G<RunSync> s, G<FitState> st, uint32_t start0, uint32_t n,
+                                            int32_t left0, int32_t n_steps) {
+    s->start = (uint64_t)(start0 + n);
+    s->start0 = start0 + n;
+    s->left = 0u;
+    s->patience = 1u + kRunAgain;
+    st->steps_left = left0 - n_steps;
 }
 
 // ------------------------------------------------------------ kept kernels ----
@@ -191,21 +214,21 @@ struct Kept {
 // what the finalize kernel does for them (smoothing, Delta, force table,
 // chi^2 part); one wave's 16 lanes per row group, the row groups added over
 // the wave and then over the waves, in a fixed order.
-template <typename T, int BLOCK>
-__device__ __forceinline__ void obs_job(const FitDev& fd, const RunArgs& ra, const Waiter& w, int q,
+template <typename T, int BLOCK, typename F, typename R>
+__device__ __forceinline__ void obs_job(F fd, R ra, const Waiter& w, int q,
                                         int n_rows, int ncol, uint32_t tag, int k, bool last,
                                         double (*part)[kRunCols]) {
     constexpr int RG = BLOCK / kRunCols, NW = BLOCK / 64;
     const int t = thread_here(), lane = t & 63, wave = t >> 6;
     const int col = q * kRunCols + (t & (kRunCols - 1));
-    const bool in = col < fd.J;
+    const bool in = col < fd->J;
     double yt0 = 0.0, sg = 1.0, Yj = 0.0;
     if (t < kRunCols && in) {
-        yt0 = gmem(fd.ytil)[col];
-        sg = gmem(fd.sigma)[col];
-        Yj = gmem(fd.Y)[col];
+        yt0 = gmem(fd->ytil)[col];
+        sg = gmem(fd->sigma)[col];
+        Yj = gmem(fd->Y)[col];
     }
-    const G<const Word> rows = gmem<const Word>(ra.rows);
+    const G<const Word> rows = gmem<const Word>(ra->rows);
     double s = in ? take_rows<4>(w, rows + (size_t)col * 2, (size_t)ncol * 2, t / kRunCols, RG, n_rows, tag)
                   : 0.0;
     s += __shfl_xor(s, 16, 64);
@@ -217,21 +240,21 @@ __device__ __forceinline__ void obs_job(const FitDev& fd, const RunArgs& ra, con
         if (lane < kRunCols && in) {
             double tot = 0.0;
             for (int v = 0; v < NW; ++v) tot += part[v][lane];
-            const double yt = yt0 + fd.q * (tot - yt0);
+            const double yt = yt0 + fd->q * (tot - yt0);
             const double d = (yt - Yj) / sg;
-            const T r = (T)(fd.foc_chi * d / sg);
-            Words<T>::put(gmem<Word>(ra.res) + (size_t)col * Words<T>::n, r, tag);
-            gmem(fd.ytil)[col] = yt;
+            const T r = (T)(fd->foc_chi * d / sg);
+            Words<T>::put(gmem<Word>(ra->res) + (size_t)col * Words<T>::n, r, tag);
+            gmem(fd->ytil)[col] = yt;
             if (last) {
-                gmem(fd.yv)[col] = tot;
-                gmem(fd.delta)[col] = d;
-                gmem<T>(fd.rp)[col] = r;
+                gmem(fd->yv)[col] = tot;
+                gmem(fd->delta)[col] = d;
+                gmem<T>(fd->rp)[col] = r;
             }
             d2 = d * d;
         }
         for (int off = kRunCols / 2; off >= 1; off >>= 1) d2 += __shfl_xor(d2, off, 64);
         if (lane == 0)
-            Words<double>::put(gmem<Word>(ra.parts) + ((size_t)k * ra.n_jobs + q) * 2, d2, tag);
+            Words<double>::put(gmem<Word>(ra->parts) + ((size_t)k * ra->n_jobs + q) * 2, d2, tag);
     }
     __syncthreads();
 }
@@ -242,8 +265,9 @@ __device__ __forceinline__ void obs_job(const FitDev& fd, const RunArgs& ra, con
 struct SmWords {
     G<Word> data, what, prior, mean, score;
 };
-__device__ __forceinline__ SmWords sm_words(const RunArgs& ra, int C, int half) {
-    const G<Word> p = gmem<Word>(ra.parts) + (size_t)ra.n_jobs * kRunMaxSteps * 2;
+template <typename R>
+__device__ __forceinline__ SmWords sm_words(R ra, int C, int half) {
+    const G<Word> p = gmem<Word>(ra->parts) + (size_t)ra->n_jobs * kRunMaxSteps * 2;
     const G<Word> h = p + (size_t)C * 6 + (size_t)half * (2 + 3 * kSmoothMaxPoints * 2);
     return SmWords{p, p + (size_t)C * 2, p + (size_t)C * 4, h, h + 2};
 }
@@ -252,19 +276,19 @@ __device__ __forceinline__ SmWords sm_words(const RunArgs& ra, int C, int half) 
 // and counts over all rows, and the means that become the priors or (SMOOTH)
 // the data of their smoothing. ptag: the launch's last refresh before this one
 // (0: none), whose smoothed priors another block may have written.
-template <typename T, int BLOCK, bool SMOOTH>
-__device__ __forceinline__ void cell_job(const FitDev& fd, const RunArgs& ra, const Waiter& w, int q,
+template <typename T, int BLOCK, bool SMOOTH, typename F, typename R>
+__device__ __forceinline__ void cell_job(F fd, R ra, const Waiter& w, int q,
                                          int n_rows, int ncol, uint32_t tag, uint32_t ptag,
                                          double (*part)[kRunCols], double (*part2)[kRunCols]) {
     constexpr int RG = BLOCK / kRunCols, NW = BLOCK / 64;
     const int t = thread_here(), lane = t & 63, wave = t >> 6;
     const int c = q * kRunCols + (t & (kRunCols - 1));
-    const bool in = c < fd.C;
-    const G<const Word> rows = gmem<const Word>(ra.rows);
+    const bool in = c < fd->C;
+    const G<const Word> rows = gmem<const Word>(ra->rows);
     double s = 0.0, m = 0.0;
     if (in) {
-        s = take_rows<2>(w, rows + (size_t)(fd.J + c) * 2, (size_t)ncol * 2, t / kRunCols, RG, n_rows, tag);
-        m = take_rows<2>(w, rows + (size_t)(fd.J + fd.C + c) * 2, (size_t)ncol * 2, t / kRunCols, RG,
+        s = take_rows<2>(w, rows + (size_t)(fd->J + c) * 2, (size_t)ncol * 2, t / kRunCols, RG, n_rows, tag);
+        m = take_rows<2>(w, rows + (size_t)(fd->J + fd->C + c) * 2, (size_t)ncol * 2, t / kRunCols, RG,
                          n_rows, tag);
     }
     for (int off = 16; off <= 32; off <<= 1) {
@@ -284,18 +308,18 @@ __device__ __forceinline__ void cell_job(const FitDev& fd, const RunArgs& ra, co
         }
         // the cell's mean weight, or the previous prior if it is empty
         if constexpr (SMOOTH) {
-            const SmWords sw = sm_words(ra, fd.C, 0);
+            const SmWords sw = sm_words(ra, fd->C, 0);
             const double d = cnt > 0.0 ? tot / cnt
                              : ptag   ? take<double>(w, sw.prior + (size_t)c * 2, ptag)
-                                      : gmem(fd.gprior)[c];
-            gmem(fd.cdata)[c] = d;
+                                      : gmem(fd->gprior)[c];
+            gmem(fd->cdata)[c] = d;
             Words<double>::put(sw.data + (size_t)c * 2, d, tag);
         } else {
-            const double d = cnt > 0.0 ? tot / cnt : gmem(fd.gprior)[c];
-            gmem(fd.cdata)[c] = d;
-            gmem(fd.gprior)[c] = d;
-            gmem<T>(fd.ucell)[c] = (T)d;
-            Words<T>::put(gmem<Word>(ra.cell) + (size_t)c * Words<T>::n, (T)d, tag);
+            const double d = cnt > 0.0 ? tot / cnt : gmem(fd->gprior)[c];
+            gmem(fd->cdata)[c] = d;
+            gmem(fd->gprior)[c] = d;
+            gmem<T>(fd->ucell)[c] = (T)d;
+            Words<T>::put(gmem<Word>(ra->cell) + (size_t)c * Words<T>::n, (T)d, tag);
         }
     }
     __syncthreads();
@@ -317,20 +341,20 @@ __device__ __forceinline__ void cell_job(const FitDev& fd, const RunArgs& ra, co
 // steps 959 us by the step and finalize kernels, 408 so). The areas are free again at the next refresh,
 // at least two steps later: no block is past the step between them before
 // all have left this one.
-template <typename T, int BLOCK>
-__device__ __forceinline__ void run_smooth(const FitDev& fd, const RunArgs& ra, const Waiter& w, int half,
+template <typename T, int BLOCK, typename F, typename R>
+__device__ __forceinline__ void run_smooth(F fd, R ra, const Waiter& w, int half,
                                            int b, int nb, uint32_t tag, unsigned char* lds,
                                            double (*part)[kRunCols], int* pick) {
     constexpr int RG = BLOCK / kRunCols, NW = BLOCK / 64, QPB = NW / 4;
     const int t = thread_here(), lane = t & 63, wave = t >> 6;
     // as values that the compiler knows nothing of, so that nothing is derived
     // from them before the step loop and held through it
-    int nE = fd.n_E, nx = fd.n_x, base = half * fd.cell_half;
+    int nE = fd->n_E, nx = fd->n_x, base = half * fd->cell_half;
     asm volatile("" : "+s"(nE), "+s"(nx), "+s"(base));
     const int n = nE * nx;
-    const G<const double> basis = gmem<const double>(fd.sm_basis);
+    const G<const double> basis = gmem<const double>(fd->sm_basis);
     const SmBlocks B = sm_blocks(nE, nx);
-    const SmWords sw = sm_words(ra, fd.C, half);
+    const SmWords sw = sm_words(ra, fd->C, half);
     const G<Word> data = sw.data + (size_t)base * 2, what = sw.what + (size_t)base * 2;
     double* sa = reinterpret_cast<double*>(lds);
     double* sb = sa + n;
@@ -381,7 +405,7 @@ __device__ __forceinline__ void run_smooth(const FitDev& fd, const RunArgs& ra, 
     }
 
     // search, by the blocks that score lambdas and those that transform back
-    const int quads = B.mE0 * B.mX0, scorers = (max(fd.sm_k1, 65) + NW - 1) / NW;
+    const int quads = B.mE0 * B.mX0, scorers = (max(fd->sm_k1, 65) + NW - 1) / NW;
     if (b >= scorers && b * QPB >= quads) return;
     for (int c = t; c < n; c += BLOCK) {
         sa[c] = basis[c];  // eigenvalues
@@ -389,11 +413,11 @@ __device__ __forceinline__ void run_smooth(const FitDev& fd, const RunArgs& ra, 
     }
     __syncthreads();
     // stage 0: sm_k1 points lo + 0.25 i; stages 1 and 2: 65 points lo + (hi - lo) i / 64
-    double lo = fd.sm_plo, hi = 0.0;
+    double lo = fd->sm_plo, hi = 0.0;
     int best = 0;
 #pragma unroll 1
     for (int st = 0; st < 3; ++st) {
-        const int npts = st == 0 ? fd.sm_k1 : 65;
+        const int npts = st == 0 ? fd->sm_k1 : 65;
         const G<Word> sc = sw.score + (size_t)st * kSmoothMaxPoints * 2;
         for (int i = b * NW + wave; i < npts; i += nb * NW) {
             const double lam = pow10_of(st == 0 ? lo + 0.25 * i : lo + (hi - lo) * i / 64.0);
@@ -459,10 +483,10 @@ __device__ __forceinline__ void run_smooth(const FitDev& fd, const RunArgs& ra, 
                                           return part[t >> 2][p];
                                       }), floor_v);
                 const int c = base + k * nx + l;
-                gmem(fd.gprior)[c] = v;
-                gmem<T>(fd.ucell)[c] = (T)v;
+                gmem(fd->gprior)[c] = v;
+                gmem<T>(fd->ucell)[c] = (T)v;
                 Words<double>::put(sw.prior + (size_t)c * 2, v, tag);
-                Words<T>::put(gmem<Word>(ra.cell) + (size_t)c * Words<T>::n, (T)v, tag);
+                Words<T>::put(gmem<Word>(ra->cell) + (size_t)c * Words<T>::n, (T)v, tag);
             }
         }
         __syncthreads();
@@ -497,9 +521,11 @@ struct RunParams {
 // at the start of the kernel they cost a launch of one step 0.6-0.9 of 12.4 us).
 // SMOOTH: the priors are smoothed at every refresh.
 // late(): where fd and ra are in memory, as addresses that the compiler knows nothing
-// of: what the end of the launch needs is read again there, as everything held
-// through the step loop costs its scalar registers (they spill to lanes, and
-// reading ten of them back per particle took 100 steps of 10^6 from 1154 to 1179 us).
+// of: what a step needs after its particles, and the end of the launch, is read
+// there. Held through the particle loop it costs the loop's scalar registers: 154
+// values spilled to lanes, 100 of them read back in the loop (FP32 Gauss-Hermite,
+// 1024 threads), now 92 and 48. 100 steps of 10^6 particles 1173 us so and 1124 now, one
+// step of 4001 11.2 and 10.3.
 template <typename T, int BLOCK, int KIN, bool KNOWN, bool OWN, bool SMOOTH, typename Late>
 __device__ __forceinline__ void run_fit(const FitDev& fd, const RunArgs& ra, int b,
                                         const uint32_t n_blocks, const RunCall& call, Late late) {
@@ -507,7 +533,7 @@ __device__ __forceinline__ void run_fit(const FitDev& fd, const RunArgs& ra, int
     constexpr int NW = BLOCK / 64;
     __shared__ double part[NW][kRunCols], part2[NW][kRunCols];
     __shared__ int flag;
-    __shared__ uint32_t dead[2];
+    __shared__ uint32_t dead[2], group[3];
     using A = double;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int n = (int)fd.n;
@@ -521,8 +547,9 @@ __device__ __forceinline__ void run_fit(const FitDev& fd, const RunArgs& ra, int
     }
     const uint32_t start0 = KNOWN ? call.start0 : sync->start0;
     const uint32_t tag0 = KNOWN ? call.tag0 : sync->tag0;
+    uint64_t came = 0;
     if (tid == 0) {
-        (void)__hip_atomic_fetch_add(&ra.sync->start, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        came = __hip_atomic_fetch_add(&ra.sync->start, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         const uint32_t most = sync->wait;
         dead[0] = 0;
         dead[1] = most ? most : kRunWait;
@@ -584,23 +611,35 @@ __device__ __forceinline__ void run_fit(const FitDev& fd, const RunArgs& ra, int
         }
     }
     if (tid == 0) {
-        int how = 1;
-        if (!all_running(ra.sync, start0 + n_blocks)) {
-            const uint32_t out =
-                __hip_atomic_fetch_add(&ra.sync->left, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            how = out == n_blocks - 1 ? 2 : 0;
+        // the blocks that do the run (0: this one leaves) and this one's place among
+        // them, and whether others had to leave
+        const uint64_t v = all_running(ra.sync, start0, n_blocks, sync->patience);
+        uint32_t m = n_blocks, at = (uint32_t)b, off = 0;
+        if ((uint32_t)v & kRunOff) {
+            off = 1;
+            m = (uint32_t)(v >> 32);
+            at = (uint32_t)came - start0;
+            if ((uint32_t)came & kRunOff) {
+                const bool end = leave_run(sync, n_blocks);
+                if (end && m > 0)
+                    ready_again(sync, st, start0, n_blocks, OWN ? st->steps_left : n_steps, n_steps);
+                m = end && m == 0 ? 1 : 0;
+                at = 0;
+                off = 2;  // alone: has left already
+            }
         }
-        flag = how;
+        group[0] = m;
+        group[1] = at;
+        group[2] = off;
     }
     __syncthreads();
-    const int how = __builtin_amdgcn_readfirstlane(flag);
-    if (how == 0) return;
-    const bool alone = how == 2;
-    if (alone) {
-        b = 0;
-        nb = 1;
-        i0 = tid;
-        istep = BLOCK;
+    const bool whole = __builtin_amdgcn_readfirstlane(group[2]) == 0;
+    if (!whole) {
+        nb = __builtin_amdgcn_readfirstlane(group[0]);
+        if (nb == 0) return;
+        b = __builtin_amdgcn_readfirstlane(group[1]);
+        i0 = (wave * nb + b) * 64 + lane;
+        istep = NW * nb * 64;
         if (i0 < n) load(i0);
     }
     const Waiter wt{dead};
@@ -610,7 +649,7 @@ __device__ __forceinline__ void run_fit(const FitDev& fd, const RunArgs& ra, int
     kept.slots = (n + istep - 1) / istep * BLOCK;
     kept.val = reinterpret_cast<T*>(lds_raw + ra.keep_at);
     kept.code = reinterpret_cast<uint32_t*>(kept.val + Kept<T, KIN>::nv * kept.slots);
-    const bool keep = !alone && ra.keep_bytes > 0;
+    const bool keep = whole && ra.keep_bytes > 0;
     bool assigned = false;  // some step of this launch wrote the priors
     uint32_t ptag = 0u;     // the last refresh of this launch
 
@@ -691,10 +730,11 @@ __device__ __forceinline__ void run_fit(const FitDev& fd, const RunArgs& ra, int
         }
         // the first particle of the next step, requested before the exchange
         if (!resident && !last && i0 < n) load(i0);
+        const auto la = late();
         __syncthreads();
         // this block's row of sums; the bins are cleared for the next step
         const int t0 = thread_here();
-        const G<Word> row = gmem<Word>(ra.rows) + (size_t)b * ncol * 2;
+        const G<Word> row = gmem<Word>(la.ra->rows) + (size_t)b * ncol * 2;
         for (int j = t0; j < J; j += BLOCK) {
             double t = 0.0;
             for (int g = 0; g < kp; ++g) {
@@ -710,20 +750,21 @@ __device__ __forceinline__ void run_fit(const FitDev& fd, const RunArgs& ra, int
                 tb.csum[j] = 0.0;
                 tb.ccnt[j] = 0u;
             }
-        for (int q = b; q < ra.n_jobs; q += nb)
-            obs_job<T, BLOCK>(fd, ra, wt, q, nb, ncol, tag, k, last, part);
+        for (int q = b; q < la.ra->n_jobs; q += nb)
+            obs_job<T, BLOCK>(la.fd, la.ra, wt, q, nb, ncol, tag, k, last, part);
         if (refresh)
             // cell jobs from the last block down, away from the observable jobs
-            for (int q = nb - 1 - b; q < ra.n_cell_jobs; q += nb)
-                cell_job<T, BLOCK, SMOOTH>(fd, ra, wt, q, nb, ncol, tag, ptag, part, part2);
+            for (int q = nb - 1 - b; q < la.ra->n_cell_jobs; q += nb)
+                cell_job<T, BLOCK, SMOOTH>(la.fd, la.ra, wt, q, nb, ncol, tag, ptag, part, part2);
         if (SMOOTH && refresh) {
-            for (int half = 0; half <= (fd.cell_flags & 1); ++half)
-                run_smooth<T, BLOCK>(fd, ra, wt, half, b, nb, tag, lds_raw + run_smooth_at(ra), part, &flag);
+            for (int half = 0; half <= (la.fd->cell_flags & 1); ++half)
+                run_smooth<T, BLOCK>(la.fd, la.ra, wt, half, b, nb, tag,
+                                     lds_raw + ((la.ra->keep_at + la.ra->keep_bytes + 7) & ~7), part, &flag);
             ptag = tag;
         }
         if (!last) {
             for (int j = t0; j < J; j += BLOCK)
-                tb.rp[j] = take<T>(wt, gmem<const Word>(ra.res) + (size_t)j * Words<T>::n, tag);
+                tb.rp[j] = take<T>(wt, gmem<const Word>(la.ra->res) + (size_t)j * Words<T>::n, tag);
             __syncthreads();
         }
         assign = refresh;
@@ -732,12 +773,18 @@ __device__ __forceinline__ void run_fit(const FitDev& fd, const RunArgs& ra, int
     // every block reports its own waits: the last one may be done before
     const auto la = late();
     const G<FitState> se = gmem(la.fd->st);
-    if (tid == 0 && dead[0]) add_error(se, 2);
+    if (tid == 0) {
+        if (dead[0]) add_error(se, 2);
+        if (group[2]) {
+            const G<RunSync> sy = gmem(la.ra->sync);
+            if (group[2] == 2 || leave_run(sy, n_blocks))
+                ready_again(sy, se, start0, n_blocks, OWN ? se->steps_left : n_steps, n_steps);
+        }
+    }
     // the last block (it has the fewest particles) ends the run: chi^2 of every
     // step from its jobs' parts in order, then the counters
     if (b != nb - 1) return;
     const int64_t kstep0 = se->kstep, tstep0 = se->tstep;
-    const int32_t left0 = OWN ? se->steps_left : n_steps;
     // up to 16 lanes a step, so that the steps take one pass: one lane per step
     // read 164 parts (2610 observables) in turn, 31 us at the end of every launch
     bool bad = false;
@@ -761,15 +808,14 @@ __device__ __forceinline__ void run_fit(const FitDev& fd, const RunArgs& ra, int
         if (any_bad || dead[0]) add_error(se, (any_bad ? 1 : 0) | (dead[0] ? 2 : 0));
         se->tstep = tstep0 + n_steps;
         if (correct) se->kstep = kstep0 + n_steps;
-        se->steps_left = left0 - n_steps;
         se->correct = correct ? 1 : 0;
         se->assign_pending = assign ? 1 : 0;
         const G<RunSync> sy = gmem(la.ra->sync);
         sy->tag0 = tag0 + (uint32_t)n_steps;
-        sy->start0 = start0 + n_blocks;
-        if (alone) {
-            sy->start = start0 + n_blocks;
-            sy->left = 0u;
+        if (group[2] == 0) {
+            sy->start0 = start0 + n_blocks;
+            sy->patience = 0u;
+            se->steps_left = OWN ? se->steps_left - n_steps : 0;
         }
     }
 }
@@ -794,7 +840,7 @@ __global__ __launch_bounds__(BLOCK) void k_runs(const FitDev* __restrict__ fits,
             // the index, not the tables' addresses: these stay known as read only
             int f = t.fit;
             asm volatile("" : "+s"(f));
-            return LateArgs<const FitDev*, const RunArgs*>{fits + f, ras + f};
+            return LateArgs<Const<FitDev>, Const<RunArgs>>{(Const<FitDev>)(fits + f), (Const<RunArgs>)(ras + f)};
         });
 }
 

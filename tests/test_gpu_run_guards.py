@@ -16,8 +16,9 @@ torch = pytest.importorskip("torch")
 
 # byte offset of the error bits in the workspace (FitState comes first)
 ERROR_AT = 28
-# of the longest wait within a run, in the counters of its launches
-WAIT_IN_SYNC = 16
+# in the counters of a fit's launches: blocks started, longest wait within a run,
+# patience with blocks that do not start
+START, WAIT, PATIENCE = 0, 20, 24
 
 
 @pytest.fixture(scope="module")
@@ -40,6 +41,7 @@ def _sync(f, at):
     """The counters of a fit's launches: they come last in the workspace, and a fit
     with a refresh on every step has the same workspace up to there."""
     from paper_1202_2355_amd import _abi as A
+    torch.cuda.synchronize()
     base = A.m2m_workspace_bytes(f.layout, dict(f.params, prior_every=1), f.n, f.dtype)
     return f._ws[base + at:base + at + 4].view(torch.int32)
 
@@ -54,7 +56,7 @@ def test_a_wait_without_its_value_fails_one_launch_only(oracle, Fit, kin, dtype,
     for f in (a, b):
         f.step(5)
     good, parts = b.get_state(), {k: v.clone() for k, v in b.t.items()}
-    wait = _sync(b, WAIT_IN_SYNC)
+    wait = _sync(b, WAIT)
     assert int(wait[0]) == 0
     wait.fill_(1)
     b.step(6)
@@ -74,6 +76,133 @@ def test_a_wait_without_its_value_fails_one_launch_only(oracle, Fit, kin, dtype,
         np.testing.assert_allclose(pb[c], pa[c], rtol=tol, atol=1e-12)
     a.close()
     b.close()
+
+
+# (kind, dtype, particles, smoothed priors)
+CALLED_OFF = [("gh", "f32", 1001, False), ("gh", "f32", 40_009, False), ("gh6", "f64", 20_011, False),
+              ("losvd", "f32", 100_003, False), ("gh", "f32", 262_147, False), ("gh", "f32", 30_011, True),
+              ("v2", "f64", 9001, True)]
+
+
+def _smoothed(oracle, Fit, kin, dtype, n, smooth, **kw):
+    wl = _workload(kin, 4)
+    wl = wl.with_(params=dict(wl.params, smooth=int(smooth)))
+    parts = cast(wl.initial_particles(n=n, seed=n % 97), dtype)
+    return _fit(Fit, wl, parts, _targets(oracle, wl, parts, n), dtype, **kw)
+
+
+def _same(a, b, dtype):
+    tol = 1e-5 if dtype == "f32" else 1e-10
+    np.testing.assert_allclose(b.chi2_history(), a.chi2_history(), rtol=10 * tol)
+    pa, pb = a.particles(), b.particles()
+    for c in pa:
+        np.testing.assert_allclose(pb[c], pa[c], rtol=tol, atol=1e-5 if dtype == "f32" else 1e-11)
+
+
+@pytest.fixture(scope="module")
+def hog(oracle, Fit):
+    """A fit whose step kernels hold every compute unit for 0.16 ms each."""
+    wl = _workload("v2", 4)
+    wl = wl.with_(layout=dict(wl.layout, dens="alm", l_max=8, n_r=20))
+    parts = cast(wl.initial_particles(n=1_500_000, seed=1), "f32")
+    f = Fit(wl.potential, wl.layout, wl.params, parts, dtype="f32", stream=torch.cuda.Stream())
+    y = f.observe()
+    f.set_targets(y, 0.05 * np.abs(y) + 1e-3 * np.abs(y).max())
+    yield f
+    f.close()
+
+
+@pytest.mark.parametrize("kin,dtype,n,smooth", CALLED_OFF)
+def test_a_launch_called_off_before_it_started(oracle, Fit, kin, dtype, n, smooth):
+    """A launch marked as called off from the host: no block of it has started, so
+    the last to leave does its steps, refreshes and the assignment carried over
+    among them; the launches after it run as usual."""
+    _say("marked", kin, dtype, n, smooth)
+    a, b = (_smoothed(oracle, Fit, kin, dtype, n, smooth) for _ in range(2))
+    for f in (a, b):
+        f.step(3)
+    blocks = int(_sync(b, START)[0])
+    _sync(b, START).add_(-(1 << 31))
+    for f in (a, b):
+        f.step(7)
+    assert int(_sync(b, START)[0]) == 2 * blocks and int(_sync(b, PATIENCE)[0]) > 1
+    for f in (a, b):
+        f.step(5)
+    assert int(_sync(b, START)[0]) == 3 * blocks and int(_sync(b, PATIENCE)[0]) == 0
+    _same(a, b, dtype)
+    a.close()
+    b.close()
+
+
+@pytest.mark.parametrize("kin,dtype,n,smooth", CALLED_OFF)
+def test_a_launch_called_off_is_done_by_the_blocks_that_started(oracle, Fit, hog, kin, dtype, n, smooth):
+    """Launches without patience for blocks that have not started (set from the
+    host) beside kernels that hold the compute units. Streams that share the
+    other kernels' hardware queue never meet them, so several are tried."""
+    _say("no patience", kin, dtype, n, smooth)
+    off = 0
+    for _ in range(8):
+        a = _smoothed(oracle, Fit, kin, dtype, n, smooth)
+        b = _smoothed(oracle, Fit, kin, dtype, n, smooth, stream=torch.cuda.Stream())
+        for k in range(16):
+            _sync(b, PATIENCE).fill_(1)
+            torch.cuda.synchronize()
+            hog.step(6)
+            b.step(2 + k % 4)
+            a.step(2 + k % 4)
+            off += int(_sync(b, PATIENCE)[0]) > 1
+        _same(a, b, dtype)
+        a.close()
+        b.close()
+        if off > 1:
+            break
+    _say("called off", off)
+    assert off > 0
+
+
+@pytest.mark.parametrize("kin,dtype", [("gh", "f32"), ("v2", "f64"), ("losvd", "f32")])
+def test_fits_of_a_batch_called_off_one_by_one(oracle, Fit, hog, kin, dtype):
+    """A batch of uneven fits with different numbers of steps beside such kernels,
+    some fits without patience, one marked as called off: blocks that start late
+    find the steps that the fit had left, however far the others are."""
+    from paper_1202_2355_amd.batch import Batch
+    plan = [(40_009, 33), (1003, 9), (90_001, 60)] if kin != "losvd" else [(40_009, 33), (9001, 60)]
+    _say("batch called off", kin, plan)
+    off = 0
+    for attempt in range(8):
+        st = torch.cuda.Stream()
+        b = Batch(max_fits=4, stream=st)
+        ref, fits = [], []
+        for n, steps in plan:
+            r = _made(oracle, Fit, kin, dtype, n)
+            r.step(steps)
+            ref.append(r)
+            f = _made(oracle, Fit, kin, dtype, n, stream=st)
+            assert b.admit(f, steps)
+            fits.append(f)
+        for k in range(16):
+            for j, f in enumerate(fits):
+                if j != k % 3:
+                    _sync(f, PATIENCE).fill_(1)
+            if k == 2:
+                _sync(fits[-1], START).add_(-(1 << 31))
+            torch.cuda.synchronize()
+            hog.step(6)
+            b.run(4)
+            off += sum(int(_sync(f, PATIENCE)[0]) > 1 for f in fits)
+        done, left = b.poll()
+        assert left == 0 and len(done) == len(plan)
+        b.close()
+        for f, r in zip(fits, ref):
+            f.step(2)
+            r.step(2)
+            _same(r, f, dtype)
+            f.close()
+            r.close()
+        if off > 3 + attempt:  # more than the marked ones
+            break
+    _say("called off", off)
+    assert off > 3
 
 
 @pytest.mark.parametrize("lagged", [False, True])
