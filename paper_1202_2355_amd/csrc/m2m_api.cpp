@@ -822,6 +822,18 @@ bool use_run(const m2m_ctx* c, int32_t n_steps) {
     return c->run && (c->w.J <= kRunShortJ || n_steps > 2) && !capturing(c->stream);
 }
 
+// Compute units that a stream may use: all, or those of its mask. A run of more
+// blocks would be called off at every launch (50 ms, then 0.1 ms and more).
+int stream_cus(hipStream_t s) {
+    uint32_t mask[32] = {};
+    int n = 0;
+    if (hipExtStreamGetCUMask(s, 32, mask) == hipSuccess)
+        for (uint32_t m : mask) n += __builtin_popcount(m);
+    else
+        (void)hipGetLastError();
+    return n > 0 ? std::min(n, n_cus()) : n_cus();
+}
+
 bool own_order(const RunOwner& a, const RunOwner& b) {
     return a.stream == b.stream && a.stream != hipStreamPerThread;
 }
@@ -1219,7 +1231,7 @@ m2m_status m2m_create(const m2m_potential* pot, const m2m_obs_layout* layout,
     if (hipGetDevice(&c->dev) != hipSuccess) return bail(M2M_EDEVICE);
     c->run_sh = run_shape(n, c->f64, w.J);
     c->run = w.run && c->acc64 && g_interleave < 0 && c->dev >= 0 && c->dev < kRunDevices &&
-             c->run_sh.blocks <= n_cus() && c->lds + run_smooth_lds(c->par) + 8 + kRunStaticLds <= max_lds();
+             c->run_sh.blocks <= stream_cus(c->stream) && c->lds + run_smooth_lds(c->par) + 8 + kRunStaticLds <= max_lds();
     if (c->run) {
         c->run_args.n_jobs = (w.J + kRunCols - 1) / kRunCols;
         c->run_args.n_cell_jobs = (w.C + kRunCols - 1) / kRunCols;
@@ -1967,7 +1979,7 @@ m2m_status run_fits(m2m_batch* b) {
         least += (c->run_args.n_jobs + 2) / 3;
         b->run_many |= c->w.J > kRunShortJ;
     }
-    const int room = std::min(kRunMaxBlocks, n_cus());
+    const int room = std::min(kRunMaxBlocks, stream_cus(b->stream));
     if (ntot > kRunMaxN || least + nf > room) return M2M_OK;
     const bool f64 = b->f64 == 1;
     const int64_t tile = (ntot + (room - least) - 1) / (room - least);

@@ -293,3 +293,35 @@ def test_many_streams_share_the_slots(oracle, Fit):
     for f, u in zip(fits, alone):
         np.testing.assert_allclose(f.particles()["u"], u, rtol=1e-5)
         f.close()
+
+
+def test_a_stream_with_few_compute_units(oracle, Fit):
+    """On a stream that may use 64 compute units, a fit whose runs have more blocks
+    takes its steps one launch each, alone and in a batch; a small fit runs."""
+    import ctypes as C
+    from paper_1202_2355_amd.batch import Batch
+    hip = C.CDLL("libamdhip64.so")
+    h = C.c_void_p()
+    mask = (C.c_uint32 * 8)(0xffffffff, 0xffffffff)
+    assert hip.hipExtStreamCreateWithCUMask(C.byref(h), 8, mask) == 0
+    st = torch.cuda.ExternalStream(h.value)
+    for n, runs in ((1001, True), (300_007, False)):
+        _say("64 compute units", n)
+        a = _made(oracle, Fit, "gh", "f32", n)
+        b = _made(oracle, Fit, "gh", "f32", n, stream=st)
+        for f in (a, b):
+            f.step(9)
+        assert (int(_sync(b, START)[0]) > 0) == runs and int(_sync(b, PATIENCE)[0]) == 0
+        _same(a, b, "f32")
+        q = Batch(max_fits=1, stream=st)
+        assert q.admit(b, 4)
+        before = int(_sync(b, START)[0])
+        q.run(4)
+        assert (int(_sync(b, START)[0]) > before) == runs and int(_sync(b, PATIENCE)[0]) == 0
+        q.poll()
+        q.close()
+        a.step(4)
+        _same(a, b, "f32")
+        a.close()
+        b.close()
+    torch.cuda.synchronize()
