@@ -306,8 +306,8 @@ struct WsLayout {
     size_t cdata, gprior, scf_rho, scf_sum, scf_tab, sm_basis;
     size_t Y, sigma, yv, ytil, delta, obs, hist, chi2p, partials, total;
     size_t tail, otab;  // after what batched steps use: GH tables of an observation
-    bool run;           // the run kernel's exchange areas, last:
-    size_t run_sync, run_rows, run_res, run_cell, run_parts;
+    bool run;           // counters of the run kernel's launches, last:
+    size_t run_sync;
     int seg_cap, seg_lean, row_len, nbj, ncj, npj, J, C, P;  // P: interval sums of the expansion
 };
 
@@ -371,6 +371,23 @@ size_t run_smooth_lds(const m2m_params& P) {
     return P.smooth ? 16 * (size_t)P.n_E * (size_t)P.n_x : 0;
 }
 
+// The exchange areas of a run of `blocks` blocks, from `base` on, and their bytes.
+size_t place_areas(RunArgs& a, unsigned char* base, int J, int C, bool f64, bool smooth, int blocks) {
+    const size_t jobs = (size_t)(J + kRunCols - 1) / kRunCols, vw = f64 ? 16 : 8;
+    size_t o = 0;
+    const auto take = [&](size_t bytes) {
+        uint64_t* at = reinterpret_cast<uint64_t*>(base + o);
+        o = align_up(o + bytes, 256);
+        return at;
+    };
+    a.rows = take(16 * (size_t)blocks * (size_t)(J + 2 * C));
+    a.res = take(vw * (size_t)J);
+    a.cell = take(vw * (size_t)C);
+    a.parts = take(16 * jobs * (size_t)kRunMaxSteps +
+                   (smooth ? 8 * (6 * (size_t)C + 2 * (2 + 6 * (size_t)kSmoothMaxPoints)) : 0));
+    return o;
+}
+
 // cell_index = false: no per-particle cell index (observation only)
 WsLayout plan(const m2m_obs_layout& L, const m2m_params& P, int64_t n, bool f64,
               bool cell_index = true) {
@@ -427,15 +444,7 @@ WsLayout plan(const m2m_obs_layout& L, const m2m_params& P, int64_t n, bool f64,
     w.tail = o;
     w.otab = take(cell_index && L.kin == M2M_KIN_GH ? w.rp - w.Vp : 0);
     w.run = cell_index && run_kind(L, P, n);
-    if (w.run) {
-        const size_t jobs = (size_t)(w.J + kRunCols - 1) / kRunCols, vw = f64 ? 16 : 8;
-        w.run_sync = take(sizeof(RunSync));
-        w.run_rows = take(16 * (size_t)run_shape(n, f64, w.J).blocks * (size_t)(w.J + 2 * w.C));
-        w.run_res = take(vw * (size_t)w.J);
-        w.run_cell = take(vw * (size_t)w.C);
-        w.run_parts = take(16 * jobs * (size_t)kRunMaxSteps +
-                           (P.smooth ? 8 * (6 * (size_t)w.C + 2 * (2 + 6 * (size_t)kSmoothMaxPoints)) : 0));
-    }
+    if (w.run) w.run_sync = take(sizeof(RunSync));
     w.total = o;
     return w;
 }
@@ -537,8 +546,25 @@ void put_obs_tables(unsigned char* img, const WsLayout& w, const m2m_obs_layout&
 // takes. Each run carries an event of its owner, completed by the launch itself:
 // no call is made on another owner's stream (which may be captured or destroyed
 // at any time), and nothing but runs is waited for.
-struct RunOwner {  // a context or a batch
+//
+// The blocks of a run exchange through memory of its stream (its runs come one
+// after another), made at the first and as large as the largest needs, up to 52 MiB
+// for a fit and 256 blocks of 12288 columns for a batch. In the fits' workspaces
+// it would be many times the rest: 17.6 MB for 4001 particles of the LOSVD layout
+// (0.13 MB of state).
+struct StreamArea {
     hipStream_t stream = nullptr;
+    int users = 0;                // contexts and batches
+    unsigned char* mem = nullptr;
+    size_t bytes = 0;
+    // smaller ones before it: batches keep their places in them
+    std::vector<std::pair<unsigned char*, size_t>> old;
+    // the last step tag given out. Cleared words carry tag 0, and the first round of
+    // tags is short, so that what happens at its end happens often.
+    uint32_t tag = 0u - 8192u;
+};
+struct RunOwner {  // a context or a batch
+    StreamArea* area = nullptr;
     hipEvent_t ev = nullptr;   // its last run that carried an event
     // slots that its runs in flight lie in, of which that run is the last to end;
     // 0 blocks: nothing to wait for
@@ -548,6 +574,8 @@ struct RunOwner {  // a context or a batch
 struct RunGate {
     std::mutex mu;
     std::vector<RunOwner*> owners;
+    std::vector<StreamArea*> areas;
+    std::vector<std::pair<unsigned char*, size_t>> idle;  // memory of streams that are gone
     bool shared = false;  // their streams are not all the same
     uint64_t seq = 0;
 };
@@ -583,9 +611,9 @@ struct m2m_ctx {
     RunShape run_sh{};
     RunArgs run_args{};
     RunOwner run_owner;
-    // its steps and blocks run so (count_run), exactly (run_known: no run in a
-    // batch, where a fit may have fewer steps left) or at most
-    uint32_t run_tag = 0, run_start = 0;
+    // its counter of blocks started, as long as no batch has run it (where a fit
+    // with no steps left does not count)
+    uint32_t run_start = 0;
     bool run_known = true;
     hipGraphExec_t graph_prof = nullptr;  // steps with an extra measuring reduction
     bool targets = false;
@@ -688,13 +716,24 @@ struct Pinned {
     Pinned(const Pinned&) = delete;
     Pinned& operator=(const Pinned&) = delete;
 };
-void count_context(int d) {
+bool any_context() {
     PinPool& g = pins();
     std::lock_guard<std::mutex> lock(g.mu);
-    if ((g.contexts += d) > 0) return;
-    for (void* q : g.idle) (void)hipHostFree(q);
-    g.made -= (int)g.idle.size();
-    g.idle.clear();
+    return g.contexts > 0;
+}
+constexpr int kRunDevices = 64;
+RunGate g_run_gate[kRunDevices];
+void free_idle_memory();
+void count_context(int d) {
+    PinPool& g = pins();
+    {
+        std::lock_guard<std::mutex> lock(g.mu);
+        if ((g.contexts += d) > 0) return;
+        for (void* q : g.idle) (void)hipHostFree(q);
+        g.made -= (int)g.idle.size();
+        g.idle.clear();
+    }
+    free_idle_memory();
 }
 
 m2m_status upload(m2m_ctx* c, size_t off, const std::vector<double>& v) {
@@ -806,9 +845,6 @@ hipError_t launch_one_step(m2m_ctx* c, hipStream_t s) {
 }
 
 // ---- run kernel -------------------------------------------------------------
-constexpr int kRunDevices = 64;
-RunGate g_run_gate[kRunDevices];
-
 bool capturing(hipStream_t s) {
     hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
     return hipStreamIsCapturing(s, &st) != hipSuccess || st != hipStreamCaptureStatusNone;
@@ -834,23 +870,120 @@ int stream_cus(hipStream_t s) {
     return n > 0 ? std::min(n, n_cus()) : n_cus();
 }
 
-bool own_order(const RunOwner& a, const RunOwner& b) {
-    return a.stream == b.stream && a.stream != hipStreamPerThread;
+bool own_order(const RunOwner& a, const RunOwner& b) { return a.area == b.area; }
+
+// Another thread may be capturing: allocations of this one are none of its business.
+struct CaptureRelaxed {
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    CaptureRelaxed() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
+    ~CaptureRelaxed() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
+};
+
+// Device memory of at least `bytes`: what a stream that is gone has left, or new. At
+// most kIdleBlocks are left, and none once the last context is gone.
+constexpr size_t kIdleBlocks = 4;
+unsigned char* take_memory(int dev, RunGate& g, size_t bytes, size_t* got) {
+    auto best = g.idle.end();
+    for (auto it = g.idle.begin(); it != g.idle.end(); ++it)
+        if (it->second >= bytes && (best == g.idle.end() || it->second < best->second)) best = it;
+    if (best != g.idle.end()) {
+        unsigned char* p = best->first;
+        *got = best->second;
+        g.idle.erase(best);
+        return p;
+    }
+    size_t n = size_t(1) << 20;
+    while (n < bytes) n *= 2;
+    const CaptureRelaxed relaxed;
+    int now = 0;
+    void* p = nullptr;
+    const bool elsewhere = hipGetDevice(&now) == hipSuccess && now != dev && hipSetDevice(dev) == hipSuccess;
+    if (hipMalloc(&p, n) != hipSuccess) {
+        (void)hipGetLastError();
+        p = nullptr;
+    }
+    if (elsewhere) (void)hipSetDevice(now);
+    *got = n;
+    return static_cast<unsigned char*>(p);
+}
+void leave_memory(RunGate& g, unsigned char* p, size_t bytes) {
+    if (!p) return;
+    if (g.idle.size() < kIdleBlocks && any_context()) {
+        g.idle.emplace_back(p, bytes);
+        return;
+    }
+    const CaptureRelaxed relaxed;
+    (void)hipFree(p);
+}
+void free_idle_memory() {
+    for (RunGate& g : g_run_gate) {
+        std::lock_guard<std::mutex> lock(g.mu);
+        for (auto& m : g.idle) (void)hipFree(m.first);
+        g.idle.clear();
+    }
 }
 
-// An owner of runs on the gate's device comes or goes (its runs have ended).
-void join_gate(int dev, RunOwner* o, bool in) {
+// An owner of runs on the stream comes or goes (its runs have ended).
+void join_gate(int dev, RunOwner* o, hipStream_t stream) {
     RunGate& g = g_run_gate[dev];
     std::lock_guard<std::mutex> lock(g.mu);
-    if (in)
-        g.owners.push_back(o);
-    else
-        g.owners.erase(std::remove(g.owners.begin(), g.owners.end(), o), g.owners.end());
-    g.shared = false;
-    for (const RunOwner* x : g.owners) g.shared |= !own_order(*x, *g.owners[0]);
-    if (in) return;
+    for (StreamArea* a : g.areas)
+        if (a->stream == stream && stream != hipStreamPerThread) o->area = a;
+    if (!o->area) {
+        o->area = new StreamArea();
+        o->area->stream = stream;
+        g.areas.push_back(o->area);
+    }
+    ++o->area->users;
+    g.owners.push_back(o);
+    g.shared = g.areas.size() > 1;
+}
+void leave_gate(int dev, RunOwner* o) {
+    RunGate& g = g_run_gate[dev];
+    std::lock_guard<std::mutex> lock(g.mu);
+    g.owners.erase(std::remove(g.owners.begin(), g.owners.end(), o), g.owners.end());
     if (o->ev) (void)hipEventDestroy(o->ev);
-    o->ev = nullptr;
+    StreamArea* a = o->area;
+    *o = RunOwner();
+    if (--a->users > 0) return;
+    leave_memory(g, a->mem, a->bytes);
+    for (auto& m : a->old) leave_memory(g, m.first, m.second);
+    g.areas.erase(std::remove(g.areas.begin(), g.areas.end(), a), g.areas.end());
+    g.shared = g.areas.size() > 1;
+    delete a;
+}
+
+// Exchange memory of `bytes` for runs on the area's stream (under the gate's
+// mutex), cleared on that stream; NULL if there is none.
+unsigned char* exchange_memory(int dev, RunGate& g, StreamArea* a, size_t bytes) {
+    if (a->bytes >= bytes) return a->mem;
+    size_t got = 0;
+    unsigned char* p = take_memory(dev, g, bytes, &got);
+    if (!p) return nullptr;
+    if (hipMemsetAsync(p, 0, got, a->stream) != hipSuccess) {
+        (void)hipGetLastError();
+        leave_memory(g, p, got);
+        return nullptr;
+    }
+    if (a->mem) a->old.emplace_back(a->mem, a->bytes);
+    a->mem = p;
+    a->bytes = got;
+    return p;
+}
+
+// The tags of n_steps steps on the area's stream are *tag0 + 1 and on. Before they
+// come round every word is cleared: none may carry the tag of an old step.
+hipError_t take_tags(StreamArea* a, int32_t n_steps, uint32_t* tag0) {
+    if (a->tag > 0xffffffffu - (uint32_t)n_steps) {
+        hipError_t e = hipMemsetAsync(a->mem, 0, a->bytes, a->stream);
+        for (auto& m : a->old)
+            if (e == hipSuccess) e = hipMemsetAsync(m.first, 0, m.second, a->stream);
+        if (e != hipSuccess) return e;
+        a->tag = 0;
+    }
+    *tag0 = a->tag;
+    a->tag += (uint32_t)n_steps;
+    return hipSuccess;
 }
 
 // The first of the `blocks` slots of the owner's next run: its own slots again if
@@ -878,26 +1011,32 @@ int place_run(const RunGate& g, const RunOwner* o, int blocks) {
     return best;
 }
 
-// go(done) launches the owner's run of `blocks` blocks, which completes the event
-// `done` (NULL: none is needed), after the runs whose slots it takes. While all
+// go(done, mem, tag0) launches the owner's run of `blocks` blocks and n_steps steps with
+// `bytes` of exchange memory, which completes the event `done` (NULL: none is
+// needed), after the runs whose slots it takes. hipErrorOutOfMemory, with nothing
+// launched, if there is no such memory. While all
 // owners are on one stream, no run carries an event: it costs a launch 3 us (64 steps
 // of a batch 504.0 us without, 508.6 with). So runs already in flight when the first
 // owner on another stream comes are not waited for; blocks that cannot start
 // beside them are what the launch's call-off is for.
 template <typename F>
-hipError_t ordered_run(int dev, RunOwner* o, int blocks, F&& go) {
+hipError_t ordered_run(int dev, RunOwner* o, int blocks, int32_t n_steps, size_t bytes, F&& go) {
     RunGate& g = g_run_gate[dev];
     std::lock_guard<std::mutex> lock(g.mu);
-    if (!g.shared) return go(nullptr);
-    hipError_t e = hipSuccess;
+    unsigned char* mem = exchange_memory(dev, g, o->area, bytes);
+    if (!mem) return hipErrorOutOfMemory;
+    uint32_t tag0 = 0;
+    hipError_t e = take_tags(o->area, n_steps, &tag0);
+    if (e != hipSuccess) return e;
+    if (!g.shared) return go(nullptr, mem, tag0);
     if (!o->ev) e = hipEventCreateWithFlags(&o->ev, hipEventDisableTiming);
     const int at = place_run(g, o, blocks);
     const auto in_the_way = [&](const RunOwner* x) {
         return x != o && x->blocks > 0 && !own_order(*x, *o) && x->at < at + blocks && at < x->at + x->blocks;
     };
     for (const RunOwner* x : g.owners)
-        if (e == hipSuccess && in_the_way(x)) e = hipStreamWaitEvent(o->stream, x->ev, 0);
-    if (e == hipSuccess) e = go(o->ev);
+        if (e == hipSuccess && in_the_way(x)) e = hipStreamWaitEvent(o->area->stream, x->ev, 0);
+    if (e == hipSuccess) e = go(o->ev, mem, tag0);
     if (e != hipSuccess) return e;
     // who would wait for a run whose slots are all taken now waits for this one
     for (RunOwner* x : g.owners)
@@ -910,36 +1049,27 @@ hipError_t ordered_run(int dev, RunOwner* o, int blocks, F&& go) {
     return hipSuccess;
 }
 
-// Counts n_steps more steps and `blocks` more blocks of the context's runs. Before
-// the 32-bit counters on the device come round, the exchange areas are cleared
-// (on stream st): no word may carry the tag of an old step.
-hipError_t count_run(m2m_ctx* c, int32_t n_steps, int blocks, hipStream_t st) {
-    hipError_t e = hipSuccess;
-    if (c->run_tag > 0xffffffffu - (uint32_t)kRunMaxSteps || c->run_start > 0x40000000u) {
-        e = hipMemsetAsync(c->ws + c->w.run_sync, 0, c->w.total - c->w.run_sync, st);
-        c->run_tag = 0;
-        c->run_start = 0;
-        c->run_known = e == hipSuccess;
-    }
-    c->run_tag += (uint32_t)n_steps;
-    c->run_start += (uint32_t)blocks;
-    return e;
-}
-
-m2m_status launch_run(m2m_ctx* c, int32_t n_steps, int32_t correct) {
-    const hipError_t counted = count_run(c, n_steps, c->run_sh.blocks, c->stream);
-    if (counted != hipSuccess) return hip_fail(c, counted, "run of steps");
-    const RunCall call{n_steps, correct ? 1 : 0, c->run_known ? 1 : 0,
-                       c->run_start - (uint32_t)c->run_sh.blocks, c->run_tag - (uint32_t)n_steps};
-    const hipError_t e = ordered_run(c->dev, &c->run_owner, c->run_sh.blocks, [&](hipEvent_t done) {
+// hipErrorOutOfMemory: nothing was launched, as the stream has no exchange memory
+hipError_t launch_run(m2m_ctx* c, int32_t n_steps, int32_t correct) {
+    const int nb = c->run_sh.blocks;
+    RunArgs ra = c->run_args;
+    const auto place = [&](unsigned char* mem) {
+        return place_areas(ra, mem, c->w.J, c->w.C, c->f64, c->par.smooth != 0, nb);
+    };
+    return ordered_run(c->dev, &c->run_owner, nb, n_steps, place(nullptr),
+                       [&](hipEvent_t done, unsigned char* mem, uint32_t tag0) {
+        (void)place(mem);
+        const RunCall call{n_steps, correct ? 1 : 0, c->run_known ? 1 : 0, c->run_start, tag0};
         const auto launch = c->par.smooth ? (c->f64 ? launch_run_smooth_f64 : launch_run_smooth_f32)
                                           : (c->f64 ? launch_run_f64 : launch_run_f32);
-        return launch(c->run_sh.block, c->kin, c->fd, c->run_args, c->run_sh.blocks,
-                      (size_t)run_smooth_at(c->run_args) + run_smooth_lds(c->par), call, c->stream, done);
+        const hipError_t e = launch(c->run_sh.block, c->kin, c->fd, ra, nb,
+                                    (size_t)run_smooth_at(ra) + run_smooth_lds(c->par), call, c->stream, done);
+        if (e == hipSuccess)
+            c->run_start = run_start_after(c->run_start, (uint32_t)nb);
+        else
+            c->run_known = false;
+        return e;
     });
-    if (e != hipSuccess) c->run_known = false;  // counted, but not run
-    if (e != hipSuccess) return hip_fail(c, e, "run of steps");
-    return M2M_OK;
 }
 
 // LDS bytes of the kernels kept between steps (Kept in m2m_run.h) of a fit
@@ -1238,10 +1368,6 @@ m2m_status m2m_create(const m2m_potential* pot, const m2m_obs_layout* layout,
         c->run_args.keep_at = (int32_t)c->lds;
         c->run_args.keep_bytes = kept_bytes(c, c->run_sh.block, c->run_sh.blocks);
         c->run_args.sync = reinterpret_cast<RunSync*>(b + w.run_sync);
-        c->run_args.rows = reinterpret_cast<uint64_t*>(b + w.run_rows);
-        c->run_args.res = reinterpret_cast<uint64_t*>(b + w.run_res);
-        c->run_args.cell = reinterpret_cast<uint64_t*>(b + w.run_cell);
-        c->run_args.parts = reinterpret_cast<uint64_t*>(b + w.run_parts);
     }
 
     // ---- tables
@@ -1300,8 +1426,7 @@ m2m_status m2m_create(const m2m_potential* pot, const m2m_obs_layout* layout,
         copy_sync(c->stream, c->fd_dev, &f, sizeof(FitDev), hipMemcpyHostToDevice) != hipSuccess)
         return bail(M2M_EDEVICE);
     count_context(1);
-    c->run_owner.stream = c->stream;
-    if (c->run) join_gate(c->dev, &c->run_owner, true);
+    if (c->run) join_gate(c->dev, &c->run_owner, c->stream);
     *out = c;
     return M2M_OK;
 }
@@ -1355,10 +1480,14 @@ m2m_status m2m_step(m2m_ctx* c, int32_t n_steps, int32_t correct) {
     if (n_steps == 0) return M2M_OK;
     c->may_assign = true;
     if (use_run(c, n_steps)) {
-        for (int32_t done = 0; done < n_steps; done += kRunMaxSteps)
-            if (m2m_status s = launch_run(c, std::min(n_steps - done, kRunMaxSteps), correct); s != M2M_OK)
-                return s;
-        return M2M_OK;
+        hipError_t e = hipSuccess;
+        while (n_steps > 0 && e == hipSuccess) {
+            const int32_t k = std::min(n_steps, kRunMaxSteps);
+            if ((e = launch_run(c, k, correct)) == hipSuccess) n_steps -= k;
+        }
+        if (e == hipSuccess) return M2M_OK;
+        if (e != hipErrorOutOfMemory) return hip_fail(c, e, "run of steps");
+        // the remaining steps one launch each
     }
     M2M_HIP(c, launch_poke(c->st, n_steps, correct ? 1 : 0, c->stream));
     const int full = n_steps / kGraphSteps, rem = n_steps % kGraphSteps;
@@ -1679,7 +1808,7 @@ m2m_status m2m_destroy(m2m_ctx* c) {
     if (!c) return M2M_EINVAL;
     if (c->batch) return fail(c, M2M_ESTATE, "fit is in a batch");
     (void)hipStreamSynchronize(c->stream);
-    if (c->run) join_gate(c->dev, &c->run_owner, false);
+    if (c->run) leave_gate(c->dev, &c->run_owner);
     if (c->idle_ev) {
         // the batch runs that may still read the fit have ended
         (void)hipEventSynchronize(c->idle_ev);
@@ -1761,8 +1890,7 @@ struct m2m_batch {
     bool run = false, run_many = false;
     int run_block = 0, run_blocks = 0, dev = 0;
     RunOwner run_owner;  // joins the gate with its first tables
-    size_t run_lds = 0;
-    std::vector<int> run_nb;  // blocks per fit
+    size_t run_lds = 0, run_bytes = 0;  // and its exchange memory
     RunArgs* run_args_dev = nullptr;
     RunTile* run_tiles_dev = nullptr;
     size_t cap_run_args = 0, cap_run_tiles = 0;
@@ -1969,7 +2097,7 @@ constexpr int kRunMaxFits = 32;
 m2m_status run_fits(m2m_batch* b) {
     const int nf = (int)b->fits.size();
     b->run = b->run_many = false;
-    if (nf < 1 || nf > kRunMaxFits || g_batch_graphs) return M2M_OK;
+    if (nf < 1 || nf > kRunMaxFits || g_batch_graphs || capturing(b->stream)) return M2M_OK;
     int64_t ntot = 0;
     int want = 0, least = 0;
     for (m2m_ctx* c : b->fits) {
@@ -1985,37 +2113,51 @@ m2m_status run_fits(m2m_batch* b) {
     const int64_t tile = (ntot + (room - least) - 1) / (room - least);
     std::vector<RunArgs> ra;
     std::vector<RunTile> rt;
-    b->run_nb.clear();
+    std::vector<int> run_nb;  // blocks per fit
     int64_t most = 0;
     for (int f = 0; f < nf; ++f) {
         m2m_ctx* c = b->fits[f];
         int nb = c->run_sh.blocks;
         if (want > room)
             nb = std::min<int>(nb, std::max<int64_t>((c->n + tile - 1) / tile, (c->run_args.n_jobs + 2) / 3));
-        b->run_nb.push_back(nb);
+        run_nb.push_back(nb);
         most = std::max(most, (c->n + nb - 1) / nb);
         for (int k = 0; k < nb; ++k) rt.push_back(RunTile{f, k, nb, 0});
     }
     if ((int)rt.size() > room) return M2M_OK;
+    if (b->run_blocks == 0) {
+        b->dev = b->fits[0]->dev;
+        join_gate(b->dev, &b->run_owner, b->stream);
+        b->run_blocks = 1;
+    }
     b->run_block = f64 || most <= 512 ? 512 : 1024;
     b->run_lds = 0;
-    for (int f = 0; f < nf; ++f) {
-        m2m_ctx* c = b->fits[f];
-        RunArgs a = c->run_args;
-        a.keep_bytes = kept_bytes(c, b->run_block, b->run_nb[f]);
-        b->run_lds = std::max(b->run_lds, c->lds + (size_t)a.keep_bytes);
-        ra.push_back(a);
+    // the fits' areas one after another in memory of the batch stream
+    unsigned char* mem = nullptr;
+    for (int pass = 0; pass < 2; ++pass) {
+        b->run_bytes = 0;
+        ra.clear();
+        for (int f = 0; f < nf; ++f) {
+            m2m_ctx* c = b->fits[f];
+            RunArgs a = c->run_args;
+            a.keep_bytes = kept_bytes(c, b->run_block, run_nb[f]);
+            b->run_lds = std::max(b->run_lds, c->lds + (size_t)a.keep_bytes);
+            b->run_bytes += place_areas(a, mem + b->run_bytes, c->w.J, c->w.C, f64, false, run_nb[f]);
+            ra.push_back(a);
+        }
+        if (pass == 0) {
+            RunGate& g = g_run_gate[b->dev];
+            std::lock_guard<std::mutex> lock(g.mu);
+            mem = exchange_memory(b->dev, g, b->run_owner.area, b->run_bytes);
+            if (!mem) return M2M_OK;
+        }
     }
     const m2m_status copied = copy_tables(
         b, b->run_staging,
         {{reinterpret_cast<void**>(&b->run_args_dev), &b->cap_run_args, ra.data(), sizeof(RunArgs) * ra.size()},
          {reinterpret_cast<void**>(&b->run_tiles_dev), &b->cap_run_tiles, rt.data(), sizeof(RunTile) * rt.size()}});
     if (copied != M2M_OK) return copied;
-    if (b->run_blocks == 0) {
-        b->dev = b->fits[0]->dev;
-        b->run_owner.stream = b->stream;
-        join_gate(b->dev, &b->run_owner, true);
-    }
+    for (m2m_ctx* c : b->fits) c->run_known = false;
     b->run_blocks = (int)rt.size();
     b->run = true;
     return M2M_OK;
@@ -2227,16 +2369,12 @@ m2m_status m2m_batch_run(m2m_batch* b, int32_t steps_per_launch) {
         hipError_t e = hipSuccess;
         for (int32_t done = 0; done < steps_per_launch && e == hipSuccess; done += kRunMaxSteps) {
             const int k = std::min(steps_per_launch - done, kRunMaxSteps);
-            for (size_t f = 0; f < b->fits.size() && e == hipSuccess; ++f) {
-                e = count_run(b->fits[f], k, b->run_nb[f], b->stream);
-                b->fits[f]->run_known = false;
-            }
-            if (e == hipSuccess)
-                e = ordered_run(b->dev, &b->run_owner, b->run_blocks, [&](hipEvent_t done) {
-                    return (b->f64 == 1 ? launch_runs_f64 : launch_runs_f32)(
-                        b->run_block, b->kin, b->all.fits_dev, b->run_args_dev, b->run_tiles_dev,
-                        b->run_blocks, b->run_lds, k, b->stream, done);
-                });
+            e = ordered_run(b->dev, &b->run_owner, b->run_blocks, k, b->run_bytes,
+                            [&](hipEvent_t done_ev, unsigned char*, uint32_t tag0) {
+                return (b->f64 == 1 ? launch_runs_f64 : launch_runs_f32)(
+                    b->run_block, b->kin, b->all.fits_dev, b->run_args_dev, b->run_tiles_dev,
+                    b->run_blocks, b->run_lds, k, tag0, b->stream, done_ev);
+            });
         }
         if (e == hipSuccess) e = snapshot(b);
         return e == hipSuccess ? M2M_OK : M2M_EDEVICE;
@@ -2390,7 +2528,7 @@ m2m_status m2m_batch_destroy(m2m_batch* b) {
     if (!b) return M2M_EINVAL;
     (void)hipStreamSynchronize(b->stream);
     for (m2m_ctx* c : b->fits) c->batch = nullptr;
-    if (b->run_blocks > 0) join_gate(b->dev, &b->run_owner, false);
+    if (b->run_blocks > 0) leave_gate(b->dev, &b->run_owner);
     free_staging(b->run_staging);
     if (b->run_args_dev) (void)hipFree(b->run_args_dev);
     if (b->run_tiles_dev) (void)hipFree(b->run_tiles_dev);

@@ -182,20 +182,24 @@ constexpr uint32_t kRunWait = 1000000000; // 10 s (100 MHz counter): a wait with
 // the blocks wanted for each that runs after a launch that was called off.
 constexpr uint32_t kRunStart = 5000000, kRunAgain = 10000;
 
-// counters of the launches of a context
+// Counters of the launches of a context, in its workspace.
 struct RunSync {
     // low half: blocks that have started, over all launches, and kRunOff once this
     // launch is called off; high half: the blocks that had started by then
     uint64_t start;
     uint32_t start0;    // the low half before this launch
     uint32_t left;      // blocks that have left a launch that was called off
-    uint32_t tag0;      // tag of the last step done so
     uint32_t wait;      // longest wait within a run, 100 MHz ticks (0: kRunWait)
     uint32_t patience;  // 1 + kRunAgain after a launch that was called off, 0 after another
 };
+// After a launch that ends beyond this many blocks the count begins again.
+constexpr uint32_t kRunStartMax = 0x40000000u;
+__host__ __device__ inline uint32_t run_start_after(uint32_t start0, uint32_t blocks) {
+    return start0 + blocks > kRunStartMax ? 0u : start0 + blocks;
+}
 
-// Exchange areas in the fit's workspace: 64-bit words of 32 data and 32 tag
-// bits (m2m_run.h).
+// Exchange areas of a run, in memory of its stream: 64-bit words of 32 data and 32
+// tag bits (m2m_run.h).
 struct RunArgs {
     int32_t keep_at, keep_bytes;  // LDS offset and size of the kept kernels (0: not kept)
     int32_t n_jobs, n_cell_jobs;  // ceil(J / kRunCols), ceil(C / kRunCols)
@@ -213,9 +217,9 @@ __host__ __device__ inline int run_smooth_at(const RunArgs& a) {
 }
 
 // What one launch does: n_steps steps with the force of change on or off (a fit
-// of a batch: as many of them as it has left, with its own setting). known:
-// start0 and tag0 are the counters' values before the launch, else the
-// kernel reads them.
+// of a batch: as many of them as it has left, with its own setting), their tags
+// from tag0 + 1. known: start0 is the counter's value before the launch, else the
+// kernel reads it.
 struct RunCall {
     int32_t n_steps, correct, known;
     uint32_t start0, tag0;
@@ -260,11 +264,11 @@ hipError_t launch_run_smooth_f32(int block, int kin, const FitDev& fd, const Run
 hipError_t launch_run_smooth_f64(int block, int kin, const FitDev& fd, const RunArgs& ra, int blocks,
                                  size_t lds, const RunCall& call, hipStream_t s, hipEvent_t done);
 hipError_t launch_runs_f32(int block, int kin, const FitDev* fits, const RunArgs* ras,
-                           const RunTile* tiles, int blocks, size_t lds, int n_steps, hipStream_t s,
-                           hipEvent_t done);
+                           const RunTile* tiles, int blocks, size_t lds, int n_steps, uint32_t tag0,
+                           hipStream_t s, hipEvent_t done);
 hipError_t launch_runs_f64(int block, int kin, const FitDev* fits, const RunArgs* ras,
-                           const RunTile* tiles, int blocks, size_t lds, int n_steps, hipStream_t s,
-                           hipEvent_t done);
+                           const RunTile* tiles, int blocks, size_t lds, int n_steps, uint32_t tag0,
+                           hipStream_t s, hipEvent_t done);
 
 // ---- launchers (m2m_kernels.hip) ------------------------------------------
 // kin: kinematic kind of every fit in the launch, from kin_class()

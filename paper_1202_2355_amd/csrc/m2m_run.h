@@ -31,7 +31,7 @@ __device__ __forceinline__ int thread_here() {
 // agent-scope atomics (which bypass the caches that are not shared). A reader
 // waits for the tag, so no word needs an order to any other and no fence is
 // taken: an agent-scope release would write back an L2 full of particles.
-// The tags of a context never repeat (the host counts them).
+// The tags of a stream's area never repeat (the host counts them).
 //
 // Measured between 256 blocks of 1024 threads without particles: 3.6 us a
 // step for 160 columns this way (owners of 16 neighbouring columns, so that a
@@ -167,8 +167,9 @@ __device__ __forceinline__ bool leave_run(G<RunSync> s, uint32_t n) {
 // the counters after a launch of n_steps steps whose blocks have all left
 __device__ __forceinline__ void ready_again(G<RunSync> s, G<FitState> st, uint32_t start0, uint32_t n,
                                             int32_t left0, int32_t n_steps) {
-    s->start = (uint64_t)(start0 + n);
-    s->start0 = start0 + n;
+    const uint32_t next = run_start_after(start0, n);
+    s->start = next;
+    s->start0 = next;
     s->left = 0u;
     s->patience = 1u + kRunAgain;
     st->steps_left = left0 - n_steps;
@@ -516,7 +517,7 @@ struct RunParams {
 // wave + NW, ..., so that every compute unit gets the same number of waves to
 // within one (blocks of 1024 consecutive particles left 300 007 FP64 particles
 // on 147 compute units for two rounds, or on 37 of 256 for the second).
-// KNOWN: the launch's start0 and tag0 come with the call; OWN: a fit of a
+// KNOWN: the launch's start0 comes with the call; OWN: a fit of a
 // batch, with its own steps left and setting (both at compile time: as branches
 // at the start of the kernel they cost a launch of one step 0.6-0.9 of 12.4 us).
 // SMOOTH: the priors are smoothed at every refresh.
@@ -546,7 +547,7 @@ __device__ __forceinline__ void run_fit(const FitDev& fd, const RunArgs& ra, int
         if (n_steps <= 0) return;  // uniform: the fit is idle
     }
     const uint32_t start0 = KNOWN ? call.start0 : sync->start0;
-    const uint32_t tag0 = KNOWN ? call.tag0 : sync->tag0;
+    const uint32_t tag0 = call.tag0;
     uint64_t came = 0;
     if (tid == 0) {
         came = __hip_atomic_fetch_add(&ra.sync->start, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -811,9 +812,10 @@ __device__ __forceinline__ void run_fit(const FitDev& fd, const RunArgs& ra, int
         se->correct = correct ? 1 : 0;
         se->assign_pending = assign ? 1 : 0;
         const G<RunSync> sy = gmem(la.ra->sync);
-        sy->tag0 = tag0 + (uint32_t)n_steps;
         if (group[2] == 0) {
-            sy->start0 = start0 + n_blocks;
+            const uint32_t next = run_start_after(start0, n_blocks);
+            if (next == 0u) sy->start = 0u;
+            sy->start0 = next;
             sy->patience = 0u;
             se->steps_left = OWN ? se->steps_left - n_steps : 0;
         }
@@ -833,10 +835,11 @@ __global__ __launch_bounds__(BLOCK) void k_run(const RunParams P) {
 template <typename T, int BLOCK, int KIN>
 __global__ __launch_bounds__(BLOCK) void k_runs(const FitDev* __restrict__ fits,
                                                 const RunArgs* __restrict__ ras,
-                                                const RunTile* __restrict__ tiles, int32_t n_steps) {
+                                                const RunTile* __restrict__ tiles, int32_t n_steps,
+                                                uint32_t tag0) {
     const RunTile t = tiles[blockIdx.x];
     run_fit<T, BLOCK, KIN, false, true, false>(
-        fits[t.fit], ras[t.fit], t.b, (uint32_t)t.nb, RunCall{n_steps, 1, 0, 0u, 0u}, [=] {
+        fits[t.fit], ras[t.fit], t.b, (uint32_t)t.nb, RunCall{n_steps, 1, 0, 0u, tag0}, [=] {
             // the index, not the tables' addresses: these stay known as read only
             int f = t.fit;
             asm volatile("" : "+s"(f));
@@ -887,10 +890,11 @@ hipError_t launch_run_t(int kin, const FitDev& fd, const RunArgs& ra, int blocks
 
 template <typename T, int BLOCK>
 hipError_t launch_runs_t(int kin, const FitDev* fits, const RunArgs* ras, const RunTile* tiles,
-                         int blocks, size_t lds, int n_steps, hipStream_t s, hipEvent_t done) {
+                         int blocks, size_t lds, int n_steps, uint32_t tag0, hipStream_t s,
+                         hipEvent_t done) {
     return with_kin(kin, [&](auto K) {
         launch_blocks(k_runs<T, BLOCK, decltype(K)::value>, blocks, BLOCK, lds, s, done, fits, ras, tiles,
-                      n_steps);
+                      n_steps, tag0);
     });
 }
 

@@ -10,9 +10,9 @@ hipError_t launch_run_f64(int block, int kin, const FitDev& fd, const RunArgs& r
 }
 
 hipError_t launch_runs_f64(int block, int kin, const FitDev* fits, const RunArgs* ras,
-                           const RunTile* tiles, int blocks, size_t lds, int n_steps, hipStream_t s,
-                           hipEvent_t done) {
-    if (block == 512) return launch_runs_t<double, 512>(kin, fits, ras, tiles, blocks, lds, n_steps, s, done);
+                           const RunTile* tiles, int blocks, size_t lds, int n_steps, uint32_t tag0,
+                           hipStream_t s, hipEvent_t done) {
+    if (block == 512) return launch_runs_t<double, 512>(kin, fits, ras, tiles, blocks, lds, n_steps, tag0, s, done);
     return hipErrorInvalidValue;
 }
 

@@ -16,9 +16,9 @@ torch = pytest.importorskip("torch")
 
 # byte offset of the error bits in the workspace (FitState comes first)
 ERROR_AT = 28
-# in the counters of a fit's launches: blocks started, longest wait within a run,
-# patience with blocks that do not start
-START, WAIT, PATIENCE = 0, 20, 24
+# in the counters of a fit's launches: blocks started, the same before the next
+# launch, longest wait within a run, patience with blocks that do not start
+START, START0, WAIT, PATIENCE = 0, 8, 16, 20
 
 
 @pytest.fixture(scope="module")
@@ -325,3 +325,81 @@ def test_a_stream_with_few_compute_units(oracle, Fit):
         a.close()
         b.close()
     torch.cuda.synchronize()
+
+
+def test_the_tags_of_a_stream_come_round(oracle, Fit):
+    """Two fits on one stream take 4200 steps each, one after the other, in calls
+    that refresh the priors: the first round of tags ends within the second."""
+    _say("tags")
+    st = torch.cuda.Stream()
+    a, b = (_made(oracle, Fit, "v2", "f64", 3001, stream=st) for _ in range(2))
+    for f in (a, b):
+        for _ in range(20):
+            f.step(210)
+    np.testing.assert_allclose(b.chi2_history(), a.chi2_history(), rtol=1e-8)
+    a.close()
+    b.close()
+
+
+def test_the_count_of_blocks_begins_again(oracle, Fit):
+    """The count of blocks started, set near its end from the host (a fit with
+    smoothed priors reads it on the device), and one launch more."""
+    _say("count of blocks")
+    a, b = (_smoothed(oracle, Fit, "gh", "f32", 20_011, True) for _ in range(2))
+    for f in (a, b):
+        f.step(3)
+    blocks = int(_sync(b, START)[0])
+    last = (1 << 30) - blocks
+    for at in (START, START0):
+        _sync(b, at).fill_(last)
+    for f in (a, b):
+        f.step(5)
+    assert int(_sync(b, START)[0]) == int(_sync(b, START0)[0]) == 1 << 30
+    for k in range(1, 3):
+        for f in (a, b):
+            f.step(4)
+        assert int(_sync(b, START)[0]) == int(_sync(b, START0)[0]) == (k - 1) * blocks
+    _same(a, b, "f32")
+    a.close()
+    b.close()
+
+
+def test_exchange_memory_is_not_in_the_workspace():
+    """The workspace of a fit that steps by runs has the counters of its launches
+    more than that of one that does not (a refresh on every step)."""
+    from paper_1202_2355_amd import _abi as A
+    for kin in ("v2", "gh", "losvd"):
+        wl = _workload(kin, 4)
+        for n in (1, 4001, 1_000_000):
+            for dtype in ("f32", "f64"):
+                more = (A.m2m_workspace_bytes(wl.layout, wl.params, n, dtype)
+                        - A.m2m_workspace_bytes(wl.layout, dict(wl.params, prior_every=1), n, dtype))
+                assert 0 < more <= 256, (kin, n, dtype)
+
+
+def test_batches_and_fits_share_a_stream(oracle, Fit):
+    """A batch, then a larger fit on the batch's stream (its exchange memory does
+    not hold the fit's), then the batch again; another stream takes up memory that
+    a first one has left."""
+    from paper_1202_2355_amd.batch import Batch
+    for kin, dtype, small, large in (("gh", "f32", 20_011, 262_147), ("losvd", "f64", 3001, 150_001)):
+        _say("one stream", kin, dtype)
+        for _ in range(2):
+            st = torch.cuda.Stream()
+            ref = [_made(oracle, Fit, kin, dtype, n) for n in (small, small + 7, large)]
+            fits = [_made(oracle, Fit, kin, dtype, n, stream=st) for n in (small, small + 7, large)]
+            b = Batch(max_fits=2, stream=st)
+            for f in fits[:2]:
+                assert b.admit(f, 12)
+            for k in range(3):
+                b.run(4)
+                fits[2].step(3 + k)
+                for r in ref[:2]:
+                    r.step(4)
+                ref[2].step(3 + k)
+            b.poll()
+            b.close()
+            for f, r in zip(fits, ref):
+                _same(r, f, dtype)
+                f.close()
+                r.close()
