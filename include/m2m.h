@@ -224,7 +224,12 @@ typedef struct {
 /* Number of observables J of a layout (0 if the layout is invalid). */
 int32_t m2m_num_observables(const m2m_obs_layout* layout);
 
-/* Bytes of device workspace a context needs for n particles. */
+/* Bytes of device workspace a context needs for n particles. Besides it the library
+ * may hold, on each stream on which fits step many steps per launch (see
+ * m2m_step), one piece of exchange memory as large as its largest launch needs (at
+ * most 52 MiB for a fit), and at most 16 MiB of tile rows for a small fit that steps
+ * alone one launch per step; these come from few pieces that are kept while any
+ * context exists. */
 size_t m2m_workspace_bytes(const m2m_obs_layout* layout, const m2m_params* params, int64_t n,
                            int32_t dtype);
 
@@ -456,7 +461,9 @@ int32_t m2m_get_interleave(void);
  * enqueued before (they may still read it), and m2m_destroy waits for them. */
 
 /* hbm_budget: bytes of particle state plus workspace the batch may hold
- * (0 = no limit). max_fits >= 1. */
+ * (0 = no limit). Rows that let few fits fill the GPU, and the exchange memory of
+ * launches of many steps, are used only while they fit the budget too.
+ * max_fits >= 1. */
 m2m_status m2m_batch_create(int32_t max_fits, size_t hbm_budget, void* hip_stream,
                             m2m_batch** out);
 /* Add a fit (targets set) to run n_steps correction steps. ENOMEM when its
@@ -490,7 +497,7 @@ m2m_status m2m_batch_poll_lagged(m2m_batch* b, m2m_ctx** done, int32_t max_done,
 m2m_status m2m_batch_profile(m2m_batch* b, int32_t n_steps, double* ms_step, double* ms_finalize);
 /* Particles of the admitted fits that still have steps left. Synchronizes. */
 int64_t m2m_batch_particles(m2m_batch* b);
-/* Bytes of budget in use. */
+/* Bytes of budget in use: particle state plus workspace of the admitted fits. */
 size_t m2m_batch_footprint(const m2m_batch* b);
 /* Remove a fit before it finished (cancellation); synchronizes. */
 m2m_status m2m_batch_cancel(m2m_batch* b, m2m_ctx* fit);

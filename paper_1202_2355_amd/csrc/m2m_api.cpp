@@ -305,7 +305,7 @@ struct WsLayout {
     size_t st, fd, tiles, jobs, redge2, rmesh, Redge2, vedge, Vp, isp, rp, ucell, lctab, cidx;
     size_t cdata, gprior, scf_rho, scf_sum, scf_tab, sm_basis;
     size_t Y, sigma, yv, ytil, delta, obs, hist, chi2p, partials, total;
-    size_t tail, otab;  // after what batched steps use: GH tables of an observation
+    size_t otab;        // GH tables of an observation
     bool run;           // counters of the run kernel's launches, last:
     size_t run_sync;
     int seg_cap, seg_lean, row_len, nbj, ncj, npj, J, C, P;  // P: interval sums of the expansion
@@ -328,12 +328,15 @@ int seg_cap_lean(int64_t n, int row_len) {
     return (int)cap;
 }
 
-// Most tiles of a fit. The rows of a fit of many observables and prior cells are
-// long (54 KB for the 2610 + 2 x 2048 of the LOSVD layout), and 16 bytes per particle
-// let 1e5 particles have 29 of them, so 29 of 256 compute units. A fit may therefore
-// have up to 160 tiles of at least 1024 particles, and where a particle costs much
-// (FP64 state, spherical harmonics, self-consistent potential) 256 of at least 256, in
-// 16 MiB of rows.
+// Most tiles of a fit with rows outside its workspace. The rows of a fit of many
+// observables and prior cells are long (54 KB for the 2610 + 2 x 2048 of the LOSVD
+// layout), and 16 bytes per particle let 1e5 particles have 29 of them, so 29 of 256
+// compute units. A fit that steps alone may therefore have up to 160 tiles of at
+// least 1024 particles, and where a particle costs much (FP64 state, spherical
+// harmonics, self-consistent potential) 256 of at least 256, in 16 MiB of rows that the
+// library takes when it first steps alone and gives back when it is closed or
+// joins a batch (ensure_wide): a workspace with them would be up to eight times as
+// large, and a budget of a batch would hold as many fewer fits.
 // Measured us a step, before and with tiles of at least 1024, 512, 256, 128:
 // LOSVD FP32 2e4 particles 18.2 14.8 14.6 14.5 15.4, 1e5 17.7 15.5 16.0 17.3 17.5;
 // FP64 2e4 44.3 25.3 21.4 19.8 20.0; l = 4 harmonics with Gauss-Hermite 2e4 35.7
@@ -411,7 +414,7 @@ WsLayout plan(const m2m_obs_layout& L, const m2m_params& P, int64_t n, bool f64,
     };
     w.st = take(sizeof(FitState));
     w.fd = take(sizeof(FitDev));
-    w.tiles = take(sizeof(Tile) * (size_t)w.seg_cap);
+    w.tiles = take(sizeof(Tile) * (size_t)w.seg_lean);
     w.jobs = take(sizeof(FinJob) * (size_t)(w.nbj + w.ncj + w.npj));
     const int nR = L.kin == M2M_KIN_NONE ? 0 : L.n_R;
     const int nv = L.kin == M2M_KIN_LOSVD ? L.n_v : 0;
@@ -432,7 +435,7 @@ WsLayout plan(const m2m_obs_layout& L, const m2m_params& P, int64_t n, bool f64,
     w.obs = take(8 * (size_t)w.J);
     w.hist = take(8 * (size_t)kHistCap);
     w.chi2p = take(8 * (size_t)w.nbj);
-    w.partials = take(8 * (size_t)w.seg_cap * (size_t)w.row_len);
+    w.partials = take(8 * (size_t)w.seg_lean * (size_t)w.row_len);
     w.cidx = take(cell_index ? 2 * (size_t)n : 0);
     w.cdata = take(8 * (size_t)w.C);
     w.gprior = take(8 * (size_t)w.C);
@@ -441,7 +444,6 @@ WsLayout plan(const m2m_obs_layout& L, const m2m_params& P, int64_t n, bool f64,
     w.scf_tab = take(8 * (size_t)std::max(w.P, 1));
     // eigendecomposition of the smoothing penalty (both L_z halves share it)
     w.sm_basis = take(P.smooth ? 8 * smooth_basis_len(P.n_E, P.n_x) : 8);
-    w.tail = o;
     w.otab = take(cell_index && L.kin == M2M_KIN_GH ? w.rp - w.Vp : 0);
     w.run = cell_index && run_kind(L, P, n);
     if (w.run) w.run_sync = take(sizeof(RunSync));
@@ -599,6 +601,10 @@ struct m2m_ctx {
     Tile* tiles = nullptr;
     FinJob* jobs = nullptr;
     int n_tiles = 0;
+    // more tiles, and rows for them outside the workspace while it steps alone
+    int wide_tiles = 0;
+    double* wide = nullptr;
+    size_t wide_bytes = 0;
     int n_jobs = 0;
     size_t lds = 0;
     int block = 256, kin = 0;
@@ -824,53 +830,10 @@ m2m_status check_error(m2m_ctx* c) {
     return error_status(c, s);
 }
 
-// Rebuild the self-consistent potential from the current state: the step
-// kernel deposits the interval sums only, the finalize reduces them and
-// writes the node table.
-m2m_status refresh_potential(m2m_ctx* c) {
-    M2M_HIP(c, launch_step1(c->f64, c->acc64, c->block, c->kin, c->fd, c->n_tiles, c->lds,
-                           kModePot, c->stream));
-    M2M_HIP(c, launch_finalize1(c->f64, c->fd, c->n_tiles, kModePot, c->stream));
-    return M2M_OK;
-}
-
-// One M2M step: the step kernel over all tiles, then the finalize.
-hipError_t launch_one_step(m2m_ctx* c, hipStream_t s) {
-    const int32_t il = c->il ? kModeInterleave | (c->back ? kModeBack : 0) : 0;
-    c->back = !c->back;
-    hipError_t e = launch_step1(c->f64, c->acc64, c->block, c->kin, c->fd, c->n_tiles, c->lds,
-                               kModeStep | (c->wt ? kModeWriteThrough : 0) | il, s);
-    if (e == hipSuccess) e = launch_finalize1(c->f64, c->fd, c->n_tiles, kModeStep, s);
-    return e;
-}
-
-// ---- run kernel -------------------------------------------------------------
 bool capturing(hipStream_t s) {
     hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
     return hipStreamIsCapturing(s, &st) != hipSuccess || st != hipStreamCaptureStatusNone;
 }
-
-// Steps by the run kernel, if the fit's kind has it and the stream is not being
-// captured. Beside a batch that keeps the GPU full (64 fits, streams on
-// hardware queues of their own) 64 steps of 4001 / 10^6 particles took 0.5 /
-// 1.3 ms this way and 4.0 / 6.2 ms by one launch per step.
-bool use_run(const m2m_ctx* c, int32_t n_steps) {
-    return c->run && (c->w.J <= kRunShortJ || n_steps > 2) && !capturing(c->stream);
-}
-
-// Compute units that a stream may use: all, or those of its mask. A run of more
-// blocks would be called off at every launch (50 ms, then 0.1 ms and more).
-int stream_cus(hipStream_t s) {
-    uint32_t mask[32] = {};
-    int n = 0;
-    if (hipExtStreamGetCUMask(s, 32, mask) == hipSuccess)
-        for (uint32_t m : mask) n += __builtin_popcount(m);
-    else
-        (void)hipGetLastError();
-    return n > 0 ? std::min(n, n_cus()) : n_cus();
-}
-
-bool own_order(const RunOwner& a, const RunOwner& b) { return a.area == b.area; }
 
 // Another thread may be capturing: allocations of this one are none of its business.
 struct CaptureRelaxed {
@@ -881,7 +844,7 @@ struct CaptureRelaxed {
 
 // Device memory of at least `bytes`: what a stream that is gone has left, or new. At
 // most kIdleBlocks are left, and none once the last context is gone.
-constexpr size_t kIdleBlocks = 4;
+constexpr size_t kIdleBlocks = 8;
 unsigned char* take_memory(int dev, RunGate& g, size_t bytes, size_t* got) {
     auto best = g.idle.end();
     for (auto it = g.idle.begin(); it != g.idle.end(); ++it)
@@ -922,6 +885,92 @@ void free_idle_memory() {
         g.idle.clear();
     }
 }
+
+// The rows of one step and finalize of a fit alone: those outside its workspace if
+// it has them. Not for a caller's graph, which may be replayed when they are gone.
+struct Rows {
+    FitDev f;
+    int n;
+};
+Rows rows_of(const m2m_ctx* c, bool wide) {
+    Rows r{c->fd, c->n_tiles};
+    if (wide && c->wide) {
+        r.f.partials = c->wide;
+        r.n = c->wide_tiles;
+    }
+    return r;
+}
+
+void ensure_wide(m2m_ctx* c) {
+    if (c->wide || c->wide_tiles <= c->n_tiles || c->dev < 0 || c->dev >= kRunDevices) return;
+    RunGate& g = g_run_gate[c->dev];
+    std::lock_guard<std::mutex> lock(g.mu);
+    c->wide = reinterpret_cast<double*>(
+        take_memory(c->dev, g, 8 * (size_t)c->wide_tiles * (size_t)c->w.row_len, &c->wide_bytes));
+}
+
+// gives them back; no work of the fit is in flight, and (drop_wide) no graph of
+// its steps is used again
+void give_wide(m2m_ctx* c) {
+    if (!c->wide) return;
+    RunGate& g = g_run_gate[c->dev];
+    std::lock_guard<std::mutex> lock(g.mu);
+    leave_memory(g, reinterpret_cast<unsigned char*>(c->wide), c->wide_bytes);
+    c->wide = nullptr;
+}
+
+void drop_wide(m2m_ctx* c) {
+    if (!c->wide) return;
+    for (hipGraphExec_t* x : {&c->graph, &c->graph_prof}) {
+        if (*x) (void)hipGraphExecDestroy(*x);
+        *x = nullptr;
+    }
+    give_wide(c);
+}
+
+// Rebuild the self-consistent potential from the current state: the step
+// kernel deposits the interval sums only, the finalize reduces them and
+// writes the node table.
+m2m_status refresh_potential(m2m_ctx* c) {
+    const Rows r = rows_of(c, !capturing(c->stream));
+    M2M_HIP(c, launch_step1(c->f64, c->acc64, c->block, c->kin, r.f, r.n, c->lds, kModePot, c->stream));
+    M2M_HIP(c, launch_finalize1(c->f64, r.f, r.n, kModePot, c->stream));
+    return M2M_OK;
+}
+
+// One M2M step: the step kernel over all tiles, then the finalize.
+hipError_t launch_one_step(m2m_ctx* c, hipStream_t s, bool wide) {
+    const Rows r = rows_of(c, wide);
+    const int32_t il = c->il ? kModeInterleave | (c->back ? kModeBack : 0) : 0;
+    c->back = !c->back;
+    hipError_t e = launch_step1(c->f64, c->acc64, c->block, c->kin, r.f, r.n, c->lds,
+                               kModeStep | (c->wt ? kModeWriteThrough : 0) | il, s);
+    if (e == hipSuccess) e = launch_finalize1(c->f64, r.f, r.n, kModeStep, s);
+    return e;
+}
+
+// ---- run kernel -------------------------------------------------------------
+// Steps by the run kernel, if the fit's kind has it and the stream is not being
+// captured. Beside a batch that keeps the GPU full (64 fits, streams on
+// hardware queues of their own) 64 steps of 4001 / 10^6 particles took 0.5 /
+// 1.3 ms this way and 4.0 / 6.2 ms by one launch per step.
+bool use_run(const m2m_ctx* c, int32_t n_steps) {
+    return c->run && (c->w.J <= kRunShortJ || n_steps > 2) && !capturing(c->stream);
+}
+
+// Compute units that a stream may use: all, or those of its mask. A run of more
+// blocks would be called off at every launch (50 ms, then 0.1 ms and more).
+int stream_cus(hipStream_t s) {
+    uint32_t mask[32] = {};
+    int n = 0;
+    if (hipExtStreamGetCUMask(s, 32, mask) == hipSuccess)
+        for (uint32_t m : mask) n += __builtin_popcount(m);
+    else
+        (void)hipGetLastError();
+    return n > 0 ? std::min(n, n_cus()) : n_cus();
+}
+
+bool own_order(const RunOwner& a, const RunOwner& b) { return a.area == b.area; }
 
 // An owner of runs on the stream comes or goes (its runs have ended).
 void join_gate(int dev, RunOwner* o, hipStream_t stream) {
@@ -1109,7 +1158,7 @@ m2m_status ensure_graph(m2m_ctx* c) {
     if (!c->cap) M2M_HIP(c, hipStreamCreateWithFlags(&c->cap, hipStreamNonBlocking));
     const hipError_t e = capture_steps(
         c->cap, kGraphSteps,
-        [c](hipStream_t s) { return launch_one_step(c, s); }, &c->graph, c->stream);
+        [c](hipStream_t s) { return launch_one_step(c, s, true); }, &c->graph, c->stream);
     if (e != hipSuccess) return hip_fail(c, e, "step graph");
     return M2M_OK;
 }
@@ -1123,10 +1172,10 @@ m2m_status ensure_prof_graph(m2m_ctx* c) {
     const hipError_t e = capture_steps(
         c->cap, kGraphSteps,
         [c](hipStream_t s) {
-            hipError_t r = launch_one_step(c, s);
-            if (r == hipSuccess)
-                r = launch_finalize1(c->f64, c->fd, c->n_tiles, kModeObserve, s);
-            return r;
+            const Rows r = rows_of(c, true);
+            hipError_t e = launch_one_step(c, s, true);
+            if (e == hipSuccess) e = launch_finalize1(c->f64, r.f, r.n, kModeObserve, s);
+            return e;
         },
         &c->graph_prof, c->stream);
     if (e != hipSuccess) return hip_fail(c, e, "profile graph");
@@ -1414,7 +1463,8 @@ m2m_status m2m_create(const m2m_potential* pot, const m2m_obs_layout* layout,
 
     // ---- tiles of this fit alone
     const int target = std::max(1, g_tiles_per_cu * n_cus());
-    const int count = std::max(1, std::min(w.seg_cap, target));
+    const int count = std::max(1, std::min(w.seg_lean, target));
+    c->wide_tiles = std::max(1, std::min(w.seg_cap, target));
     std::vector<Tile> tl;
     split_tiles(n, count, 0, 0, tl);
     std::vector<FinJob> jb;
@@ -1460,9 +1510,9 @@ m2m_status m2m_set_targets(m2m_ctx* c, int32_t J, const double* Y, const double*
     if ((s = upload_gh(c, V, S)) != M2M_OK) return s;
     if (!c->ytil_init) {
         if (c->par.scf_nr > 0 && (s = refresh_potential(c)) != M2M_OK) return s;
-        M2M_HIP(c, launch_step1(c->f64, c->acc64, c->block, c->kin, c->fd, c->n_tiles, c->lds,
-                               kModeInit, c->stream));
-        M2M_HIP(c, launch_finalize1(c->f64, c->fd, c->n_tiles, kModeInit, c->stream));
+        const Rows r = rows_of(c, true);
+        M2M_HIP(c, launch_step1(c->f64, c->acc64, c->block, c->kin, r.f, r.n, c->lds, kModeInit, c->stream));
+        M2M_HIP(c, launch_finalize1(c->f64, r.f, r.n, kModeInit, c->stream));
         c->ytil_init = true;
     } else {
         M2M_HIP(c, launch_residuals(c->f64, c->fd_dev, c->stream));
@@ -1489,8 +1539,10 @@ m2m_status m2m_step(m2m_ctx* c, int32_t n_steps, int32_t correct) {
         if (e != hipErrorOutOfMemory) return hip_fail(c, e, "run of steps");
         // the remaining steps one launch each
     }
+    const bool captured = capturing(c->stream);
+    if (!captured) ensure_wide(c);
     M2M_HIP(c, launch_poke(c->st, n_steps, correct ? 1 : 0, c->stream));
-    const int full = n_steps / kGraphSteps, rem = n_steps % kGraphSteps;
+    const int full = captured && c->wide ? 0 : n_steps / kGraphSteps, rem = n_steps - full * kGraphSteps;
     if (full > 0) {
         m2m_status s = ensure_graph(c);
         if (s != M2M_OK) return s;
@@ -1498,7 +1550,7 @@ m2m_status m2m_step(m2m_ctx* c, int32_t n_steps, int32_t correct) {
     }
     // the rest as direct launches: a graph launch has a fixed cost of
     // several kernel launches
-    for (int k = 0; k < rem; ++k) M2M_HIP(c, launch_one_step(c, c->stream));
+    for (int k = 0; k < rem; ++k) M2M_HIP(c, launch_one_step(c, c->stream, !captured));
     return M2M_OK;
 }
 
@@ -1528,9 +1580,9 @@ m2m_status m2m_update_priors(m2m_ctx* c) {
     if (m2m_status w_ = after_batch(c); w_ != M2M_OK) return w_;
     if (c->par.entropy != M2M_S_MPR) return fail(c, M2M_EINVAL, "moving priors need M2M_S_MPR");
     c->may_assign = true;
-    M2M_HIP(c, launch_step1(c->f64, c->acc64, c->block, c->kin, c->fd, c->n_tiles, c->lds,
-                           kModeCells, c->stream));
-    M2M_HIP(c, launch_finalize1(c->f64, c->fd, c->n_tiles, kModeCells, c->stream));
+    const Rows r = rows_of(c, !capturing(c->stream));
+    M2M_HIP(c, launch_step1(c->f64, c->acc64, c->block, c->kin, r.f, r.n, c->lds, kModeCells, c->stream));
+    M2M_HIP(c, launch_finalize1(c->f64, r.f, r.n, kModeCells, c->stream));
     M2M_HIP(c, launch_assign(c->f64, c->fd_dev, c->tiles, c->n_tiles, c->stream));
     return M2M_OK;
 }
@@ -1605,7 +1657,16 @@ m2m_status m2m_observe(m2m_ctx* c, const double* V_p, const double* sigma_p, dou
     Pinned pin(obs + tab);
     std::vector<unsigned char> own(pin.p ? 0 : tab);
     unsigned char* t = pin.p ? static_cast<unsigned char*>(pin.p) + obs : own.data();
-    FitDev f = c->fd;
+    // rows outside the workspace for the length of the call
+    const bool lend = !c->wide && !capturing(c->stream);
+    if (lend) ensure_wide(c);
+    auto [f, n_tiles] = rows_of(c, !capturing(c->stream));
+    struct Lent {
+        m2m_ctx* c;
+        ~Lent() {
+            if (c) give_wide(c);
+        }
+    } lent{lend ? c : nullptr};
     if (pin.p) f.obs_out = static_cast<double*>(pin.p);
     if (tmp) {
         const int nR = c->fd.n_R;
@@ -1627,9 +1688,8 @@ m2m_status m2m_observe(m2m_ctx* c, const double* V_p, const double* sigma_p, dou
     }
     hipError_t e = tmp ? hipMemcpyAsync(f.Vp, t, tab, hipMemcpyHostToDevice, c->stream) : hipSuccess;
     if (e == hipSuccess)
-        e = launch_step1(c->f64, c->acc64, c->block, c->kin, f, c->n_tiles, c->lds, kModeObserve,
-                         c->stream);
-    if (e == hipSuccess) e = launch_finalize1(c->f64, f, c->n_tiles, kModeObserve, c->stream);
+        e = launch_step1(c->f64, c->acc64, c->block, c->kin, f, n_tiles, c->lds, kModeObserve, c->stream);
+    if (e == hipSuccess) e = launch_finalize1(c->f64, f, n_tiles, kModeObserve, c->stream);
     if (e == hipSuccess && !pin.p)
         e = hipMemcpyAsync(y, f.obs_out, obs, hipMemcpyDeviceToHost, c->stream);
     // also after an error: what was queued uses the tables and the results' place
@@ -1759,6 +1819,7 @@ m2m_status m2m_profile_step(m2m_ctx* c, int32_t n_steps, int32_t correct, double
     if (m2m_status w_ = after_batch(c); w_ != M2M_OK) return w_;
     if (!c->targets) return fail(c, M2M_ESTATE, "set targets first");
     c->may_assign = true;
+    ensure_wide(c);
     m2m_status st = ensure_graph(c);
     if (st == M2M_OK) st = ensure_prof_graph(c);
     if (st != M2M_OK) return st;
@@ -1815,6 +1876,7 @@ m2m_status m2m_destroy(m2m_ctx* c) {
         (void)hipEventDestroy(c->idle_ev);
     }
     if (c->own_ev) (void)hipEventDestroy(c->own_ev);
+    drop_wide(c);
     if (c->graph) (void)hipGraphExecDestroy(c->graph);
     if (c->graph_prof) (void)hipGraphExecDestroy(c->graph_prof);
     if (c->cap) (void)hipStreamDestroy(c->cap);
@@ -1844,7 +1906,8 @@ struct LaunchSet {
     FitDev* fits_dev = nullptr;
     Tile* tiles_dev = nullptr;
     FinJob* jobs_dev = nullptr;
-    size_t cap_fits = 0, cap_tiles = 0, cap_jobs = 0;
+    double* rows_dev = nullptr;  // tile rows of fits that have more than their workspaces hold
+    size_t cap_fits = 0, cap_tiles = 0, cap_jobs = 0, cap_rows = 0;
     int n_tiles = 0, n_jobs = 0, n_fits = 0;
     bool whole = false;  // one whole-fit finalize job per fit (else column jobs)
     bool nt = false;     // the fits' state together exceeds kStreamMin (kModeStream)
@@ -1899,14 +1962,7 @@ struct m2m_batch {
 
 namespace {
 
-size_t footprint(const m2m_ctx* c) {
-    // without what no batched step needs (a run's exchange areas), and without
-    // the rows beyond 16 bytes per particle (at most 16 MiB)
-    const auto rows = [&](int cap) {
-        return align_up(8 * (size_t)cap * (size_t)c->w.row_len, 256) + align_up(sizeof(Tile) * (size_t)cap, 256);
-    };
-    return (size_t)c->n * 8 * (c->f64 ? 8 : 4) + c->w.tail - (rows(c->w.seg_cap) - rows(c->w.seg_lean));
-}
+size_t footprint(const m2m_ctx* c) { return (size_t)c->n * 8 * (c->f64 ? 8 : 4) + c->w.total; }
 
 hipError_t grow(void** p, size_t* cap, size_t need) {
     if (need <= *cap) return hipSuccess;
@@ -1994,11 +2050,38 @@ void free_set(LaunchSet& L) {
     if (L.fits_dev) (void)hipFree(L.fits_dev);
     if (L.tiles_dev) (void)hipFree(L.tiles_dev);
     if (L.jobs_dev) (void)hipFree(L.jobs_dev);
+    if (L.rows_dev) (void)hipFree(L.rows_dev);
+    L.rows_dev = nullptr;
+    L.cap_rows = 0;
     L.graph = nullptr;
     L.fits_dev = nullptr;
     L.tiles_dev = nullptr;
     L.jobs_dev = nullptr;
     L.cap_fits = L.cap_tiles = L.cap_jobs = 0;
+}
+
+// `need` bytes of tile rows for the set L (0: none). False, with no rows held, if
+// the budget or the device has no room for them.
+bool set_rows(m2m_batch* b, LaunchSet& L, size_t need) {
+    size_t others = 0;
+    for (const LaunchSet* x : {&b->all, &b->grp[0], &b->grp[1]})
+        if (x != &L) others += x->cap_rows;
+    const bool room = !b->budget || m2m_batch_footprint(b) + others + std::max(need, L.cap_rows) <= b->budget;
+    if (need <= L.cap_rows && room) return true;
+    // the runs enqueued so far may still use the rows held
+    if (L.rows_dev) (void)hipStreamSynchronize(b->stream);
+    if (L.rows_dev) (void)hipFree(L.rows_dev);
+    L.rows_dev = nullptr;
+    L.cap_rows = 0;
+    if (need == 0) return true;
+    if (b->budget && m2m_batch_footprint(b) + others + need > b->budget) return false;
+    if (hipMalloc(reinterpret_cast<void**>(&L.rows_dev), need) != hipSuccess) {
+        (void)hipGetLastError();
+        L.rows_dev = nullptr;
+        return false;
+    }
+    L.cap_rows = need;
+    return true;
 }
 
 // The tables of the fits `members` (indices into b->fits, in that order)
@@ -2028,9 +2111,10 @@ m2m_status fill_set(m2m_batch* b, LaunchSet& L, const std::vector<int>& members,
     // column jobs for every fit
     bool whole = members.size() >= kWholeFitMinFits;
     std::vector<int> cnts(members.size());
-    // tiles of a fit: lean rows, or where these leave compute units idle as many
-    // tiles as bring the set to five eighths of the units (a set shares them with
-    // another). Measured us a step of 3, 8, 12 LOSVD fits of 5e4 FP32 particles: lean
+    // tiles of a fit: those its workspace has rows for, or where these leave compute
+    // units idle as many tiles as bring the set to five eighths of the units (a set
+    // shares them with another), with rows of the set's own if the budget has room for
+    // them beside the fits. Measured us a step of 3, 8, 12 LOSVD fits of 5e4 FP32 particles: lean
     // rows 21.8 23.5 25.1, filled to 128 18.8 21.6 24.3, to 192 18.6 22.7 24.2; with
     // every tile of seg_cap 19.5 23.1 27.6, and 12 of 1.5e5 55 instead of 36.
     const auto tiles_of = [](const m2m_ctx* c, int64_t size, int cap) {
@@ -2040,16 +2124,34 @@ m2m_status fill_set(m2m_batch* b, LaunchSet& L, const std::vector<int>& members,
     for (int m : members) lean += tiles_of(b->fits[m], tile, b->fits[m]->w.seg_lean);
     const int fill = std::max(1, n_cus() * 5 / 8);
     const int64_t wide = std::max(tile, (ntot + fill - 1) / fill);
+    size_t rows = 0;
+    const auto row_bytes = [&](size_t f) {
+        const m2m_ctx* c = b->fits[members[f]];
+        return cnts[f] > c->w.seg_lean ? align_up(8 * (size_t)cnts[f] * (size_t)c->w.row_len, 256) : 0;
+    };
     for (size_t f = 0; f < members.size(); ++f) {
         m2m_ctx* c = b->fits[members[f]];
         cnts[f] = tiles_of(c, tile, c->w.seg_lean);
-        if (lean < fill) cnts[f] = std::max(cnts[f], tiles_of(c, wide, c->w.seg_cap));
+        if (lean < fill && !(&L == &b->all && b->n_groups > 1))
+            cnts[f] = std::max(cnts[f], tiles_of(c, wide, c->w.seg_cap));
+        rows += row_bytes(f);
+    }
+    if (!set_rows(b, L, rows))
+        for (size_t f = 0; f < members.size(); ++f)
+            cnts[f] = tiles_of(b->fits[members[f]], tile, b->fits[members[f]]->w.seg_lean);
+    rows = 0;
+    for (size_t f = 0; f < members.size(); ++f) {
+        m2m_ctx* c = b->fits[members[f]];
         if ((size_t)cnts[f] * (size_t)c->w.J * 8 > kWholeFitMaxBytes || c->w.nbj > kWholeFitMaxJobs)
             whole = false;
     }
     for (size_t f = 0; f < members.size(); ++f) {
         m2m_ctx* c = b->fits[members[f]];
         fd.push_back(c->fd);
+        if (const size_t r = row_bytes(f)) {
+            fd.back().partials = L.rows_dev + rows / 8;
+            rows += r;
+        }
         split_tiles(c->n, cnts[f], (int)f, 0, tl);
         if (whole)
             jb.push_back(FinJob{(int)f, kFinWholeFit, 0, cnts[f]});
@@ -2146,6 +2248,8 @@ m2m_status run_fits(m2m_batch* b) {
             ra.push_back(a);
         }
         if (pass == 0) {
+            const size_t rows = b->all.cap_rows + b->grp[0].cap_rows + b->grp[1].cap_rows;
+            if (b->budget && m2m_batch_footprint(b) + rows + b->run_bytes > b->budget) return M2M_OK;
             RunGate& g = g_run_gate[b->dev];
             std::lock_guard<std::mutex> lock(g.mu);
             mem = exchange_memory(b->dev, g, b->run_owner.area, b->run_bytes);
@@ -2344,6 +2448,11 @@ m2m_status m2m_batch_admit(m2m_batch* b, m2m_ctx* c, int32_t n_steps) {
     m2m_status s = after_batch(c);
     if (s != M2M_OK) return s;
     if ((s = flush_assign(c)) != M2M_OK) return s;
+    if (c->wide) {
+        // the budget counts the workspace, so the fit keeps nothing else
+        if ((s = sync(c)) != M2M_OK) return s;
+        drop_wide(c);
+    }
     // the batch stream waits for the fit's own work (its creation, targets,
     // steps) on the device; the host does not wait
     if (!c->own_ev) M2M_HIP(c, hipEventCreateWithFlags(&c->own_ev, hipEventDisableTiming));

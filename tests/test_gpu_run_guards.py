@@ -403,3 +403,87 @@ def test_batches_and_fits_share_a_stream(oracle, Fit):
                 _same(r, f, dtype)
                 f.close()
                 r.close()
+
+
+def _alm(oracle, Fit, n, **kw):
+    wl = _workload("gh", 4)
+    wl = wl.with_(layout=dict(wl.layout, dens="alm", l_max=2, n_r=20))
+    parts = cast(wl.initial_particles(n=n, seed=n % 97), "f32")
+    f = Fit(wl.potential, wl.layout, wl.params, parts, dtype="f32", **kw)
+    V, S = np.zeros(wl.layout["n_R"]), np.full(wl.layout["n_R"], 0.4)
+    y = f.observe(V, S)
+    f.set_targets(y, 0.05 * np.abs(y) + 1e-3 * np.abs(y).max(), V, S)
+    return f
+
+
+def test_a_batch_counts_state_and_workspace(oracle, Fit):
+    """The budget is the particle state and the workspace of the fits, to the byte,
+    also of fits that have stepped alone; with a budget for two fits exactly, the
+    batch steps them without memory of its own and the results are the same."""
+    from paper_1202_2355_amd import _abi as A
+    from paper_1202_2355_amd.batch import Batch
+    for made, n, dtype in ((lambda n: _made(oracle, Fit, "losvd", "f64", n), 5003, "f64"),
+                           (lambda n: _made(oracle, Fit, "gh", "f32", n), 40_009, "f32"),
+                           (lambda n: _alm(oracle, Fit, n), 5003, "f32")):
+        _say("budget", n, dtype)
+        fits = [made(n + k) for k in range(3)]
+        ref = [made(n + k) for k in range(2)]
+        for f in fits[:2] + ref:
+            f.step(3)
+        want = [(64 if dtype == "f64" else 32) * f.n + A.m2m_workspace_bytes(f.layout, f.params, f.n, dtype)
+                for f in fits]
+        for budget in (want[0] + want[1], 0):
+            b = Batch(max_fits=3, hbm_budget=budget)
+            assert b.admit(fits[0], 6) and b.footprint == want[0]
+            assert b.admit(fits[1], 6) and b.footprint == want[0] + want[1]
+            if budget:
+                assert not b.admit(fits[2], 6)
+            b.run(6)
+            b.poll()
+            b.close()
+            for f in ref:
+                f.step(6)
+        b = Batch(max_fits=3, hbm_budget=want[0] + want[1] - 1)
+        assert b.admit(fits[0], 6) and not b.admit(fits[1], 6)
+        b.cancel(fits[0])
+        b.close()
+        for f, r in zip(fits, ref):
+            _same(r, f, dtype)
+        for f in fits + ref:
+            f.close()
+
+
+def test_steps_in_a_graph_outlive_the_rows_of_a_fit_alone(oracle, Fit):
+    """Steps recorded into a caller's graph after eager steps (which take rows
+    outside the workspace), replayed when the fit has been in a batch."""
+    from paper_1202_2355_amd.batch import Batch
+    _say("graph and batch")
+    st = torch.cuda.Stream()
+    a, b = _alm(oracle, Fit, 20_011), _alm(oracle, Fit, 20_011, stream=st)
+    b.step(3)
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g, stream=st):
+        b.step(35)
+    a.step(3)
+    for _ in range(2):
+        q = Batch(max_fits=1, stream=st)
+        assert q.admit(b, 4)
+        q.run(4)
+        q.poll()
+        q.close()
+        with torch.cuda.stream(st):
+            g.replay()
+        torch.cuda.synchronize()
+        other = _alm(oracle, Fit, 20_011)  # takes up the rows that b has left
+        other.step(3)
+        with torch.cuda.stream(st):
+            g.replay()
+        b.step(1)
+        other.step(40)
+        a.step(4 + 35 + 35 + 1)
+        torch.cuda.synchronize()
+        _same(a, b, "f32")
+        other.close()
+    a.close()
+    b.close()
