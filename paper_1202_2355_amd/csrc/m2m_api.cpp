@@ -302,7 +302,7 @@ constexpr double kLzHalo1 = 3.68887945411394;  // ln 40: with the logarithmic ha
 
 // ---------------------------------------------------------------- layout ---
 struct WsLayout {
-    size_t st, fd, tiles, jobs, redge2, rmesh, Redge2, vedge, Vp, isp, rp, ucell, lctab, cidx;
+    size_t st, fd, redge2, rmesh, Redge2, vedge, Vp, isp, rp, ucell, lctab, cidx;
     size_t cdata, gprior, scf_rho, scf_sum, scf_tab, sm_basis;
     size_t Y, sigma, yv, ytil, delta, obs, hist, chi2p, partials, total;
     size_t otab;        // GH tables of an observation
@@ -414,8 +414,6 @@ WsLayout plan(const m2m_obs_layout& L, const m2m_params& P, int64_t n, bool f64,
     };
     w.st = take(sizeof(FitState));
     w.fd = take(sizeof(FitDev));
-    w.tiles = take(sizeof(Tile) * (size_t)w.seg_lean);
-    w.jobs = take(sizeof(FinJob) * (size_t)(w.nbj + w.ncj + w.npj));
     const int nR = L.kin == M2M_KIN_NONE ? 0 : L.n_R;
     const int nv = L.kin == M2M_KIN_LOSVD ? L.n_v : 0;
     w.redge2 = take(sz * (size_t)(L.n_r + 1));
@@ -598,14 +596,11 @@ struct m2m_ctx {
     FitDev fd{};
     FitDev* fd_dev = nullptr;
     FitState* st = nullptr;
-    Tile* tiles = nullptr;
-    FinJob* jobs = nullptr;
     int n_tiles = 0;
     // more tiles, and rows for them outside the workspace while it steps alone
     int wide_tiles = 0;
     double* wide = nullptr;
     size_t wide_bytes = 0;
-    int n_jobs = 0;
     size_t lds = 0;
     int block = 256, kin = 0;
     bool acc64 = true;
@@ -769,9 +764,11 @@ void split_tiles(int64_t n, int count, int fit, int row0, std::vector<Tile>& out
     for (int t = 0; t < count; ++t) out.push_back(tile_of(n, t, count, fit, row0));
 }
 
-void fin_jobs(const WsLayout& w, int fit, int n_rows, std::vector<FinJob>& out) {
-    for (int b = 0; b < std::max(w.nbj, w.ncj); ++b)
-        out.push_back(FinJob{fit, 0, b * kFinCols, n_rows});
+void fin_jobs(const WsLayout& w, int32_t every, int fit, int n_rows, std::vector<FinJob>& out) {
+    const int own = cells_apart(every) ? w.nbj : column_jobs(w.nbj, w.ncj, every);
+    for (int b = 0; b < own; ++b) out.push_back(FinJob{fit, 0, b * kFinCols, n_rows});
+    for (int b = own; b < column_jobs(w.nbj, w.ncj, every); ++b)
+        out.push_back(FinJob{fit, 1, (b - own) * kFinCols, n_rows});
     for (int b = 0; b < w.npj; ++b) out.push_back(FinJob{fit, 2, b * kFinCols, n_rows});
 }
 
@@ -803,7 +800,7 @@ m2m_status flush_assign(m2m_ctx* c) {
     m2m_status r = read_state(c, s);
     if (r != M2M_OK) return r;
     if (s.assign_pending) {
-        M2M_HIP(c, launch_assign(c->f64, c->fd_dev, c->tiles, c->n_tiles, c->stream));
+        M2M_HIP(c, launch_assign(c->f64, c->fd_dev, c->wide_tiles, c->stream));
         if ((r = sync(c)) != M2M_OK) return r;
     }
     c->may_assign = false;
@@ -1404,8 +1401,6 @@ m2m_status m2m_create(const m2m_potential* pot, const m2m_obs_layout* layout,
     f.q = -std::expm1(-c->par.alpha * dt);
     c->fd_dev = reinterpret_cast<FitDev*>(b + w.fd);
     c->st = f.st;
-    c->tiles = reinterpret_cast<Tile*>(b + w.tiles);
-    c->jobs = reinterpret_cast<FinJob*>(b + w.jobs);
     // ---- run kernel: one block of it per compute unit has to fit
     if (hipGetDevice(&c->dev) != hipSuccess) return bail(M2M_EDEVICE);
     c->run_sh = run_shape(n, c->f64, w.J);
@@ -1463,17 +1458,9 @@ m2m_status m2m_create(const m2m_potential* pot, const m2m_obs_layout* layout,
 
     // ---- tiles of this fit alone
     const int target = std::max(1, g_tiles_per_cu * n_cus());
-    const int count = std::max(1, std::min(w.seg_lean, target));
+    c->n_tiles = std::max(1, std::min(w.seg_lean, target));
     c->wide_tiles = std::max(1, std::min(w.seg_cap, target));
-    std::vector<Tile> tl;
-    split_tiles(n, count, 0, 0, tl);
-    std::vector<FinJob> jb;
-    fin_jobs(w, 0, count, jb);
-    c->n_tiles = (int)tl.size();
-    c->n_jobs = (int)jb.size();
-    if (copy_sync(c->stream, c->tiles, tl.data(), sizeof(Tile) * tl.size(), hipMemcpyHostToDevice) != hipSuccess ||
-        copy_sync(c->stream, c->jobs, jb.data(), sizeof(FinJob) * jb.size(), hipMemcpyHostToDevice) != hipSuccess ||
-        copy_sync(c->stream, c->fd_dev, &f, sizeof(FitDev), hipMemcpyHostToDevice) != hipSuccess)
+    if (copy_sync(c->stream, c->fd_dev, &f, sizeof(FitDev), hipMemcpyHostToDevice) != hipSuccess)
         return bail(M2M_EDEVICE);
     count_context(1);
     if (c->run) join_gate(c->dev, &c->run_owner, c->stream);
@@ -1580,10 +1567,12 @@ m2m_status m2m_update_priors(m2m_ctx* c) {
     if (m2m_status w_ = after_batch(c); w_ != M2M_OK) return w_;
     if (c->par.entropy != M2M_S_MPR) return fail(c, M2M_EINVAL, "moving priors need M2M_S_MPR");
     c->may_assign = true;
-    const Rows r = rows_of(c, !capturing(c->stream));
+    const bool captured = capturing(c->stream);
+    if (!captured) ensure_wide(c);
+    const Rows r = rows_of(c, !captured);
     M2M_HIP(c, launch_step1(c->f64, c->acc64, c->block, c->kin, r.f, r.n, c->lds, kModeCells, c->stream));
     M2M_HIP(c, launch_finalize1(c->f64, r.f, r.n, kModeCells, c->stream));
-    M2M_HIP(c, launch_assign(c->f64, c->fd_dev, c->tiles, c->n_tiles, c->stream));
+    M2M_HIP(c, launch_assign(c->f64, c->fd_dev, c->wide_tiles, c->stream));
     return M2M_OK;
 }
 
@@ -2156,7 +2145,7 @@ m2m_status fill_set(m2m_batch* b, LaunchSet& L, const std::vector<int>& members,
         if (whole)
             jb.push_back(FinJob{(int)f, kFinWholeFit, 0, cnts[f]});
         else
-            fin_jobs(c->w, (int)f, cnts[f], jb);
+            fin_jobs(c->w, c->par.prior_every, (int)f, cnts[f], jb);
         lds = std::max(lds, c->lds);
     }
     const m2m_status copied = copy_tables(

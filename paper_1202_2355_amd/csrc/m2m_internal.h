@@ -167,10 +167,17 @@ __host__ __device__ inline Tile tile_of(int64_t n, int t, int count, int fit, in
 constexpr int32_t kFinWholeFit = 3;
 struct FinJob {
     int32_t fit;
-    int32_t kind;  // 0: observable and cell columns, 2: potential columns, 3: all
+    int32_t kind;  // 0: observable and cell columns, 1: cell columns, 2: potential columns, 3: all
     int32_t col0;
     int32_t n_tiles;  // rows of the fit to reduce
 };
+
+// Fits whose cell columns have jobs of their own (kind 1, after those of kind 0), and
+// the observable and cell jobs of a fit.
+__host__ __device__ inline bool cells_apart(int32_t prior_every) { return prior_every == 1; }
+__host__ __device__ inline int column_jobs(int nbj, int ncj, int32_t prior_every) {
+    return cells_apart(prior_every) ? nbj + ncj : (nbj > ncj ? nbj : ncj);
+}
 
 // ---- run kernel (m2m_run.h): several steps of one fit in one launch ---------
 constexpr int kRunCols = 16;        // columns per reduction job
@@ -307,8 +314,7 @@ size_t smooth_basis_len(int nE, int nx);
 // Compute it (or take it from the process-wide cache of grid shapes) into
 // out; false if the eigen-iteration does not converge.
 bool smooth_basis(int nE, int nx, double hE, double hx, double* out);
-hipError_t launch_assign(bool f64, const FitDev* fits, const Tile* tiles, int n_tiles,
-                         hipStream_t s);
+hipError_t launch_assign(bool f64, const FitDev* fit, int blocks, hipStream_t s);
 hipError_t launch_weights(bool f64, const void* u, void* w, int64_t n, double scale,
                           hipStream_t s);
 hipError_t launch_poke(FitState* st, int32_t steps_left, int32_t correct, hipStream_t s);
