@@ -396,7 +396,8 @@ m2m_status m2m_get_launch(int32_t* block, int32_t* tiles_per_cu);
 
 /* Most private copies of the in-tile observable bins per block of the step
  * kernel, for contexts created afterwards: 1, 2, 4 or 8, or 0 (default) for
- * as many as fit 48 KiB of LDS, at most 8. Lanes add into copy
+ * as many as fit 48 KiB of LDS (112 KiB for spherical harmonics of 2^18 and more
+ * FP32 particles with blocks of 1024 threads), at most 8. Lanes add into copy
  * (thread index mod copies), which spreads the LDS atomics of a hot bin.
  * EINVAL otherwise. Chosen by the autotuner. */
 m2m_status m2m_set_private_copies(int32_t copies);

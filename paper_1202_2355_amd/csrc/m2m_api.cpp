@@ -34,6 +34,14 @@ constexpr int kBatchProfileMax = 256;  // most steps one m2m_batch_profile call 
 constexpr size_t kWholeFitMaxBytes = size_t(1) << 20;
 constexpr int kWholeFitMaxJobs = 8;  // columns / kFinCols
 constexpr size_t kWholeFitMinFits = 24;
+// Column jobs take 16 waves where all fits of a batch together have at most this many,
+// as then 4 waves have 32 rows each to add and more, else 4, which find a place
+// beside the other group's step kernel sooner. Measured us a step, 4 waves / 16,
+// harmonics with Gauss-Hermite and 2 copies of the bins: 2 fits of 262144, l = 4 (52
+// jobs) 53.5 / 42.7, 3 of 3e5 (78) 66.0 / 60.5, 3 of 3e5, l = 3 (51) 93.9 / 85.9;
+// but 4 of 1e6 (104) 197 / 206, 12 of 3e5 (312) 182 / 193; 20 Gauss-Hermite fits of 3e5
+// (320) 74 / 82.
+constexpr int kFinWideJobs = 80;
 constexpr uint32_t kStateMagic = 0x4d324d31u;  // "M2M1"
 constexpr uint32_t kStateVersion = 2u;         // 2: with the FP64 prior grid
 constexpr double kPi = 3.14159265358979323846;
@@ -1897,7 +1905,7 @@ struct LaunchSet {
     FinJob* jobs_dev = nullptr;
     double* rows_dev = nullptr;  // tile rows of fits that have more than their workspaces hold
     size_t cap_fits = 0, cap_tiles = 0, cap_jobs = 0, cap_rows = 0;
-    int n_tiles = 0, n_jobs = 0, n_fits = 0;
+    int n_tiles = 0, n_jobs = 0;
     bool whole = false;  // one whole-fit finalize job per fit (else column jobs)
     bool nt = false;     // the fits' state together exceeds kStreamMin (kModeStream)
     size_t lds = 0;
@@ -1937,6 +1945,7 @@ struct m2m_batch {
     int block = 256, kin = -1;
     bool acc64 = true;
     bool smooth = false;  // some fit smooths its prior grid
+    bool fin_wide = false;  // column jobs of 16 waves (kFinWideJobs)
     bool graphs = false;  // steps replayed from captured graphs (else launched directly)
     // the fits step by the run kernel (run_fits): its tables and launch shape
     bool run = false, run_many = false;
@@ -1969,8 +1978,8 @@ hipError_t batch_step(const m2m_batch* b, const LaunchSet& L, bool f64, hipStrea
     hipError_t e = launch_step(f64, b->acc64, b->block, b->kin, L.fits_dev, L.tiles_dev, L.n_tiles,
                                L.lds, kModeStep | (L.nt ? kModeStream : 0), s);
     if (e == hipSuccess)
-        e = launch_finalize(f64, L.fits_dev, L.n_fits, L.jobs_dev, L.n_jobs, kModeStep, s,
-                            kin_scf(b->kin), b->smooth, L.whole);
+        e = launch_finalize(f64, L.fits_dev, L.jobs_dev, L.n_jobs, kModeStep, s,
+                            kin_scf(b->kin), b->smooth, L.whole, b->fin_wide);
     return e;
 }
 
@@ -2083,7 +2092,7 @@ m2m_status fill_set(m2m_batch* b, LaunchSet& L, const std::vector<int>& members,
         (void)hipGraphExecDestroy(L.graph);
         L.graph = nullptr;
     }
-    L.n_tiles = L.n_jobs = L.n_fits = 0;
+    L.n_tiles = L.n_jobs = 0;
     if (members.empty()) return M2M_OK;
     const bool f64 = b->f64 == 1;
     std::vector<FitDev> fd;
@@ -2156,7 +2165,6 @@ m2m_status fill_set(m2m_batch* b, LaunchSet& L, const std::vector<int>& members,
     if (copied != M2M_OK) return copied;
     L.n_tiles = (int)tl.size();
     L.n_jobs = (int)jb.size();
-    L.n_fits = (int)fd.size();
     L.whole = whole;
     size_t state = 0;
     for (int m : members) state += (size_t)b->fits[m]->n * 8 * (f64 ? 8 : 4);
@@ -2268,7 +2276,7 @@ m2m_status rebuild(m2m_batch* b) {
         for (LaunchSet* L : {&b->all, &b->grp[0], &b->grp[1]}) {
             if (L->graph) (void)hipGraphExecDestroy(L->graph);
             L->graph = nullptr;
-            L->n_tiles = L->n_jobs = L->n_fits = 0;
+            L->n_tiles = L->n_jobs = 0;
         }
         b->run = false;
         b->dirty = false;
@@ -2282,6 +2290,9 @@ m2m_status rebuild(m2m_batch* b) {
     std::vector<int> every(nf);
     for (int f = 0; f < nf; ++f) every[f] = f;
     b->graphs = g_batch_graphs != 0;
+    int jobs = 0;
+    for (const m2m_ctx* c : b->fits) jobs += column_jobs(c->w.nbj, c->w.ncj, c->par.prior_every) + c->w.npj;
+    b->fin_wide = jobs <= kFinWideJobs;
     m2m_status s = fill_set(b, b->all, every, b->graphs && b->n_groups == 1);
     if (s != M2M_OK) return s;
     if (b->n_groups > 1) {
@@ -2572,8 +2583,8 @@ m2m_status m2m_batch_profile(m2m_batch* b, int32_t n_steps, double* ms_step, dou
                             b->stream);
         if (e == hipSuccess) e = hipEventRecord(ev[2 * k + 1], b->stream);
         if (e == hipSuccess)
-            e = launch_finalize(f64, b->all.fits_dev, b->all.n_fits, b->all.jobs_dev, b->all.n_jobs,
-                                kModeStep, b->stream, kin_scf(b->kin), b->smooth, b->all.whole);
+            e = launch_finalize(f64, b->all.fits_dev, b->all.jobs_dev, b->all.n_jobs,
+                                kModeStep, b->stream, kin_scf(b->kin), b->smooth, b->all.whole, b->fin_wide);
     }
     if (e == hipSuccess) e = hipEventRecord(ev[2 * (size_t)n_steps], b->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(b->stream);

@@ -287,9 +287,9 @@ hipError_t launch_step(bool f64, bool acc64, int block, int kin, const FitDev* f
 // smooth: some fit of the launch smooths its prior grid (the variant with the
 // smoothing's LDS grids); whole: every job is a whole-fit job (one block per
 // fit, the kernel with small blocks), else every job is a column job
-hipError_t launch_finalize(bool f64, const FitDev* fits, int n_fits, const FinJob* jobs,
-                           int n_jobs, int32_t mode, hipStream_t s, bool scf, bool smooth,
-                           bool whole);
+// wide: column jobs of 16 waves (else 4)
+hipError_t launch_finalize(bool f64, const FitDev* fits, const FinJob* jobs, int n_jobs, int32_t mode,
+                           hipStream_t s, bool scf, bool smooth, bool whole, bool wide);
 bool kin_scf(int kin);
 // the step kernel of one particle-state / in-tile-sum type pair (one == nullptr:
 // over the fit and tile tables, else over that one fit); m2m_step_*.hip

@@ -818,7 +818,8 @@ size_t step_lds_bytes(bool f64, bool acc64, int J, int n_r, int n_R, int n_v, in
 // harmonics: the adds of 64 lanes to one (l, m) of their mesh intervals collide). l = 4
 // with Gauss-Hermite (1620 observables), 2 copies / 8, us a step: 1e6 particles
 // 62.2 / 50.5, 6e5 43.9 / 38.5, 3e5 30.1 / 28.9, 1e5 20.9 / 22.1 (the copies are
-// cleared and added once per tile).
+// cleared and added once per tile). In batches too, whatever the tiles: 3 fits of 3e5
+// at one tile a compute unit 66 / 55, at six 70 / 65; 12 of 3e5 182 / 139 and 209 / 181.
 int private_copies(int J, size_t bytes) {
     int k = 8;
     while (k > 1 && 8 * (size_t)J * (size_t)k > bytes) k >>= 1;
@@ -849,9 +850,29 @@ hipError_t launch_step1(bool f64, bool acc64, int block, int kin, const FitDev& 
 namespace {
 constexpr int kFitWaves = 4;  // waves of a batch's finalize blocks without smoothing
 
+template <bool SCF, bool SMOOTH, int NW>
+void launch_fin_waves(bool f64, const FitDev* fits, const FinJob* jobs, int n_blocks, int32_t mode,
+                      hipStream_t s) {
+    if (f64)
+        hipLaunchKernelGGL((k_finalize<double, SCF, SMOOTH, NW>), dim3(n_blocks), dim3(NW * 64), 0, s,
+                           fits, jobs, mode);
+    else
+        hipLaunchKernelGGL((k_finalize<float, SCF, SMOOTH, NW>), dim3(n_blocks), dim3(NW * 64), 0, s,
+                           fits, jobs, mode);
+}
+
+template <bool SCF, bool SMOOTH>
+void launch_fin_jobs(bool f64, const FitDev* fits, const FinJob* jobs, int n_blocks, bool wide,
+                     int32_t mode, hipStream_t s) {
+    if (SMOOTH || wide)
+        launch_fin_waves<SCF, SMOOTH, kFinWaves>(f64, fits, jobs, n_blocks, mode, s);
+    else
+        launch_fin_waves<SCF, SMOOTH, SMOOTH ? kFinWaves : kFitWaves>(f64, fits, jobs, n_blocks, mode, s);
+}
+
 template <bool SCF, bool SMOOTH>
 hipError_t launch_fin_t(bool f64, const FitDev* fits, const FinJob* jobs, const FitDev* one,
-                        int n_blocks, int n_rows, int32_t mode, hipStream_t s, bool whole) {
+                        int n_blocks, int n_rows, int32_t mode, hipStream_t s, bool whole, bool wide) {
     if (one) {
         if (f64)
             hipLaunchKernelGGL((k_finalize1<double, SCF, SMOOTH>), dim3(n_blocks), dim3(kFinThreads), 0,
@@ -868,34 +889,26 @@ hipError_t launch_fin_t(bool f64, const FitDev* fits, const FinJob* jobs, const 
             hipLaunchKernelGGL((k_finalize_fits<float, SCF, SMOOTH, NW>), dim3(n_blocks),
                                dim3(NW * 64), 0, s, fits, jobs, mode);
     } else {
-        constexpr int NW = SMOOTH ? kFinWaves : kFitWaves;
-        if (f64)
-            hipLaunchKernelGGL((k_finalize<double, SCF, SMOOTH, NW>), dim3(n_blocks), dim3(NW * 64), 0,
-                               s, fits, jobs, mode);
-        else
-            hipLaunchKernelGGL((k_finalize<float, SCF, SMOOTH, NW>), dim3(n_blocks), dim3(NW * 64), 0,
-                               s, fits, jobs, mode);
+        launch_fin_jobs<SCF, SMOOTH>(f64, fits, jobs, n_blocks, wide, mode, s);
     }
     return hipGetLastError();
 }
 
 hipError_t launch_fin_any(bool f64, bool scf, bool smooth, const FitDev* fits, const FinJob* jobs,
                           const FitDev* one, int n_blocks, int n_rows, int32_t mode, hipStream_t s,
-                          bool whole) {
+                          bool whole, bool wide) {
     if (n_blocks <= 0) return hipSuccess;
     if (scf && smooth)
-        return launch_fin_t<true, true>(f64, fits, jobs, one, n_blocks, n_rows, mode, s, whole);
-    if (scf) return launch_fin_t<true, false>(f64, fits, jobs, one, n_blocks, n_rows, mode, s, whole);
-    if (smooth) return launch_fin_t<false, true>(f64, fits, jobs, one, n_blocks, n_rows, mode, s, whole);
-    return launch_fin_t<false, false>(f64, fits, jobs, one, n_blocks, n_rows, mode, s, whole);
+        return launch_fin_t<true, true>(f64, fits, jobs, one, n_blocks, n_rows, mode, s, whole, wide);
+    if (scf) return launch_fin_t<true, false>(f64, fits, jobs, one, n_blocks, n_rows, mode, s, whole, wide);
+    if (smooth) return launch_fin_t<false, true>(f64, fits, jobs, one, n_blocks, n_rows, mode, s, whole, wide);
+    return launch_fin_t<false, false>(f64, fits, jobs, one, n_blocks, n_rows, mode, s, whole, wide);
 }
 }  // namespace
 
-hipError_t launch_finalize(bool f64, const FitDev* fits, int n_fits, const FinJob* jobs,
-                           int n_jobs, int32_t mode, hipStream_t s, bool scf, bool smooth,
-                           bool whole) {
-    (void)n_fits;
-    return launch_fin_any(f64, scf, smooth, fits, jobs, nullptr, n_jobs, 0, mode, s, whole);
+hipError_t launch_finalize(bool f64, const FitDev* fits, const FinJob* jobs, int n_jobs, int32_t mode,
+                           hipStream_t s, bool scf, bool smooth, bool whole, bool wide) {
+    return launch_fin_any(f64, scf, smooth, fits, jobs, nullptr, n_jobs, 0, mode, s, whole, wide);
 }
 
 bool kin_scf(int kin) { return (kin & kKinScf) != 0; }
@@ -903,7 +916,7 @@ bool kin_scf(int kin) { return (kin & kKinScf) != 0; }
 hipError_t launch_finalize1(bool f64, const FitDev& fd, int n_rows, int32_t mode, hipStream_t s) {
     const int n_jobs = column_jobs(fd.n_bin_jobs, fd.n_cell_jobs, fd.prior_every) + fd.n_pot_jobs;
     return launch_fin_any(f64, fd.scf_nr > 0, fd.smooth != 0, nullptr, nullptr, &fd, n_jobs, n_rows,
-                          mode, s, false);
+                          mode, s, false, false);
 }
 
 hipError_t launch_assign(bool f64, const FitDev* fit, int blocks, hipStream_t s) {
