@@ -914,8 +914,7 @@ void ensure_wide(m2m_ctx* c) {
         take_memory(c->dev, g, 8 * (size_t)c->wide_tiles * (size_t)c->w.row_len, &c->wide_bytes));
 }
 
-// gives them back; no work of the fit is in flight, and (drop_wide) no graph of
-// its steps is used again
+// gives them back; no work of the fit is in flight
 void give_wide(m2m_ctx* c) {
     if (!c->wide) return;
     RunGate& g = g_run_gate[c->dev];
@@ -924,6 +923,7 @@ void give_wide(m2m_ctx* c) {
     c->wide = nullptr;
 }
 
+// the same of a fit that has stepped, with the graphs that use them
 void drop_wide(m2m_ctx* c) {
     if (!c->wide) return;
     for (hipGraphExec_t* x : {&c->graph, &c->graph_prof}) {
@@ -1537,7 +1537,8 @@ m2m_status m2m_step(m2m_ctx* c, int32_t n_steps, int32_t correct) {
     const bool captured = capturing(c->stream);
     if (!captured) ensure_wide(c);
     M2M_HIP(c, launch_poke(c->st, n_steps, correct ? 1 : 0, c->stream));
-    const int full = captured && c->wide ? 0 : n_steps / kGraphSteps, rem = n_steps - full * kGraphSteps;
+    // a capture does not record the launch of another graph
+    const int full = captured ? 0 : n_steps / kGraphSteps, rem = n_steps - full * kGraphSteps;
     if (full > 0) {
         m2m_status s = ensure_graph(c);
         if (s != M2M_OK) return s;

@@ -453,18 +453,22 @@ def test_a_batch_counts_state_and_workspace(oracle, Fit):
             f.close()
 
 
-def test_steps_in_a_graph_outlive_the_rows_of_a_fit_alone(oracle, Fit):
-    """Steps recorded into a caller's graph after eager steps (which take rows
-    outside the workspace), replayed when the fit has been in a batch."""
+@pytest.mark.parametrize("first", ["eager", "captured"])
+def test_steps_in_a_graph_outlive_the_rows_of_a_fit_alone(oracle, Fit, first):
+    """Steps recorded into a caller's graph before or after eager steps (which take
+    rows outside the workspace), replayed when the fit has been in a batch."""
     from paper_1202_2355_amd.batch import Batch
-    _say("graph and batch")
+    _say("graph and batch", first)
     st = torch.cuda.Stream()
     a, b = _alm(oracle, Fit, 20_011), _alm(oracle, Fit, 20_011, stream=st)
-    b.step(3)
+    if first == "eager":
+        b.step(3)
     torch.cuda.synchronize()
     g = torch.cuda.CUDAGraph()
     with torch.cuda.graph(g, stream=st):
         b.step(35)
+    if first == "captured":
+        b.step(3)
     a.step(3)
     for _ in range(2):
         q = Batch(max_fits=1, stream=st)
@@ -485,5 +489,31 @@ def test_steps_in_a_graph_outlive_the_rows_of_a_fit_alone(oracle, Fit):
         torch.cuda.synchronize()
         _same(a, b, "f32")
         other.close()
+    a.close()
+    b.close()
+
+
+@pytest.mark.parametrize("kin,n", [("v2", 9001), ("alm", 20_011)])
+def test_long_calls_captured_into_a_graph(oracle, Fit, kin, n):
+    """Calls of 32 steps and more (which a fit takes by graphs of its own, or by runs)
+    recorded into a caller's graph, with eager steps between the replays."""
+    _say("long captured calls", kin)
+    st = torch.cuda.Stream()
+    make = (lambda **k: _alm(oracle, Fit, n, **k)) if kin == "alm" else (
+        lambda **k: _made(oracle, Fit, kin, "f64", n, **k))
+    a, b = make(), make(stream=st)
+    b.step(1)
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g, stream=st):
+        b.step(70)
+    a.step(1)
+    for _ in range(3):
+        with torch.cuda.stream(st):
+            g.replay()
+        b.step(33)
+        a.step(103)
+        torch.cuda.synchronize()
+        np.testing.assert_allclose(b.chi2_history(), a.chi2_history(), rtol=1e-4 if kin == "alm" else 1e-9)
     a.close()
     b.close()
