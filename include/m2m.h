@@ -227,7 +227,7 @@ int32_t m2m_num_observables(const m2m_obs_layout* layout);
 /* Bytes of device workspace a context needs for n particles. Besides it the library
  * may hold, on each stream on which fits step many steps per launch (see
  * m2m_step), one piece of exchange memory as large as its largest launch needs (at
- * most 52 MiB for a fit), and at most 16 MiB of tile rows for a small fit that steps
+ * most 64 MiB), and at most 16 MiB of tile rows for a small fit that steps
  * alone one launch per step; these come from few pieces that are kept while any
  * context exists. */
 size_t m2m_workspace_bytes(const m2m_obs_layout* layout, const m2m_params* params, int64_t n,

@@ -365,6 +365,8 @@ int seg_cap_of(int64_t n, int row_len, bool dear) {
 // kernels / run kernel: FP32 2e4 particles 13.8 / 10.9, 1e5 14.8 / 10.2, 8e5 20.9 /
 // 17.7, 4e6 51.2 / 44.6, FP64 1e5 23.3 / 13.8, 8e5 43.3 / 29.1; a call of one, two, four
 // steps of 1e5 FP32 particles 27.8 / 32.0, 42.4 / 41.0, 74.9 / 59.3.
+// At kRunMaxN both gain (4e6 above); no larger fit has been measured, so the line is
+// not known to be where the gain ends.
 constexpr int kRunMaxJ = 4096;
 constexpr int kRunShortJ = 1024;
 constexpr int64_t kRunMaxN = int64_t(1) << 22;
@@ -556,10 +558,9 @@ void put_obs_tables(unsigned char* img, const WsLayout& w, const m2m_obs_layout&
 // at any time), and nothing but runs is waited for.
 //
 // The blocks of a run exchange through memory of its stream (its runs come one
-// after another), made at the first and as large as the largest needs, up to 52 MiB
-// for a fit and 256 blocks of 12288 columns for a batch. In the fits' workspaces
-// it would be many times the rest: 17.6 MB for 4001 particles of the LOSVD layout
-// (0.13 MB of state).
+// after another), made at the first and as large as the largest needs, in powers of two up
+// to 64 MiB (256 blocks of 12288 columns). In the fits' workspaces it would be many
+// times the rest: 17.6 MB for 4001 particles of the LOSVD layout (0.13 MB of state).
 struct StreamArea {
     hipStream_t stream = nullptr;
     int users = 0;                // contexts and batches
@@ -731,7 +732,7 @@ bool any_context() {
     return g.contexts > 0;
 }
 constexpr int kRunDevices = 64;
-RunGate g_run_gate[kRunDevices];
+RunGate* const g_run_gate = new RunGate[kRunDevices];  // never destroyed: contexts may outlive statics
 void free_idle_memory();
 void count_context(int d) {
     PinPool& g = pins();
@@ -884,7 +885,9 @@ void leave_memory(RunGate& g, unsigned char* p, size_t bytes) {
     (void)hipFree(p);
 }
 void free_idle_memory() {
-    for (RunGate& g : g_run_gate) {
+    const CaptureRelaxed relaxed;
+    for (int d = 0; d < kRunDevices; ++d) {
+        RunGate& g = g_run_gate[d];
         std::lock_guard<std::mutex> lock(g.mu);
         for (auto& m : g.idle) (void)hipFree(m.first);
         g.idle.clear();
@@ -1068,11 +1071,11 @@ int place_run(const RunGate& g, const RunOwner* o, int blocks) {
 // go(done, mem, tag0) launches the owner's run of `blocks` blocks and n_steps steps with
 // `bytes` of exchange memory, which completes the event `done` (NULL: none is
 // needed), after the runs whose slots it takes. hipErrorOutOfMemory, with nothing
-// launched, if there is no such memory. While all
-// owners are on one stream, no run carries an event: it costs a launch 3 us (64 steps
-// of a batch 504.0 us without, 508.6 with). So runs already in flight when the first
-// owner on another stream comes are not waited for; blocks that cannot start
-// beside them are what the launch's call-off is for.
+// launched, if there is no such memory. While all owners are on one stream, no run
+// carries an event: it costs a launch 3 us (64 steps of a batch 504.0 us without,
+// 508.6 with). So runs already in flight when the first owner on another stream comes
+// are not waited for; blocks that cannot start beside them are what the launch's
+// call-off is for.
 template <typename F>
 hipError_t ordered_run(int dev, RunOwner* o, int blocks, int32_t n_steps, size_t bytes, F&& go) {
     RunGate& g = g_run_gate[dev];

@@ -1,8 +1,10 @@
 // The run kernel: several whole steps of one fit in one launch (its launch shape is
-// run_shape in m2m_internal.h). A block keeps its particles for the whole launch (in registers where every thread has at
-// most one, else in its L2) and the blocks exchange only the tile sums: the
-// force of change of step k + 1 needs the residuals of step k, and nothing
-// else crosses blocks.
+// run_shape in m2m_internal.h). A block has the same particles for the whole launch,
+// in registers where every thread has at most one; with more they are read and
+// written every step, in the 4 MB L2 of the block's XCD or, above about 10^6 FP32
+// particles, the 256 MB memory-side cache. The blocks exchange only the tile sums: the
+// force of change of step k + 1 needs the residuals of step k, and nothing else
+// crosses blocks.
 #pragma once
 
 #include <hip/hip_ext.h>
