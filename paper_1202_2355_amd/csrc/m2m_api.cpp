@@ -1659,9 +1659,9 @@ m2m_status m2m_observe(m2m_ctx* c, const double* V_p, const double* sigma_p, dou
     std::vector<unsigned char> own(pin.p ? 0 : tab);
     unsigned char* t = pin.p ? static_cast<unsigned char*>(pin.p) + obs : own.data();
     // rows outside the workspace for the length of the call
-    const bool lend = !c->wide && !capturing(c->stream);
+    const bool captured = capturing(c->stream), lend = !c->wide && !captured;
     if (lend) ensure_wide(c);
-    auto [f, n_tiles] = rows_of(c, !capturing(c->stream));
+    auto [f, n_tiles] = rows_of(c, !captured);
     struct Lent {
         m2m_ctx* c;
         ~Lent() {
