@@ -270,11 +270,12 @@ m2m_status m2m_set_targets(m2m_ctx* ctx, int32_t J, const double* Y, const doubl
  * launch: one kernel whose blocks exchange their sums. Its blocks wait for each
  * other, so such launches on different streams of one device are ordered one
  * after another where they need more than 256 blocks together (and after
- * nothing else on those streams). If the stream
- * may not use as many compute units as the launch has blocks (one per 1024
- * particles, or per 16 observables, at most 256), or if it is being captured, the steps are launched one by one (two kernels each) as
- * for all other fits. A launch whose blocks do not all start within 50 ms (the
- * compute units are held by other work) is done by the blocks that did. */
+ * nothing else on those streams). If the stream may not use as many compute
+ * units as the launch has blocks (one per 1024 particles, or per 16 observables,
+ * at most 256), or if it is being captured, the steps are launched one by one
+ * (two kernels each) as for all other fits. A launch whose blocks do not all
+ * start within 50 ms (the compute units are held by other work) is done by the
+ * blocks that did. */
 m2m_status m2m_step(m2m_ctx* ctx, int32_t n_steps, int32_t correct);
 
 /* Recompute the cell priors from the current state now (Sec. 2.3.1) and
