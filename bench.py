@@ -286,7 +286,7 @@ def run_serve(args, torch, rate=SERVE_RATE):
     tdt = torch.float32 if args.state == "f32" else torch.float64
     model = lambda r: plummer_jeans_device(r.n, r.potential, r.seed, dtype=tdt)
     from paper_1202_2355_amd import tuning
-    tuning.use("batch", args.state, base.layout)
+    tuning.use("serve", args.state, base.layout)
     srv = Server(datasets, hbm_budget=int(args.hbm_gb * 2 ** 30), max_fits=args.max_fits,
                  steps_per_launch=args.steps_per_launch, dtype=args.state, initial_model=model,
                  preparers=args.preparers)

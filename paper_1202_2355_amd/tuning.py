@@ -1,8 +1,8 @@
 """Launch parameters of the step kernel per workload class, as the autotuner
 (``autotune.py``) picked them on an MI355X, and their application.
 
-A class is the kind of run (one fit, or a batch of fits), the particle-state
-type, the kind of kinematic observables and, for one fit, the order of
+A class is the kind of run (one fit, a batch of fits, or a batch that a server
+keeps full while it prepares and finishes others), the particle-state type, the kind of kinematic observables and, for one fit, the order of
 magnitude of its particle count. Its parameters are the step kernel's block
 size and tiles per compute unit, the in-tile deposit mode, the most private
 bin copies per block, and for batches the number of overlapping groups and
@@ -28,11 +28,12 @@ DEFAULT_F64 = dict(DEFAULT, block=256)
 
 
 def class_key(mode: str, dtype: str, layout: dict, n: int | None = None) -> str:
-    """'single:<dtype>:<kin>:<log10 N>' or 'batch:<dtype>:<kin>'; kin carries
-    '+alm' for spherical-harmonic density observables."""
+    """'single:<dtype>:<kin>:<log10 N>', 'batch:<dtype>:<kin>' or
+    'serve:<dtype>:<kin>'; kin carries '+alm' for spherical-harmonic density
+    observables."""
     kin = layout["kin"] + ("+alm" if layout.get("dens") == "alm" else "")
-    if mode == "batch":
-        return f"batch:{dtype}:{kin}"
+    if mode in ("batch", "serve"):
+        return f"{mode}:{dtype}:{kin}"
     if mode != "single":
         raise ValueError(mode)
     return f"single:{dtype}:{kin}:{int(round(math.log10(max(int(n), 1))))}"
@@ -48,12 +49,15 @@ def load(path: str = TUNED_FILE) -> dict:
 
 def lookup(mode: str, dtype: str, layout: dict, n: int | None = None, table=None) -> dict:
     """The tuned parameters of the class, else those of the nearest tuned
-    size of the same run kind, state type and kinematics, else defaults."""
+    size of the same run kind, state type and kinematics (for a server those
+    of the batch), else defaults."""
     table = load() if table is None else table
     base = DEFAULT_F64 if dtype == "f64" else DEFAULT
     key = class_key(mode, dtype, layout, n)
     if key in table:
         return dict(base, **table[key]["params"])
+    if mode == "serve":
+        return lookup("batch", dtype, layout, n, table)
     if mode == "single":
         stem, mag = key.rsplit(":", 1)
         near = [(abs(int(k.rsplit(":", 1)[1]) - int(mag)), k) for k in table
